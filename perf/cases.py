@@ -253,3 +253,64 @@ def tolerance(case):
     if case["out"] == "bf16" and case["call"] != "update":
         tol = {"rel": 1.5e-4, "max": 1.6e-2}
     return tol
+
+
+def exact(case, seed):
+    """The same pass in 64 bits, from the inputs that prepare() makes: Algorithm 1 inside Algorithm 2 matrix by matrix
+    with torch's own products (a column whose squared norm is <= 1e-30 when its turn comes is zero)."""
+    s = prepare(case, seed)
+    plan, W, call = s["plan"], case["workers"], case["call"]
+    z = plan.sizes
+    g = s["grad"].view(W, z.grad_stride)
+    e = s["err"].view(W, z.err_stride)
+    err = torch.zeros(e.shape, dtype=torch.float64, device=e.device)
+    out = torch.zeros(z.out_elems, dtype=torch.float64, device=e.device)
+    sparse = call in ("random_k", "random_block")
+    q, p = s["q"].double(), s["p"].double()
+    vals = s["vals"].double() if sparse else None
+    for t, shape in enumerate(shapes_of(case)):
+        off, p_off, q_off, r = plan.offsets(t)
+        if len(shape) == 1:
+            out[off: off + shape[0]] = g[:, off: off + shape[0]].double().mean(0)
+            continue
+        n, m = shape
+        M = g[:, off: off + n * m].double() + e[:, off: off + n * m].double()
+        if sparse:
+            at, b = plan.kept(t)
+            if call == "random_k":
+                keep = s["draw"][at: at + b]
+            else:
+                keep = torch.arange(int(s["draw"][t]), min(int(s["draw"][t]) + b, n * m), device=e.device)
+            mean = M[:, keep].mean(0)
+            vals[at: at + keep.numel()] = mean
+            out[off + keep] = mean
+            M[:, keep] -= mean
+            err[:, off: off + n * m] = M
+            continue
+        mean = M.mean(0).view(n, m)
+        Q = q[q_off: q_off + m * r].view(m, r)
+        for _ in range(case["iterations"]):
+            P = mean @ Q
+            for k in range(r):
+                for j in range(k):
+                    P[:, k] -= (P[:, j] @ P[:, k]) * P[:, j]
+                nn = float(P[:, k] @ P[:, k])
+                P[:, k] = P[:, k] / math.sqrt(nn) if nn > 1e-30 else 0.0
+            Q = mean.T @ P
+        q[q_off: q_off + m * r] = Q.reshape(-1)
+        p[p_off: p_off + n * r] = P.reshape(-1)
+        d = (P @ Q.T).reshape(-1)
+        out[off: off + n * m] = d
+        err[:, off: off + n * m] = M - d
+    if sparse:
+        return {"out": out, "err": err.view(-1), "vals": vals}
+    if call == "update":
+        mom = MOMENTUM * s["mom"].double() + out
+        live = torch.zeros(z.out_elems, dtype=torch.bool, device=e.device)
+        for t, shape in enumerate(shapes_of(case)):
+            off = plan.offsets(t)[0]
+            live[off: off + math.prod(shape)] = True
+        mom = torch.where(live, mom, s["mom"].double())
+        param = torch.where(live, s["param"].double() - LR * (out + mom), s["param"].double())
+        return {"param": param, "mom": mom, "err": err.view(-1), "q": q, "p": p}
+    return {"out": out, "err": err.view(-1), "q": q, "p": p}
