@@ -167,7 +167,9 @@ PSGD_API psgd_status psgd_plan_set_tuning(psgd_plan* plan, const char* key, int6
  *   hip_stream            a hipStream_t (NULL = the default stream)
  * Everything is enqueued on hip_stream; the call does not synchronise, allocate
  * or read back, except that a plan's first GPU call allocates and uploads its
- * descriptor tables (one hipMalloc, one synchronous copy).
+ * descriptor tables (one hipMalloc, one synchronous copy; from three workers on, on the
+ * kernels for rank <= 8, a second hipMalloc of 4 N bytes for the mean over the workers of
+ * M, without which, should it fail, each worker's M is multiplied by itself).
  * Vector-shaped tensors are not touched by this call. */
 PSGD_API psgd_status psgd_compress(psgd_plan* plan, const void* grad, float* err, float* q, float* p,
                           void* workspace, void* hip_stream);
@@ -201,8 +203,10 @@ PSGD_API psgd_status psgd_decompress(psgd_plan* plan, const float* p, const floa
  * psgd_plan_check (below) reports it and moves the plan to the kernels that
  * need no co-residency.  A caller that may share the GPU checks every step,
  * or sets the tuning keys resident = 0 and gram_fused = 0.
- * The plan's first GPU call (any entry point) uploads its tables (one device
- * allocation and copy).  After that this call, psgd_compress and psgd_decompress
+ * With three workers or more the streaming kernels also keep the mean over the
+ * workers of M in plan-owned memory (only where gram_fused holds).
+ * The plan's first GPU call (any entry point) uploads its tables (device
+ * allocations and one copy).  After that this call, psgd_compress and psgd_decompress
  * only launch kernels on hip_stream: no allocation, no memset, no host
  * synchronisation, so they may be captured into a HIP graph and replayed. */
 PSGD_API psgd_status psgd_step(psgd_plan* plan, const void* grad, float* err, float* q, float* p,
@@ -226,7 +230,7 @@ PSGD_API psgd_status psgd_iterate(psgd_plan* plan, float* err, float* q, float* 
  * every GPU it is loaded on (PSGD_STATIC_WORKSPACE_BYTES, part of the code object, kept until the process
  * ends).  The call allocates and frees nothing and otherwise behaves exactly like psgd_step with that workspace.
  * Conditions: the plan's tables are on the device already (psgd_plan_check, or any earlier GPU call on the plan,
- * puts them there; that upload is the one allocation a plan makes) - else PSGD_EINVAL; the plan's
+ * puts them there; that upload makes all the allocations of a plan) - else PSGD_EINVAL; the plan's
  * workspace_bytes fit - else PSGD_EUNSUPPORTED (the ResNet18-shaped set up to 16 workers and the LSTM-shaped set
  * fit, the 24-layer transformer-shaped set does not); the current device is the plan's.  All plans on a GPU share
  * the one array and it keeps whatever the last call left there (the kernels read nothing of it that they have
@@ -312,7 +316,7 @@ PSGD_API psgd_status psgd_plan_kernel_times(psgd_plan* plan, double* ms_sum, int
  * kernel trace (prefix of the symbol); NULL if out of range. */
 PSGD_API const char* psgd_kernel_name(int32_t index);
 
-/* A plan that has made no GPU call yet: uploads its tables (the plan's one device allocation) and returns.
+/* A plan that has made no GPU call yet: uploads its tables (the plan's only device allocations) and returns.
  * Otherwise waits for hip_stream, then returns PSGD_EHIP if a kernel of this plan whose
  * workgroups wait for each other (resident mode; the one-launch orthogonalisation
  * over row blocks) gave up waiting since the last check, PSGD_OK otherwise.

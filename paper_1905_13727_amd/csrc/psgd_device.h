@@ -136,15 +136,18 @@ __device__ __forceinline__ void buf_ldv(buf_rsrc r, unsigned off, float (&x)[V],
     }
 }
 template <int V>
-__device__ __forceinline__ void buf_stv(buf_rsrc r, unsigned off, const float (&x)[V]) {
+__device__ __forceinline__ void buf_stv(buf_rsrc r, unsigned off, const float (&x)[V], bool stream = false) {
     if constexpr (V == 4) {
         const v4u t{__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3])};
-        __builtin_amdgcn_raw_buffer_store_b128(t, r, (int)off, 0, 0);
+        if (stream) __builtin_amdgcn_raw_buffer_store_b128(t, r, (int)off, 0, 2);
+        else __builtin_amdgcn_raw_buffer_store_b128(t, r, (int)off, 0, 0);
     } else if constexpr (V == 2) {
         const v2u t{__float_as_uint(x[0]), __float_as_uint(x[1])};
-        __builtin_amdgcn_raw_buffer_store_b64(t, r, (int)off, 0, 0);
+        if (stream) __builtin_amdgcn_raw_buffer_store_b64(t, r, (int)off, 0, 2);
+        else __builtin_amdgcn_raw_buffer_store_b64(t, r, (int)off, 0, 0);
     } else {
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x[0]), r, (int)off, 0, 0);
+        if (stream) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x[0]), r, (int)off, 0, 2);
+        else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x[0]), r, (int)off, 0, 0);
     }
 }
 

@@ -908,7 +908,7 @@ psgd_status hr_compress(psgd_plan* plan, const void* grad, float* err, float* q,
     }
     HR_CHECK("launch k_hr_left");
     HR_MARK(3);
-    psgd_status st = launch_q_reduce(plan, ws, q, stream);
+    psgd_status st = launch_q_reduce(plan, ws, q, stream, plan->workers);
     if (st != PSGD_OK) return st;
     HR_MARK(4);
     return PSGD_OK;

@@ -23,6 +23,9 @@ constexpr int kPanelFloats = 12288;  // n*r up to this: Gram-Schmidt by one work
 constexpr int kGramRows = 256;     // rows per workgroup of the Gram / apply kernels (Cholesky-QR over row blocks)
 constexpr int kPreReduceParts = 16; // more partial-P slices than this: a reduction kernel runs before the orthogonalisation
 constexpr int kOrthoMaxRows = 1024; // largest value of the tuning key ortho_rows: panels with more rows always take the multi-workgroup route
+constexpr int kMeanWorkers = 3;    // streaming kernels: from this many workers on the products are taken of the mean over the workers
+                                   // (12 W + 8 bytes per element for the first two sweeps instead of 16 W: no gain at two workers, where
+                                   // it measured 330 us against 318 on 30 matrices of 24 M elements)
 constexpr int kFlatTileElems = 1024;        // baselines: elements of a flattened matrix per workgroup of the elementwise sweep (one 16-byte access per
                                             // lane and array: the smallest slices were the fastest, 8192 -> 1024: 34.7 -> 28.7 us on the ResNet18 set)
 constexpr int kFactorAlignElems = 4;        // P and Q of a matrix start at multiples of 4 floats (vector loads of factor rows)
@@ -98,7 +101,8 @@ struct RTile {
 struct Tuning {
     int64_t k1_rows = 0;    // rows per workgroup tile, P = M Q; 0: by the access width of the matrix (16 / 32 / 64; twice
                             // that for small sets)
-    int64_t k1_nv = 2;      // column vectors per lane (<= kMaxVecPerLaneK1)
+    int64_t k1_nv = 2;      // column vectors per lane (<= kMaxVecPerLaneK1) ...
+    bool k1_nv_set = false; // ... by the tuning key; else one from kMeanWorkers workers on
     int64_t k3_rows = 0;    // rows per workgroup tile, Q = M^T P; 0: 128, or 1024 for matrices >= 2048 x 2048
     int64_t k3_nv = 1;      // column vectors per lane (<= kMaxVecPerLaneK3)
     int64_t k4_rows = 0;    // rows per workgroup tile, decompress + residual; 0: 16 (32 for small sets)
@@ -191,6 +195,9 @@ struct psgd_plan {
     int64_t ws_chol_doubles = 0;
     std::vector<psgd::Tile> tilesp;         // 64-element slices of the n x r panels (pre-reduction of partial P)
     bool p_pre_reduce = false;              // some matrix has more than kPreReduceParts partial-P slices
+    bool p_pre_reduce_mean = false;         // the same for the products of the mean over the workers
+    int32_t k1_nv = 2;                      // column vectors per lane of the first sweep (see Tuning::k1_nv)
+    float* mbar = nullptr;                  // device, N floats: mean over the workers of M (workers >= kMeanWorkers, streaming kernels)
     bool stream_hints = false;              // see Tuning::stream_hints
     bool gram_fused = false;                // Cholesky-QR panels: one launch (k_gram_chol) instead of two (set at upload)
     int32_t max_n = 0;
@@ -239,14 +246,16 @@ void build_resident(psgd_plan* plan, int64_t max_blocks);
 // device side (psgd_kernels.hip)
 psgd_status upload_tables(psgd_plan* plan);
 void free_tables(psgd_plan* plan);
-// add = false: one more subspace iteration on the update already held in err (grad is not read, err not written)
+// add = false: one more subspace iteration on the update already held in err (grad is not read, err not written);
+// with grad = nullptr the same right after a compress or iteration of the same call, on the same M
 psgd_status launch_compress(psgd_plan* plan, const void* grad, float* err, float* q, float* p,
                             void* workspace, void* stream, bool add = true);
 psgd_status launch_decompress(psgd_plan* plan, const float* p, const float* q, float* err,
                               const void* grad, void* out, void* workspace, void* stream,
                               const UpdateArgs& upd = UpdateArgs());
 psgd_status set_profiling(psgd_plan* plan, bool enable);
-psgd_status launch_q_reduce(psgd_plan* plan, float* ws, float* q, void* stream);
+// workers: those that have partial Q of their own
+psgd_status launch_q_reduce(psgd_plan* plan, float* ws, float* q, void* stream, int workers);
 psgd_status finish_profiled_step(psgd_plan* plan);
 psgd_status hr_compress(psgd_plan* plan, const void* grad, float* err, float* q, float* p, void* workspace,
                         void* stream, bool add);

@@ -7,6 +7,8 @@
 //   k_ef_right    M_w = g_w + e_w (stored in e_w's place) fused with the row dot
 //                 products of P_w = M_w Q               (Alg. 2 "Delta_w", Alg. 1 "P <- M Q");
 //                 without the add, one more subspace iteration on a stored M (Appendix G.7)
+//   k_ef_right_mean  the same from three workers on: M_w of all workers, their mean, and the products of the
+//                 mean, which the launches up to Q then work on
 //   k_gram_chol   mean over workers / column chunks, then the orthonormal factor Gram-Schmidt
 //                 gives, by Cholesky-QR over many workgroups in one launch; k_gram,
 //                 k_chol_apply: the same in two launches (Alg. 1 "all reduce mean", "orthogonalize";
@@ -155,6 +157,137 @@ __global__ __launch_bounds__(kBlock) void k_ef_right(const MatDesc* __restrict__
     if (d.vec == 4) ef_right_tile<R, 4, NV, ADD, GBF>(t, d, g, e, q, ws);
     else if (d.vec == 2) ef_right_tile<R, 2, NV, ADD, GBF>(t, d, g, e, q, ws);
     else ef_right_tile<R, 1, NV, ADD, GBF>(t, d, g, e, q, ws);
+}
+
+// ---- k_ef_right_mean: the same over all workers at once -----------------------------------------------------
+//
+// P and Q depend on the workers' updates only through their mean: P = mean_w(M_w) Q, Q = mean_w(M_w)^T P_hat.  With
+// several workers a wavefront therefore walks its rows once for all of them: every M_w = g_w + e_w is stored in
+// e_w's place as before, their mean goes to a buffer of its own, and the products are taken of the mean, once
+// instead of once per worker.  What follows (Q = M^T P_hat, further iterations) reads 4 bytes per element instead of
+// 4 W.  HBM-bound: 12 W + 4 bytes per element.  A step is RS rows of NV vectors, 16 elements per lane and array;
+// two workers' loads are in flight in two register sets that are consumed in turn, and the even and the odd workers
+// are summed apart.  ResNet18-shaped set, whole step: 16 workers, rank 4: 732 -> 672 us (first sweep 404 us, 5.4 TB/s,
+// second 10 us where it read 715 MB); 4 workers, rank 2: 213.5 -> 202.5 us; 24 matrices of 9 M elements, 3 workers, two
+// iterations: 208 -> 199 us.  Tiles of 8 or 32 rows and two vectors per lane were 0 to 3 % slower at 16 workers, 2 to 60 % on the other two.
+// ADD = false: M_w is read from e (psgd_iterate), nothing is added and e is not written.
+// STREAM: the M_w of all workers do not fit the memory-side cache: e is read and M_w written around it, which leaves it to the mean.
+template <int R, int V, int NV, bool ADD, bool GBF, bool STREAM>
+__device__ __forceinline__ void ef_right_mean_tile(const Tile& t, const MatDesc& d, const void* __restrict__ g,
+                                                   float* __restrict__ e, const float* __restrict__ q,
+                                                   float* __restrict__ ppart, float* __restrict__ mbar, int workers,
+                                                   int64_t gstride, int64_t estride) {
+    constexpr unsigned GS = GBF ? 2u : 4u;
+    constexpr int RS = 16 / (NV * V) * R <= kWave ? 16 / (NV * V) : 8;   // RS * R results fit the 64 lanes
+    static_assert(RS * R <= kWave, "one lane per (row, rank) result of a step");
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int ri = d.r;
+    const float inv_w = 1.0f / (float)workers;
+
+    float qr[NV][V][R];
+    unsigned coff[NV], goff[NV];   // missing columns: out of range (loads read zero, stores are dropped)
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const int jv = lane + kWave * v;
+        const bool valid = jv < t.nvec;
+        const int col = (t.vec0 + jv) * V;
+        load_factor_rows<R, V>(q + d.q_off + (int64_t)col * ri, ri, valid, qr[v]);
+        coff[v] = valid ? (unsigned)col * 4u : kOutOfRange;
+        goff[v] = valid ? (unsigned)col * GS : kOutOfRange;
+    }
+    int rb, rn;
+    wave_rows(t.nrows, wave, &rb, &rn);
+    const int64_t strip = d.off + (int64_t)(t.row0 + rb) * d.m;
+    const int64_t elems = (int64_t)rn * d.m;   // rows past the strip lie beyond the descriptors
+    const buf_rsrc mres = make_rsrc(mbar + strip, elems * 4);
+    for (int i0 = 0; i0 < rn; i0 += RS) {
+        const unsigned el0 = (unsigned)i0 * (unsigned)d.m;
+        // a worker past the last one has empty descriptors: zeros are read, nothing is stored
+        auto load = [&](int w, float (&gv)[RS][NV][V], float (&ev)[RS][NV][V]) {
+            const int ww = w < workers ? w : 0;
+            const int64_t n_el = w < workers ? elems : 0;
+            const buf_rsrc er = make_rsrc(e + (int64_t)ww * estride + strip, n_el * 4);
+            if constexpr (ADD) {
+                const buf_rsrc gr = make_rsrc(static_cast<const char*>(g) + ((int64_t)ww * gstride + strip) * GS, n_el * GS);
+#pragma unroll
+                for (int i = 0; i < RS; ++i)
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) buf_ld_grad<V, GBF>(gr, goff[v] + (el0 + (unsigned)i * (unsigned)d.m) * GS, gv[i][v]);
+            }
+#pragma unroll
+            for (int i = 0; i < RS; ++i)
+#pragma unroll
+                for (int v = 0; v < NV; ++v) buf_ldv<V>(er, coff[v] + (el0 + (unsigned)i * (unsigned)d.m) * 4u, ev[i][v], STREAM);
+        };
+        float sum[RS][NV][V], odd[RS][NV][V];   // over the even and the odd workers
+#pragma unroll
+        for (int i = 0; i < RS; ++i)
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+#pragma unroll
+                for (int x = 0; x < V; ++x) sum[i][v][x] = odd[i][v][x] = 0.f;
+        auto take = [&](int w, float (&gv)[RS][NV][V], float (&ev)[RS][NV][V], float (&to)[RS][NV][V]) {
+            const buf_rsrc er = make_rsrc(e + (int64_t)(w < workers ? w : 0) * estride + strip, w < workers ? elems * 4 : 0);
+#pragma unroll
+            for (int i = 0; i < RS; ++i)
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    if constexpr (ADD) {
+#pragma unroll
+                        for (int x = 0; x < V; ++x) ev[i][v][x] += gv[i][v][x];
+                        buf_stv<V>(er, coff[v] + (el0 + (unsigned)i * (unsigned)d.m) * 4u, ev[i][v], STREAM);
+                    }
+#pragma unroll
+                    for (int x = 0; x < V; ++x) to[i][v][x] += ev[i][v][x];
+                }
+        };
+        float ga[RS][NV][V], ea[RS][NV][V], gb[RS][NV][V], eb[RS][NV][V];
+        load(0, ga, ea);
+        load(1, gb, eb);
+        for (int w = 0; w < workers; w += 2) {
+            take(w, ga, ea, sum);
+            load(w + 2, ga, ea);
+            take(w + 1, gb, eb, odd);
+            load(w + 3, gb, eb);
+        }
+        float part[RS * R];
+#pragma unroll
+        for (int i = 0; i < RS; ++i) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+#pragma unroll
+                for (int x = 0; x < V; ++x) sum[i][v][x] = (sum[i][v][x] + odd[i][v][x]) * inv_w;
+                buf_stv<V>(mres, coff[v] + (el0 + (unsigned)i * (unsigned)d.m) * 4u, sum[i][v]);
+            }
+#pragma unroll
+            for (int k = 0; k < R; ++k) {
+                float s = 0.f;
+#pragma unroll
+                for (int v = 0; v < NV; ++v)
+#pragma unroll
+                    for (int x = 0; x < V; ++x) s = fmaf(sum[i][v][x], qr[v][x][k], s);
+                part[i * R + k] = s;
+            }
+        }
+        const float mine = lane_sums<RS * R>(part);
+        const int li = lane / R, lk = lane % R;
+        if (li < min(RS, rn - i0) && lk < ri)
+            ppart[d.ppart_off + ((int64_t)t.part * d.n + t.row0 + rb + i0 + li) * ri + lk] = mine;
+    }
+}
+
+template <int R, int NV, bool ADD, bool GBF, bool STREAM>
+__global__ __launch_bounds__(kBlock) void k_ef_right_mean(const MatDesc* __restrict__ mats, const Tile* __restrict__ tiles,
+                                                          const void* __restrict__ grad, float* __restrict__ err,
+                                                          const float* __restrict__ q, float* __restrict__ ws,
+                                                          float* __restrict__ mbar, int workers, int64_t gstride,
+                                                          int64_t estride) {
+    const Tile t = tiles[blockIdx.x];
+    const MatDesc d = mats[t.mat];
+    if (d.vec == 4) ef_right_mean_tile<R, 4, NV, ADD, GBF, STREAM>(t, d, grad, err, q, ws, mbar, workers, gstride, estride);
+    else if (d.vec == 2) ef_right_mean_tile<R, 2, NV, ADD, GBF, STREAM>(t, d, grad, err, q, ws, mbar, workers, gstride, estride);
+    else ef_right_mean_tile<R, 1, NV, ADD, GBF, STREAM>(t, d, grad, err, q, ws, mbar, workers, gstride, estride);
 }
 
 // sum of `nparts` partial slices (stride `stride` floats) at `src`, in slice order, eight loads in flight
@@ -619,7 +752,10 @@ __global__ __launch_bounds__(kBlock) void k_gram_chol(const MatDesc* __restrict_
 
 // STREAM: M is larger than the memory-side cache and will not be found there by the next sweep either way; reading it
 // with non-temporal loads keeps it from pushing out lines that are still waiting to be written back.
-template <int R, int V, int NV, bool STREAM>
+// SHORT: the sums run over eight rows and are then added up, which shortens the chain of roundings from a strip's 32
+// rows: on the mean over the workers, where the roundings of several workers' own sums no longer average out (error of
+// Q against 64 bits, ResNet18-shaped set: 7.3e-8 with four workers' own sums, 6.6e-8 this way; 16 workers: 6.6e-8, 6.1e-8).
+template <int R, int V, int NV, bool STREAM, bool SHORT>
 __device__ __forceinline__ void left_tile(const Tile& t, const MatDesc& d, const float* __restrict__ e,
                                           const float* __restrict__ p, float* __restrict__ qpart, float* lds) {
     constexpr int RU = 8;
@@ -660,6 +796,15 @@ __device__ __forceinline__ void left_tile(const Tile& t, const MatDesc& d, const
             for (int u = 0; u < RU; ++u)
 #pragma unroll
                 for (int v = 0; v < NV; ++v) buf_ldv<V>(eres, coff[v] + row_off + (unsigned)u * (unsigned)d.m * 4u, x[u][v], STREAM);
+            float sub[SHORT ? NV : 1][V][R];   // the sums of these eight rows
+            if constexpr (SHORT) {
+#pragma unroll
+                for (int v = 0; v < NV; ++v)
+#pragma unroll
+                    for (int xx = 0; xx < V; ++xx)
+#pragma unroll
+                        for (int k = 0; k < R; ++k) sub[v][xx][k] = 0.f;
+            }
 #pragma unroll
             for (int u = 0; u < RU; ++u) {
                 float pk[R];   // lanes at or past gr hold zeros: rows past the group contribute nothing
@@ -670,7 +815,18 @@ __device__ __forceinline__ void left_tile(const Tile& t, const MatDesc& d, const
 #pragma unroll
                     for (int xx = 0; xx < V; ++xx)
 #pragma unroll
-                        for (int k = 0; k < R; ++k) acc[v][xx][k] = fmaf(x[u][v][xx], pk[k], acc[v][xx][k]);
+                        for (int k = 0; k < R; ++k) {
+                            if constexpr (SHORT) sub[v][xx][k] = fmaf(x[u][v][xx], pk[k], sub[v][xx][k]);
+                            else acc[v][xx][k] = fmaf(x[u][v][xx], pk[k], acc[v][xx][k]);
+                        }
+            }
+            if constexpr (SHORT) {
+#pragma unroll
+                for (int v = 0; v < NV; ++v)
+#pragma unroll
+                    for (int xx = 0; xx < V; ++xx)
+#pragma unroll
+                        for (int k = 0; k < R; ++k) acc[v][xx][k] += sub[v][xx][k];
             }
         }
     }
@@ -710,7 +866,7 @@ __device__ __forceinline__ void left_tile(const Tile& t, const MatDesc& d, const
     }
 }
 
-template <int R, int NV, bool STREAM>
+template <int R, int NV, bool STREAM, bool SHORT>
 __global__ __launch_bounds__(kBlock) void k_left(const MatDesc* __restrict__ mats, const Tile* __restrict__ tiles,
                                                  const float* __restrict__ err, const float* __restrict__ p,
                                                  float* __restrict__ ws, int64_t estride) {
@@ -721,9 +877,9 @@ __global__ __launch_bounds__(kBlock) void k_left(const MatDesc* __restrict__ mat
     const float* e = err + (int64_t)w * estride;
     float* qp = ws;
     t.part += w * d.n_rblock;   // partial slices: [worker][row block]
-    if (d.vec == 4) left_tile<R, 4, NV, STREAM>(t, d, e, p, qp, lds);
-    else if (d.vec == 2) left_tile<R, 2, NV, STREAM>(t, d, e, p, qp, lds);
-    else left_tile<R, 1, NV, STREAM>(t, d, e, p, qp, lds);
+    if (d.vec == 4) left_tile<R, 4, NV, STREAM, SHORT>(t, d, e, p, qp, lds);
+    else if (d.vec == 2) left_tile<R, 2, NV, STREAM, SHORT>(t, d, e, p, qp, lds);
+    else left_tile<R, 1, NV, STREAM, SHORT>(t, d, e, p, qp, lds);
 }
 
 // ---- k_q_reduce: Q = (1/W) sum over workers and row blocks of the partials ------------------------
@@ -946,6 +1102,8 @@ void free_tables(psgd_plan* plan) {
         (void)hipFree(plan->dev.base);
         plan->dev = DeviceTables();
     }
+    if (plan->mbar) (void)hipFree(plan->mbar);
+    plan->mbar = nullptr;
     plan->uploaded = false;
 }
 
@@ -1062,6 +1220,12 @@ psgd_status upload_tables(psgd_plan* plan) {
     plan->dev.kept_slice_mat = reinterpret_cast<int32_t*>(b + pieces[20].at);
     plan->dev.kept_slice_first = reinterpret_cast<int64_t*>(b + pieces[21].at);
     plan->dev.mat_tensor = reinterpret_cast<int32_t*>(b + pieces[22].at);
+    // the mean over the workers of M; without it every worker's M is multiplied by itself
+    if (plan->workers >= kMeanWorkers && !plan->hr && plan->gram_fused &&
+        hipMalloc(reinterpret_cast<void**>(&plan->mbar), (size_t)plan->sizes.n_mat_elems * sizeof(float)) != hipSuccess) {
+        plan->mbar = nullptr;
+        (void)hipGetLastError();
+    }
     plan->uploaded = true;
     return PSGD_OK;
 }
@@ -1147,37 +1311,69 @@ psgd_status check_plan(psgd_plan* plan, void* stream) {
 
 template <int R>
 static void launch_ef_right(psgd_plan* plan, const void* grad, float* err, const float* q, float* ws,
-                            hipStream_t s, bool add) {
-    dim3 grid((unsigned)plan->tiles1.size(), (unsigned)plan->workers);
+                            hipStream_t s, bool add, int workers) {
+    dim3 grid((unsigned)plan->tiles1.size(), (unsigned)workers);
 #define PSGD_LAUNCH_RIGHT(NVV, ADDV, GBFV)                                                                             \
     hipLaunchKernelGGL((k_ef_right<R, NVV, ADDV, GBFV>), grid, dim3(kBlock), 0, s, plan->dev.mats, plan->dev.tiles1,   \
                        grad, err, q, ws, plan->sizes.grad_stride, plan->sizes.err_stride)
     if (!add) {   // the gradient is not read
-        if (plan->tuning.k1_nv == 1) PSGD_LAUNCH_RIGHT(1, false, false);
+        if (plan->k1_nv == 1) PSGD_LAUNCH_RIGHT(1, false, false);
         else PSGD_LAUNCH_RIGHT(2, false, false);
     } else if (plan->grad_dtype == PSGD_BF16) {
-        if (plan->tuning.k1_nv == 1) PSGD_LAUNCH_RIGHT(1, true, true);
+        if (plan->k1_nv == 1) PSGD_LAUNCH_RIGHT(1, true, true);
         else PSGD_LAUNCH_RIGHT(2, true, true);
     } else {
-        if (plan->tuning.k1_nv == 1) PSGD_LAUNCH_RIGHT(1, true, false);
+        if (plan->k1_nv == 1) PSGD_LAUNCH_RIGHT(1, true, false);
         else PSGD_LAUNCH_RIGHT(2, true, false);
     }
 #undef PSGD_LAUNCH_RIGHT
 }
 
 template <int R>
-static void launch_left(psgd_plan* plan, const float* err, const float* p, float* ws, hipStream_t s) {
-    dim3 grid((unsigned)plan->tiles3.size(), (unsigned)plan->workers);
-#define PSGD_LAUNCH_LEFT(NVV, STREAMV)                                                                                 \
-    hipLaunchKernelGGL((k_left<R, NVV, STREAMV>), grid, dim3(kBlock), 0, s, plan->dev.mats, plan->dev.tiles3, err, p, ws, \
+static void launch_ef_right_mean(psgd_plan* plan, const void* grad, float* err, const float* q, float* ws,
+                                 hipStream_t s, bool add) {
+    dim3 grid((unsigned)plan->tiles1.size());
+#define PSGD_LAUNCH_MEAN(NVV, ADDV, GBFV, STREAMV)                                                                     \
+    hipLaunchKernelGGL((k_ef_right_mean<R, NVV, ADDV, GBFV, STREAMV>), grid, dim3(kBlock), 0, s, plan->dev.mats,       \
+                       plan->dev.tiles1, grad, err, q, ws, plan->mbar, plan->workers, plan->sizes.grad_stride,         \
                        plan->sizes.err_stride)
+#define PSGD_LAUNCH_MEAN_NV(ADDV, GBFV, STREAMV)                         \
+    do {                                                                 \
+        if (plan->k1_nv == 1) PSGD_LAUNCH_MEAN(1, ADDV, GBFV, STREAMV);  \
+        else PSGD_LAUNCH_MEAN(2, ADDV, GBFV, STREAMV);                   \
+    } while (0)
+    const bool bf = plan->grad_dtype == PSGD_BF16;
     if (plan->stream_hints) {
-        if (plan->tuning.k3_nv == 1) PSGD_LAUNCH_LEFT(1, true);
-        else PSGD_LAUNCH_LEFT(2, true);
+        if (!add) PSGD_LAUNCH_MEAN_NV(false, false, true);
+        else if (bf) PSGD_LAUNCH_MEAN_NV(true, true, true);
+        else PSGD_LAUNCH_MEAN_NV(true, false, true);
     } else {
-        if (plan->tuning.k3_nv == 1) PSGD_LAUNCH_LEFT(1, false);
-        else PSGD_LAUNCH_LEFT(2, false);
+        if (!add) PSGD_LAUNCH_MEAN_NV(false, false, false);
+        else if (bf) PSGD_LAUNCH_MEAN_NV(true, true, false);
+        else PSGD_LAUNCH_MEAN_NV(true, false, false);
     }
+#undef PSGD_LAUNCH_MEAN_NV
+#undef PSGD_LAUNCH_MEAN
+}
+
+// `mean`: M is the mean over the workers; `stream`: what is read does not fit the memory-side cache
+template <int R>
+static void launch_left(psgd_plan* plan, const float* m, const float* p, float* ws, hipStream_t s, bool mean,
+                        bool stream) {
+    dim3 grid((unsigned)plan->tiles3.size(), mean ? 1u : (unsigned)plan->workers);
+#define PSGD_LAUNCH_LEFT(NVV, STREAMV, SHORTV)                                                                         \
+    hipLaunchKernelGGL((k_left<R, NVV, STREAMV, SHORTV>), grid, dim3(kBlock), 0, s, plan->dev.mats, plan->dev.tiles3, m, p, \
+                       ws, plan->sizes.err_stride)
+#define PSGD_LAUNCH_LEFT_NV(STREAMV, SHORTV)                                \
+    do {                                                                    \
+        if (plan->tuning.k3_nv == 1) PSGD_LAUNCH_LEFT(1, STREAMV, SHORTV);  \
+        else PSGD_LAUNCH_LEFT(2, STREAMV, SHORTV);                          \
+    } while (0)
+    if (mean && stream) PSGD_LAUNCH_LEFT_NV(true, true);
+    else if (mean) PSGD_LAUNCH_LEFT_NV(false, true);
+    else if (stream) PSGD_LAUNCH_LEFT_NV(true, false);
+    else PSGD_LAUNCH_LEFT_NV(false, false);
+#undef PSGD_LAUNCH_LEFT_NV
 #undef PSGD_LAUNCH_LEFT
 }
 
@@ -1238,6 +1434,8 @@ psgd_status launch_compress(psgd_plan* plan, const void* grad, float* err, float
                             void* stream, bool add) {
     psgd_status st = check_ready(plan);
     if (st != PSGD_OK) return st;
+    const bool again = !grad;
+    if (!grad) grad = err;   // not dereferenced
     if (plan->hr) return hr_compress(plan, grad, err, q, p, workspace, stream, add);
     hipStream_t s = static_cast<hipStream_t>(stream);
     float* ws = static_cast<float*>(workspace);
@@ -1246,19 +1444,27 @@ psgd_status launch_compress(psgd_plan* plan, const void* grad, float* err, float
 
     PSGD_MARK(0);
     plan->compress_marked = plan->profiling;
-    PSGD_RANK_SWITCH(launch_ef_right, plan, g, err, q, ws, s, add);
+    // Several workers: the products are taken of the mean over the workers.  It lives in plan-owned memory, which is
+    // no new restriction where gram_fused holds (calls of one plan must not overlap there); elsewhere, and where that
+    // memory could not be had, every worker's M is multiplied by itself.
+    const bool mean = plan->mbar && plan->gram_fused;
+    const int workers = mean ? 1 : plan->workers;   // of the partial P and Q
+    const float* m = mean ? plan->mbar : err;
+    if (mean && again) PSGD_RANK_SWITCH(launch_ef_right, plan, plan->mbar, plan->mbar, q, ws, s, false, 1)
+    else if (mean) PSGD_RANK_SWITCH(launch_ef_right_mean, plan, g, err, q, ws, s, add)
+    else PSGD_RANK_SWITCH(launch_ef_right, plan, g, err, q, ws, s, add, plan->workers)
     PSGD_HIP(hipGetLastError(), "launch k_ef_right");
     PSGD_MARK(1);
 
-    const int pre_reduced = plan->p_pre_reduce ? 1 : 0;
+    const int pre_reduced = (mean ? plan->p_pre_reduce_mean : plan->p_pre_reduce) ? 1 : 0;
     if (pre_reduced) {
         hipLaunchKernelGGL(k_q_reduce, dim3((unsigned)plan->tilesp.size()), dim3(kBlock), 0, s, plan->dev.mats,
-                           plan->dev.tilesp, ws, static_cast<float*>(nullptr), plan->workers, 1);
+                           plan->dev.tilesp, ws, static_cast<float*>(nullptr), workers, 1);
         PSGD_HIP(hipGetLastError(), "launch k_q_reduce (partial P)");
     }
     if (!plan->small_mats.empty()) {
         hipLaunchKernelGGL(k_ortho, dim3((unsigned)plan->small_mats.size()), dim3(kOrthoBlock), 0, s, plan->dev.mats,
-                           plan->dev.small_mats, ws, p, plan->workers, pre_reduced);
+                           plan->dev.small_mats, ws, p, workers, pre_reduced);
         PSGD_HIP(hipGetLastError(), "launch k_ortho");
     }
     if (!plan->tiles_gram.empty() && plan->gram_fused) {
@@ -1267,7 +1473,7 @@ psgd_status launch_compress(psgd_plan* plan, const void* grad, float* err, float
         slot_t* gmail = reinterpret_cast<slot_t*>(plan->dev.gram_mail);
 #define PSGD_LAUNCH_GRAM_CHOL(RR)                                                                                     \
     hipLaunchKernelGGL((k_gram_chol<RR>), ggrid, dim3(kBlock), 0, s, plan->dev.mats, plan->dev.tiles_gram, ws, p, gmail, \
-                       plan->dev.gram_sync, plan->workers, pre_reduced, (unsigned)plan->tuning.gram_spin)
+                       plan->dev.gram_sync, workers, pre_reduced, (unsigned)plan->tuning.gram_spin)
         switch (plan->rank) {
             case 1: PSGD_LAUNCH_GRAM_CHOL(1); break;
             case 2: PSGD_LAUNCH_GRAM_CHOL(2); break;
@@ -1286,7 +1492,7 @@ psgd_status launch_compress(psgd_plan* plan, const void* grad, float* err, float
         const size_t float_bytes = (size_t)(plan->ws_ppart_floats + plan->ws_qpart_floats) * sizeof(float);
         double* gram = reinterpret_cast<double*>(static_cast<char*>(workspace) + (float_bytes + 255) / 256 * 256);
         hipLaunchKernelGGL(k_gram, dim3((unsigned)plan->tiles_gram.size()), dim3(kBlock), 0, s, plan->dev.mats,
-                           plan->dev.tiles_gram, ws, p, gram, plan->workers, pre_reduced);
+                           plan->dev.tiles_gram, ws, p, gram, workers, pre_reduced);
         PSGD_HIP(hipGetLastError(), "launch k_gram");
         hipLaunchKernelGGL(k_chol_apply, dim3((unsigned)plan->tiles_gram.size()), dim3(kBlock), 0, s, plan->dev.mats,
                            plan->dev.tiles_gram, gram, p);
@@ -1294,21 +1500,23 @@ psgd_status launch_compress(psgd_plan* plan, const void* grad, float* err, float
     }
     PSGD_MARK(2);
 
-    PSGD_RANK_SWITCH(launch_left, plan, err, p, ws, s);
+    const bool stream_m = mean && plan->tuning.stream_hints < 0
+                              ? plan->sizes.n_mat_elems * (int64_t)sizeof(float) > kStreamHintBytes : plan->stream_hints;
+    PSGD_RANK_SWITCH(launch_left, plan, m, p, ws, s, mean, stream_m);
     PSGD_HIP(hipGetLastError(), "launch k_left");
     PSGD_MARK(3);
 
-    st = launch_q_reduce(plan, ws, q, stream);
+    st = launch_q_reduce(plan, ws, q, stream, workers);
     if (st != PSGD_OK) return st;
     PSGD_MARK(4);
     return PSGD_OK;
 }
 
-psgd_status launch_q_reduce(psgd_plan* plan, float* ws, float* q, void* stream) {
+psgd_status launch_q_reduce(psgd_plan* plan, float* ws, float* q, void* stream, int workers) {
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (plan->tilesq.empty()) return PSGD_OK;   // every Q was written directly
     hipLaunchKernelGGL(k_q_reduce, dim3((unsigned)plan->tilesq.size()), dim3(kBlock), 0, s, plan->dev.mats,
-                       plan->dev.tilesq, ws, q, plan->workers, 0);
+                       plan->dev.tilesq, ws, q, workers, 0);
     PSGD_HIP(hipGetLastError(), "launch k_q_reduce");
     return PSGD_OK;
 }

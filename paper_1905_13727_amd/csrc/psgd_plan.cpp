@@ -272,7 +272,9 @@ psgd_status build_tables(psgd_plan* plan) {
             (int64_t(1) << 31))
             return PSGD_EUNSUPPORTED;
     std::vector<int32_t> nrb(nm, 0), ncc(nm, 0);
-    streaming_tiles(plan, 1, tu.k1_rows, tu.k1_nv, true, &plan->tiles1, nullptr, &ncc);
+    // several workers: the sums over the workers take the registers of the second column vector
+    plan->k1_nv = plan->workers >= kMeanWorkers && !tu.k1_nv_set ? 1 : (int32_t)tu.k1_nv;
+    streaming_tiles(plan, 1, tu.k1_rows, plan->k1_nv, true, &plan->tiles1, nullptr, &ncc);
     streaming_tiles(plan, 2, tu.k3_rows, tu.k3_nv, false, &plan->tiles3, &nrb, nullptr);
     streaming_tiles(plan, 3, tu.k4_rows, tu.k4_nv, false, &plan->tiles4, nullptr, nullptr);
 
@@ -339,9 +341,10 @@ psgd_status build_tables(psgd_plan* plan) {
 
     // the same slicing of the n x r panels, used when a matrix has many partial-P slices
     plan->tilesp.clear();
-    plan->p_pre_reduce = false;
+    plan->p_pre_reduce = plan->p_pre_reduce_mean = false;
     for (size_t i = 0; i < nm; ++i) {
         const MatDesc& d = plan->mats[i];
+        if (d.n_cchunk > 2 * kPreReduceParts) plan->p_pre_reduce_mean = true;   // half as wide chunks
         if (W * d.n_cchunk > kPreReduceParts) plan->p_pre_reduce = true;
         const int64_t total = (int64_t)d.n * d.r;
         for (int64_t e = 0; e < total; e += kWave) {
@@ -714,7 +717,7 @@ psgd_status psgd_plan_set_tuning(psgd_plan* plan, const char* key, int64_t value
     if (plan->uploaded) return PSGD_EINVAL;
     Tuning tu = plan->tuning;
     if (!strcmp(key, "k1_rows")) tu.k1_rows = value;
-    else if (!strcmp(key, "k1_nv")) tu.k1_nv = value;
+    else if (!strcmp(key, "k1_nv")) { tu.k1_nv = value; tu.k1_nv_set = true; }
     else if (!strcmp(key, "k3_rows")) tu.k3_rows = value;
     else if (!strcmp(key, "k3_nv")) tu.k3_nv = value;
     else if (!strcmp(key, "k4_rows")) tu.k4_rows = value;
@@ -789,7 +792,7 @@ psgd_status psgd_step_iterations(psgd_plan* plan, const void* grad, float* err, 
     if (plan->resident_ok) return launch_resident_step(plan, grad, err, q, p, out, workspace, hip_stream, UpdateArgs(), iterations);
     psgd_status st = launch_compress(plan, grad, err, q, p, workspace, hip_stream);
     for (int32_t it = 1; it < iterations && st == PSGD_OK; ++it)
-        st = launch_compress(plan, err, err, q, p, workspace, hip_stream, false);
+        st = launch_compress(plan, nullptr, err, q, p, workspace, hip_stream, false);
     if (st != PSGD_OK) return st;
     return launch_decompress(plan, p, q, err, grad, out, workspace, hip_stream);
 }

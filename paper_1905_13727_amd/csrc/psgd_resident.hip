@@ -597,7 +597,7 @@ static psgd_status streamed_step(psgd_plan* plan, const void* grad, float* err, 
                                  void* workspace, void* stream, const UpdateArgs& upd, int iterations) {
     psgd_status st = launch_compress(plan, grad, err, q, p, workspace, stream);
     for (int it = 1; it < iterations && st == PSGD_OK; ++it)
-        st = launch_compress(plan, err, err, q, p, workspace, stream, false);
+        st = launch_compress(plan, nullptr, err, q, p, workspace, stream, false);
     if (st != PSGD_OK) return st;
     return launch_decompress(plan, p, q, err, grad, out, workspace, stream, upd);
 }

@@ -1,0 +1,80 @@
+"""Three workers or more on the streaming kernels: the products are taken of the mean over the workers' M (one mean matrix,
+plan-owned).  Compared with the general path, which multiplies every worker's M by itself: the same plan with the
+one-launch orthogonalisation switched off takes it."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+# every access width (rows of a multiple of 4, of 2, odd), rows shorter and longer than a column chunk, one and two
+# rows, fewer rows than a tile and one more than one, a vector
+SHAPES = [(64, 576), (17, 1028), (33, 650), (2, 130), (65, 257), (1, 3), (130, 63), (77,), (300, 5)]
+
+
+@pytest.mark.parametrize("rank,workers,grad_bf16,call", [
+    (1, 3, False, "step"), (2, 3, False, "split"), (3, 16, False, "step"), (4, 4, True, "iterations"),
+    (5, 5, False, "iterate"), (8, 3, True, "step"), (8, 4, False, "iterations"), (2, 4, False, "update"),
+    (3, 3, False, "hints"), (2, 2, False, "step"),
+])
+def test_mean_route_equals_general_route(rank, workers, grad_bf16, call):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1905_13727_amd import binding as B
+    dev = torch.device("cuda:0")
+    stream = torch.cuda.current_stream(dev).cuda_stream
+    outs = []
+    for fused in (1, 0):
+        plan = B.Plan(SHAPES, rank, workers, B.PSGD_BF16 if grad_bf16 else B.PSGD_F32, B.PSGD_F32)
+        plan.set_tuning("resident", 0)
+        plan.set_tuning("gram_fused", fused)
+        if call == "hints":
+            plan.set_tuning("stream_hints", 1)
+        s = plan.sizes
+        gen = torch.Generator(device=dev)
+        gen.manual_seed(rank * 100 + workers)
+        grad = torch.randn(workers * s.grad_stride, generator=gen, device=dev).to(
+            torch.bfloat16 if grad_bf16 else torch.float32)
+        err = 0.5 * torch.randn(workers * s.err_stride, generator=gen, device=dev)
+        q = torch.randn(s.q_elems, generator=gen, device=dev)
+        live = torch.zeros(s.err_stride, dtype=torch.bool, device=dev)
+        for t, shape in enumerate(SHAPES):
+            if len(shape) == 2:
+                live[plan.offsets(t)[0]: plan.offsets(t)[0] + shape[0] * shape[1]] = True
+        err0 = err.clone()
+        p = torch.zeros(s.p_elems, device=dev)
+        out = torch.zeros(s.out_elems, device=dev)
+        ws = torch.full((s.workspace_bytes // 4 + 64,), float("nan"), device=dev)
+        if call == "iterations":
+            plan.step_iterations(grad, err, q, p, out, ws, 3, stream)
+        elif call == "update":
+            param = torch.zeros(s.out_elems, device=dev)
+            plan.step_update(grad, err, q, p, out, param, 0.1, 0.9, ws, stream)
+        elif call in ("split", "iterate"):
+            plan.compress(grad, err, q, p, ws, stream)
+            M = grad.view(workers, -1)[:, : s.n_mat_elems].float() + err0.view(workers, -1)
+            assert torch.equal(err.view(workers, -1)[:, live], M[:, live])   # M_w itself is left for the next call
+            if call == "iterate":   # on whatever M the caller holds by then
+                scale = torch.linspace(0.5, 1.5, workers, device=dev).repeat_interleave(s.err_stride)
+                err, err0 = err * scale, err0 * scale
+                ws.fill_(float("nan"))
+                plan.iterate(err, q, p, ws, stream)
+            plan.decompress(p, q, err, grad, out, ws, stream)
+        else:
+            plan.step(grad, err, q, p, out, ws, stream)
+        plan.check(stream)
+        assert torch.equal(err.view(workers, -1)[:, ~live], err0.view(workers, -1)[:, ~live])   # gaps are not touched
+        outs.append((plan, q, p, out, err.view(workers, -1)[:, live]))
+    a, b = outs
+    # Per matrix: both are fp32 sums over at most 1028 terms in different orders, far below 1e-6 of the largest entry;
+    # the orthogonalisation multiplies by the panels' condition (random 1 x 3 ... 300 x 5 matrices at full rank: up to a few hundred).
+    for t, shape in enumerate(SHAPES):
+        off, p_off, q_off, r = a[0].offsets(t)
+        size = shape[0] * (shape[1] if len(shape) == 2 else 1)
+        pairs = [(a[3][off: off + size], b[3][off: off + size])]
+        if r:
+            pairs += [(a[1][q_off: q_off + shape[1] * r], b[1][q_off: q_off + shape[1] * r]),
+                      (a[2][p_off: p_off + shape[0] * r], b[2][p_off: p_off + shape[0] * r])]
+        for x, y in pairs:
+            assert torch.isfinite(x).all() and float((x - y).norm()) <= 1e-5 * float(y.norm()) + 1e-30, (t, shape)
+    assert float((a[4] - b[4]).norm()) <= 1e-6 * float(b[4].norm())
