@@ -198,6 +198,7 @@ struct psgd_plan {
     bool p_pre_reduce_mean = false;         // the same for the products of the mean over the workers
     int32_t k1_nv = 2;                      // column vectors per lane of the first sweep (see Tuning::k1_nv)
     float* mbar = nullptr;                  // device, N floats: mean over the workers of M (workers >= kMeanWorkers, streaming kernels)
+    bool update_around = false;             // fused update: momentum and parameters go around the memory-side cache
     bool stream_hints = false;              // see Tuning::stream_hints
     bool gram_fused = false;                // Cholesky-QR panels: one launch (k_gram_chol) instead of two (set at upload)
     int32_t max_n = 0;

@@ -914,7 +914,9 @@ __global__ __launch_bounds__(kBlock) void k_q_reduce(const MatDesc* __restrict__
 
 // STREAM (see left_tile): M is read with non-temporal loads and the new error memory written with non-temporal stores;
 // otherwise it is Delta' that is written with non-temporal stores
-// OBF: Delta' is stored as bf16
+// OBF: Delta' is stored as bf16; with UPD, where Delta' is not stored: momentum and parameters are read and written with
+// non-temporal accesses.  They are touched once a step, and on a set whose M fits the memory-side cache while M, momentum and
+// parameters together do not, they would push M and the error memory out (rule and figures: the planner, update_around).
 template <int R, int V, int NV, bool UPD, bool STREAM, bool OBF>
 __device__ __forceinline__ void decomp_tile(const Tile& t, const MatDesc& d, float* __restrict__ e,
                                             const float* __restrict__ p, const float* __restrict__ q,
@@ -955,8 +957,13 @@ __device__ __forceinline__ void decomp_tile(const Tile& t, const MatDesc& d, flo
                             else ldv<V>(e + row + col[v], x[u][v]);
                             if constexpr (UPD) {
                                 if (write_out) {
-                                    ldv<V>(upd.mom + row + col[v], mo[u][v]);
-                                    ldv<V>(upd.param + row + col[v], pa[u][v]);
+                                    if constexpr (OBF) {
+                                        ldv_stream<V>(upd.mom + row + col[v], mo[u][v]);
+                                        ldv_stream<V>(upd.param + row + col[v], pa[u][v]);
+                                    } else {
+                                        ldv<V>(upd.mom + row + col[v], mo[u][v]);
+                                        ldv<V>(upd.param + row + col[v], pa[u][v]);
+                                    }
                                 }
                             }
                         }
@@ -986,8 +993,13 @@ __device__ __forceinline__ void decomp_tile(const Tile& t, const MatDesc& d, flo
                             if (write_out) {
                                 if constexpr (UPD) {
                                     momentum_step<V>(mo[u][v], pa[u][v], dl, upd.lr, upd.lam);
-                                    stv<V>(upd.mom + row + col[v], mo[u][v]);
-                                    stv<V>(upd.param + row + col[v], pa[u][v]);
+                                    if constexpr (OBF) {
+                                        stv_stream<V>(upd.mom + row + col[v], mo[u][v]);
+                                        stv_stream<V>(upd.param + row + col[v], pa[u][v]);
+                                    } else {
+                                        stv<V>(upd.mom + row + col[v], mo[u][v]);
+                                        stv<V>(upd.param + row + col[v], pa[u][v]);
+                                    }
                                 } else {
                                     // a set that fits the memory-side cache: Delta' goes around it, M and e' stay
                                     st_out<V, OBF, !STREAM>(out, row + col[v], dl);
@@ -1390,20 +1402,21 @@ static void launch_decomp(psgd_plan* plan, float* err, const float* p, const flo
     hipLaunchKernelGGL((k_decomp<R, NVV, UPDV, STREAMV, OBFV>), grid, dim3(kBlock), 0, s, plan->dev.mats,               \
                        tiles, err, p, q, static_cast<const float*>(grad), out, plan->workers,                           \
                        plan->sizes.grad_stride, plan->sizes.err_stride, plan->sizes.n_mat_elems, upd, vec_here)
-#define PSGD_LAUNCH_DECOMP_NV(UPDV, STREAMV)                                     \
+#define PSGD_LAUNCH_DECOMP_NV(UPDV, STREAMV, OBFV)                               \
     do {                                                                         \
-        if (plan->tuning.k4_nv == 1) PSGD_LAUNCH_DECOMP(1, UPDV, STREAMV, false); \
-        else PSGD_LAUNCH_DECOMP(2, UPDV, STREAMV, false);                        \
+        if (plan->tuning.k4_nv == 1) PSGD_LAUNCH_DECOMP(1, UPDV, STREAMV, OBFV); \
+        else PSGD_LAUNCH_DECOMP(2, UPDV, STREAMV, OBFV);                         \
     } while (0)
     if (upd.mom) {   // Delta' is not stored
-        if (plan->stream_hints) PSGD_LAUNCH_DECOMP_NV(true, true);
-        else PSGD_LAUNCH_DECOMP_NV(true, false);
+        if (plan->stream_hints) PSGD_LAUNCH_DECOMP_NV(true, true, false);
+        else if (plan->update_around) PSGD_LAUNCH_DECOMP_NV(true, false, true);
+        else PSGD_LAUNCH_DECOMP_NV(true, false, false);
     } else if (plan->out_dtype == PSGD_BF16) {   // one column vector per lane (planner)
         if (plan->stream_hints) PSGD_LAUNCH_DECOMP(1, false, true, true);
         else PSGD_LAUNCH_DECOMP(1, false, false, true);
     } else {
-        if (plan->stream_hints) PSGD_LAUNCH_DECOMP_NV(false, true);
-        else PSGD_LAUNCH_DECOMP_NV(false, false);
+        if (plan->stream_hints) PSGD_LAUNCH_DECOMP_NV(false, true, false);
+        else PSGD_LAUNCH_DECOMP_NV(false, false, false);
     }
 #undef PSGD_LAUNCH_DECOMP_NV
 #undef PSGD_LAUNCH_DECOMP

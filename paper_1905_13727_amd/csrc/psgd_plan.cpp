@@ -281,8 +281,14 @@ psgd_status build_tables(psgd_plan* plan) {
     // The pass fused with the momentum / parameter update moves 20 bytes per element where the plain one moves 12 and
     // wants taller tiles on a mid-sized single-worker set (LSTM-shaped set, rank 4: 163 -> 155 us with 64 rows; the
     // ResNet18-shaped sets at 1 and 16 workers are at their optimum with the plain pass's tiles).
+    // Where M fits the memory-side cache and M, momentum and parameters together do not, the last two go around it, on
+    // the plain pass's 16-row tiles.  Whole steps, us, before and after: LSTM-shaped set (31.8 M elements) rank 2 bf16 244 / 230, rank 4
+    // 254 / 246; rows of 800, 39 M elements 326 / 286; with inputs that change from step to step the first is 259 / 242.
+    // Below the line ordinary accesses and 64 rows stay (21 M elements: 209 against 217).
+    plan->update_around = plan->workers == 1 && 3 * plan->sizes.n_mat_elems * (int64_t)sizeof(float) > kStreamHintBytes &&
+                          plan->sizes.n_mat_elems * (int64_t)sizeof(float) <= kStreamHintBytes && tu.stream_hints <= 0;
     plan->tiles4u.clear();
-    if (tu.k4_rows == 0 && plan->workers == 1 && !small_set(plan) &&
+    if (tu.k4_rows == 0 && !plan->update_around && plan->workers == 1 && !small_set(plan) &&
         plan->sizes.n_mat_elems * (int64_t)sizeof(float) <= kStreamHintBytes)
         streaming_tiles(plan, 3, 64, tu.k4_nv, false, &plan->tiles4u, nullptr, nullptr);
 
