@@ -148,6 +148,9 @@ PSGD_API psgd_status psgd_plan_offsets(const psgd_plan* plan, int32_t tensor, in
  *                 device holds all row blocks of the launch at once, 0 in two launches, 2 (TEST ONLY) in one
  *                 launch unconditionally: its waits may then time out, see psgd_plan_check
  *   gram_spin     polls before a wait in that launch gives up, 1 .. 2^24 (default 2^18)
+ *   worker_mean   streaming kernels, where gram_fused holds: products of the mean over the workers' M instead of each
+ *                 worker's own; -1 (default) from four workers and 2^20 elements on when every row length is a multiple
+ *                 of 4, 0 never, 1 with any two workers
  *   ortho_rows    panels of at most this many rows (0 .. 1024) are orthogonalised by one workgroup with modified
  *                 Gram-Schmidt in LDS instead of Cholesky-QR over row blocks; default 0: none
  *   bf16_valu     bf16 gradients / output at rank <= 8: 1 streaming kernels, 0 matrix-core kernels, -1 (default) the
@@ -167,8 +170,8 @@ PSGD_API psgd_status psgd_plan_set_tuning(psgd_plan* plan, const char* key, int6
  *   hip_stream            a hipStream_t (NULL = the default stream)
  * Everything is enqueued on hip_stream; the call does not synchronise, allocate
  * or read back, except that a plan's first GPU call allocates and uploads its
- * descriptor tables (one hipMalloc, one synchronous copy; from three workers on, on the
- * kernels for rank <= 8, a second hipMalloc of 4 N bytes for the mean over the workers of
+ * descriptor tables (one hipMalloc, one synchronous copy; where the tuning key
+ * worker_mean holds, a second hipMalloc of 4 N bytes for the mean over the workers of
  * M, without which, should it fail, each worker's M is multiplied by itself).
  * Vector-shaped tensors are not touched by this call. */
 PSGD_API psgd_status psgd_compress(psgd_plan* plan, const void* grad, float* err, float* q, float* p,
@@ -203,7 +206,7 @@ PSGD_API psgd_status psgd_decompress(psgd_plan* plan, const float* p, const floa
  * psgd_plan_check (below) reports it and moves the plan to the kernels that
  * need no co-residency.  A caller that may share the GPU checks every step,
  * or sets the tuning keys resident = 0 and gram_fused = 0.
- * With three workers or more the streaming kernels also keep the mean over the
+ * Where worker_mean holds the streaming kernels also keep the mean over the
  * workers of M in plan-owned memory (only where gram_fused holds).
  * The plan's first GPU call (any entry point) uploads its tables (device
  * allocations and one copy).  After that this call, psgd_compress and psgd_decompress

@@ -23,9 +23,14 @@ constexpr int kPanelFloats = 12288;  // n*r up to this: Gram-Schmidt by one work
 constexpr int kGramRows = 256;     // rows per workgroup of the Gram / apply kernels (Cholesky-QR over row blocks)
 constexpr int kPreReduceParts = 16; // more partial-P slices than this: a reduction kernel runs before the orthogonalisation
 constexpr int kOrthoMaxRows = 1024; // largest value of the tuning key ortho_rows: panels with more rows always take the multi-workgroup route
-constexpr int kMeanWorkers = 3;    // streaming kernels: from this many workers on the products are taken of the mean over the workers
-                                   // (12 W + 8 bytes per element for the first two sweeps instead of 16 W: no gain at two workers, where
-                                   // it measured 330 us against 318 on 30 matrices of 24 M elements)
+// Streaming kernels: from this many workers on, on sets of at least kMeanElems elements whose rows are all multiples of 4, the
+// products are taken of the mean over the workers.  Whole steps, us, each worker by itself / the mean first: ResNet18-shaped set, 16
+// workers 733 / 673, 4 workers 179 / 165, 1.1 M elements and 8 workers 75 / 70.  The other side of the line: two workers save no
+// bytes (24 M elements 318 / 330); three gain without the update (144 / 134) and lose with it (164 / 175); narrower accesses lose at
+// 20 M elements in odd rows (3 workers, 260 / 304) and in the LSTM-shaped set's rows of 650 (4 workers, 720 / 761); on small sets
+// the serial walk over the workers is too long (five matrices: 4 workers 24.4 / 26.7, 16 workers 24.3 / 37.1).
+constexpr int kMeanWorkers = 4;
+constexpr int64_t kMeanElems = int64_t(1) << 20;
 constexpr int kFlatTileElems = 1024;        // baselines: elements of a flattened matrix per workgroup of the elementwise sweep (one 16-byte access per
                                             // lane and array: the smallest slices were the fastest, 8192 -> 1024: 34.7 -> 28.7 us on the ResNet18 set)
 constexpr int kFactorAlignElems = 4;        // P and Q of a matrix start at multiples of 4 floats (vector loads of factor rows)
@@ -102,7 +107,8 @@ struct Tuning {
     int64_t k1_rows = 0;    // rows per workgroup tile, P = M Q; 0: by the access width of the matrix (16 / 32 / 64; twice
                             // that for small sets)
     int64_t k1_nv = 2;      // column vectors per lane (<= kMaxVecPerLaneK1) ...
-    bool k1_nv_set = false; // ... by the tuning key; else one from kMeanWorkers workers on
+    bool k1_nv_set = false; // ... by the tuning key; else one where the mean over the workers is taken first
+    int64_t worker_mean = -1;  // products of the mean over the workers: -1 by the rule at kMeanWorkers, 0 never, 1 with any two workers
     int64_t k3_rows = 0;    // rows per workgroup tile, Q = M^T P; 0: 128, or 1024 for matrices >= 2048 x 2048
     int64_t k3_nv = 1;      // column vectors per lane (<= kMaxVecPerLaneK3)
     int64_t k4_rows = 0;    // rows per workgroup tile, decompress + residual; 0: 16 (32 for small sets)
@@ -197,7 +203,8 @@ struct psgd_plan {
     bool p_pre_reduce = false;              // some matrix has more than kPreReduceParts partial-P slices
     bool p_pre_reduce_mean = false;         // the same for the products of the mean over the workers
     int32_t k1_nv = 2;                      // column vectors per lane of the first sweep (see Tuning::k1_nv)
-    float* mbar = nullptr;                  // device, N floats: mean over the workers of M (workers >= kMeanWorkers, streaming kernels)
+    float* mbar = nullptr;                  // device, N floats: mean over the workers of M (mean_first)
+    bool mean_first = false;                // streaming kernels: products of the mean over the workers (where gram_fused holds)
     bool update_around = false;             // fused update: momentum and parameters go around the memory-side cache
     bool stream_hints = false;              // see Tuning::stream_hints
     bool gram_fused = false;                // Cholesky-QR panels: one launch (k_gram_chol) instead of two (set at upload)

@@ -7,7 +7,7 @@
 //   k_ef_right    M_w = g_w + e_w (stored in e_w's place) fused with the row dot
 //                 products of P_w = M_w Q               (Alg. 2 "Delta_w", Alg. 1 "P <- M Q");
 //                 without the add, one more subspace iteration on a stored M (Appendix G.7)
-//   k_ef_right_mean  the same from three workers on: M_w of all workers, their mean, and the products of the
+//   k_ef_right_mean  the same on large sets of four workers or more: M_w of all workers, their mean, and the products of the
 //                 mean, which the launches up to Q then work on
 //   k_gram_chol   mean over workers / column chunks, then the orthonormal factor Gram-Schmidt
 //                 gives, by Cholesky-QR over many workgroups in one launch; k_gram,
@@ -168,8 +168,8 @@ __global__ __launch_bounds__(kBlock) void k_ef_right(const MatDesc* __restrict__
 // 4 W.  HBM-bound: 12 W + 4 bytes per element.  A step is RS rows of NV vectors, 16 elements per lane and array;
 // two workers' loads are in flight in two register sets that are consumed in turn, and the even and the odd workers
 // are summed apart.  ResNet18-shaped set, whole step: 16 workers, rank 4: 732 -> 672 us (first sweep 404 us, 5.4 TB/s,
-// second 10 us where it read 715 MB); 4 workers, rank 2: 213.5 -> 202.5 us; 24 matrices of 9 M elements, 3 workers, two
-// iterations: 208 -> 199 us.  Tiles of 8 or 32 rows and two vectors per lane were 0 to 3 % slower at 16 workers, 2 to 60 % on the other two.
+// second 10 us where it read 715 MB); 4 workers, rank 2: 213.5 -> 202.5 us.  Tiles of 8 or 32 rows and two vectors per
+// lane were 0 to 5 % slower on both.  Which sets take it: kMeanWorkers.
 // ADD = false: M_w is read from e (psgd_iterate), nothing is added and e is not written.
 // STREAM: the M_w of all workers do not fit the memory-side cache: e is read and M_w written around it, which leaves it to the mean.
 template <int R, int V, int NV, bool ADD, bool GBF, bool STREAM>
@@ -1233,7 +1233,7 @@ psgd_status upload_tables(psgd_plan* plan) {
     plan->dev.kept_slice_first = reinterpret_cast<int64_t*>(b + pieces[21].at);
     plan->dev.mat_tensor = reinterpret_cast<int32_t*>(b + pieces[22].at);
     // the mean over the workers of M; without it every worker's M is multiplied by itself
-    if (plan->workers >= kMeanWorkers && !plan->hr && plan->gram_fused &&
+    if (plan->mean_first && !plan->hr && plan->gram_fused &&
         hipMalloc(reinterpret_cast<void**>(&plan->mbar), (size_t)plan->sizes.n_mat_elems * sizeof(float)) != hipSuccess) {
         plan->mbar = nullptr;
         (void)hipGetLastError();

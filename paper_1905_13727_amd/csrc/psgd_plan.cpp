@@ -272,8 +272,14 @@ psgd_status build_tables(psgd_plan* plan) {
             (int64_t(1) << 31))
             return PSGD_EUNSUPPORTED;
     std::vector<int32_t> nrb(nm, 0), ncc(nm, 0);
-    // several workers: the sums over the workers take the registers of the second column vector
-    plan->k1_nv = plan->workers >= kMeanWorkers && !tu.k1_nv_set ? 1 : (int32_t)tu.k1_nv;
+    // the mean first: the sums over the workers take the registers of the second column vector
+    if (tu.worker_mean < -1 || tu.worker_mean > 1) return PSGD_EINVAL;
+    plan->mean_first = plan->workers >= kMeanWorkers && plan->sizes.n_mat_elems >= kMeanElems;
+    for (const MatDesc& d : plan->mats)
+        if (d.vec != 4) plan->mean_first = false;
+    if (tu.worker_mean >= 0) plan->mean_first = tu.worker_mean == 1 && plan->workers > 1;
+    if (!tu.gram_fused) plan->mean_first = false;
+    plan->k1_nv = plan->mean_first && !tu.k1_nv_set ? 1 : (int32_t)tu.k1_nv;
     streaming_tiles(plan, 1, tu.k1_rows, plan->k1_nv, true, &plan->tiles1, nullptr, &ncc);
     streaming_tiles(plan, 2, tu.k3_rows, tu.k3_nv, false, &plan->tiles3, &nrb, nullptr);
     streaming_tiles(plan, 3, tu.k4_rows, tu.k4_nv, false, &plan->tiles4, nullptr, nullptr);
@@ -736,6 +742,7 @@ psgd_status psgd_plan_set_tuning(psgd_plan* plan, const char* key, int64_t value
     else if (!strcmp(key, "resident")) tu.resident = value;
     else if (!strcmp(key, "stream_hints")) tu.stream_hints = value;
     else if (!strcmp(key, "bf16_valu")) tu.bf16_valu = value;
+    else if (!strcmp(key, "worker_mean")) tu.worker_mean = value;
     else if (!strcmp(key, "gram_fused")) tu.gram_fused = value;
     else if (!strcmp(key, "gram_spin")) tu.gram_spin = value;
     else if (!strcmp(key, "ortho_rows")) tu.ortho_rows = value;

@@ -1,4 +1,4 @@
-"""Three workers or more on the streaming kernels: the products are taken of the mean over the workers' M (one mean matrix,
+"""Several workers on the streaming kernels: the products are taken of the mean over the workers' M (one mean matrix,
 plan-owned).  Compared with the general path, which multiplies every worker's M by itself: the same plan with the
 one-launch orthogonalisation switched off takes it."""
 import pytest
@@ -28,6 +28,7 @@ def test_mean_route_equals_general_route(rank, workers, grad_bf16, call):
         plan = B.Plan(SHAPES, rank, workers, B.PSGD_BF16 if grad_bf16 else B.PSGD_F32, B.PSGD_F32)
         plan.set_tuning("resident", 0)
         plan.set_tuning("gram_fused", fused)
+        plan.set_tuning("worker_mean", fused)   # small sets and odd rows do not take it by themselves
         if call == "hints":
             plan.set_tuning("stream_hints", 1)
         s = plan.sizes
