@@ -275,8 +275,10 @@ psgd_status build_tables(psgd_plan* plan) {
     // the mean first: the sums over the workers take the registers of the second column vector
     if (tu.worker_mean < -1 || tu.worker_mean > 1) return PSGD_EINVAL;
     plan->mean_first = plan->workers >= kMeanWorkers && plan->sizes.n_mat_elems >= kMeanElems;
+    int64_t narrow = 0;   // elements in rows that are not multiples of 4: a small share (a first layer's rows of 27) does not count
     for (const MatDesc& d : plan->mats)
-        if (d.vec != 4) plan->mean_first = false;
+        if (d.vec != 4) narrow += (int64_t)d.n * d.m;
+    if (narrow > plan->sizes.n_mat_elems / 16) plan->mean_first = false;
     if (tu.worker_mean >= 0) plan->mean_first = tu.worker_mean == 1 && plan->workers > 1;
     if (!tu.gram_fused) plan->mean_first = false;
     plan->k1_nv = plan->mean_first && !tu.k1_nv_set ? 1 : (int32_t)tu.k1_nv;
