@@ -281,7 +281,8 @@ psgd_status build_tables(psgd_plan* plan) {
     if (narrow > plan->sizes.n_mat_elems / 16) plan->mean_first = false;
     if (tu.worker_mean >= 0) plan->mean_first = tu.worker_mean == 1 && plan->workers > 1;
     if (!tu.gram_fused) plan->mean_first = false;
-    plan->k1_nv = plan->mean_first && !tu.k1_nv_set ? 1 : (int32_t)tu.k1_nv;
+    // (not above eight workers: narrower chunks double the partial P, and the workspace is to stay within what psgd_step_static has)
+    plan->k1_nv = plan->mean_first && plan->workers <= 8 && !tu.k1_nv_set ? 1 : (int32_t)tu.k1_nv;
     streaming_tiles(plan, 1, tu.k1_rows, plan->k1_nv, true, &plan->tiles1, nullptr, &ncc);
     streaming_tiles(plan, 2, tu.k3_rows, tu.k3_nv, false, &plan->tiles3, &nrb, nullptr);
     streaming_tiles(plan, 3, tu.k4_rows, tu.k4_nv, false, &plan->tiles4, nullptr, nullptr);
