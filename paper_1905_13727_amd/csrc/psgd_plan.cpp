@@ -151,7 +151,8 @@ static psgd_status build_hr_tables(psgd_plan* plan) {
     plan->tiles1.clear(); plan->tiles3.clear(); plan->tiles4.clear(); plan->tiles4u.clear(); plan->tilesp.clear();
     plan->small_mats.clear(); plan->tiles_gram.clear(); plan->tilesq.clear();
     plan->hr_tiles1.clear(); plan->hr_tiles3.clear(); plan->hr_tiles4.clear();
-    plan->p_pre_reduce = false;
+    plan->p_pre_reduce = plan->p_pre_reduce_mean = false;
+    plan->mean_first = plan->update_around = false;   // the streaming kernels' choices, should a tuning key have moved the plan here
     const int64_t right_rows = tu.hr_k1_rows;
     // rows per workgroup of the decompression: measured best on the 24-layer transformer set at ranks 16, 32, 64
     // (one, two, four rank tiles of 16)

@@ -360,7 +360,21 @@ static void check_hr_plan(const std::vector<psgd_shape>& shapes, int rank, int w
     psgd_plan_destroy(plan);
 }
 
+// A plan that a tuning key moves to the matrix cores keeps none of the streaming kernels' choices.
+static void check_moved_to_matrix_cores() {
+    for (int W : {1, 8}) {   // one worker: a set that M fits the memory-side cache of and M, momentum and parameters do not
+        const std::vector<psgd_shape> s = {{W == 1 ? 7168 : 1024, 4096}, {33, 1}};
+        psgd_plan* plan = nullptr;
+        CHECK(psgd_plan_create(s.data(), (int)s.size(), 2, W, PSGD_BF16, PSGD_F32, &plan) == PSGD_OK);
+        CHECK(!plan->hr && plan->mean_first == (W == 8) && plan->update_around == (W == 1));
+        CHECK(psgd_plan_set_tuning(plan, "bf16_valu", 0) == PSGD_OK);
+        CHECK(plan->hr && !plan->mean_first && !plan->update_around && !plan->p_pre_reduce_mean);
+        psgd_plan_destroy(plan);
+    }
+}
+
 int main() {
+    check_moved_to_matrix_cores();
     std::vector<std::vector<psgd_shape>> sets = {
         {{64, 27}, {64, 576}, {64, 576}},
         {{37, 91}, {7, 1}, {50, 650}, {130, 1028}, {5, 3}, {300, 2}, {1, 40}, {1031, 1}, {3, 4700}, {257, 260}},
