@@ -247,7 +247,7 @@ psgd_status build_tables(psgd_plan* plan) {
     // those kernels take (24-layer transformer-shaped set, ms per step, streaming / matrix cores: rank 2: 5.17 / 5.15,
     // rank 4: 5.28 / 5.17, rank 8: 6.43 / 5.19).
     const bool bf16 = plan->grad_dtype != PSGD_F32 || plan->out_dtype != PSGD_F32;
-    if (tu.bf16_valu < -1 || tu.bf16_valu > 1) return PSGD_EINVAL;
+    if (tu.bf16_valu < -1 || tu.bf16_valu > 1 || tu.worker_mean < -1 || tu.worker_mean > 1) return PSGD_EINVAL;
     bool hr_low = bf16 && tu.bf16_valu == 0;
     if (bf16 && tu.bf16_valu < 0 && plan->rank >= 4 &&
         plan->workers * plan->sizes.n_mat_elems * (int64_t)sizeof(float) > kStreamHintBytes) {
@@ -274,7 +274,6 @@ psgd_status build_tables(psgd_plan* plan) {
             return PSGD_EUNSUPPORTED;
     std::vector<int32_t> nrb(nm, 0), ncc(nm, 0);
     // the mean first: the sums over the workers take the registers of the second column vector
-    if (tu.worker_mean < -1 || tu.worker_mean > 1) return PSGD_EINVAL;
     plan->mean_first = plan->workers >= kMeanWorkers && plan->sizes.n_mat_elems >= kMeanElems;
     int64_t narrow = 0;   // elements in rows that are not multiples of 4: a small share (a first layer's rows of 27) does not count
     for (const MatDesc& d : plan->mats)

@@ -187,3 +187,14 @@ def test_which_kernels_a_plan_runs():
     import ctypes as C
     r = C.c_int32()
     assert lib.psgd_plan_path(None, C.byref(r)) == B.PSGD_EINVAL and lib.psgd_plan_path(p._h, None) == B.PSGD_EINVAL
+
+
+@pytest.mark.parametrize("rank", [2, 16])
+def test_worker_mean_out_of_range_is_refused_on_every_kernel_set(rank):
+    plan = B.Plan([(64, 576)], rank, 4)
+    for bad in (-2, 2):
+        with pytest.raises(B.PsgdError) as ei:
+            plan.set_tuning("worker_mean", bad)
+        assert ei.value.status == B.PSGD_EINVAL
+    for good in (0, 1, -1):
+        plan.set_tuning("worker_mean", good)
