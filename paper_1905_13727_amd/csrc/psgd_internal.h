@@ -106,8 +106,7 @@ struct RTile {
 struct Tuning {
     int64_t k1_rows = 0;    // rows per workgroup tile, P = M Q; 0: by the access width of the matrix (16 / 32 / 64; twice
                             // that for small sets)
-    int64_t k1_nv = 2;      // column vectors per lane (<= kMaxVecPerLaneK1) ...
-    bool k1_nv_set = false; // ... by the tuning key; else one where the mean over the workers is taken first
+    int64_t k1_nv = 2;      // column vectors per lane (<= kMaxVecPerLaneK1); products of the mean over the workers: always one
     int64_t worker_mean = -1;  // products of the mean over the workers: -1 by the rule at kMeanWorkers, 0 never, 1 with any two workers
     int64_t k3_rows = 0;    // rows per workgroup tile, Q = M^T P; 0: 128, or 1024 for matrices >= 2048 x 2048
     int64_t k3_nv = 1;      // column vectors per lane (<= kMaxVecPerLaneK3)
@@ -145,7 +144,9 @@ struct Tuning {
 
 struct DeviceTables {
     MatDesc* mats = nullptr;
+    MatDesc* mats_mean = nullptr;
     Tile* tiles1 = nullptr;
+    Tile* tiles1m = nullptr;
     Tile* tiles3 = nullptr;
     Tile* tiles4 = nullptr;
     Tile* tiles4u = nullptr;   // decompression fused with the update: tiles of its own, or null (then tiles4)
@@ -202,7 +203,8 @@ struct psgd_plan {
     std::vector<psgd::Tile> tilesp;         // 64-element slices of the n x r panels (pre-reduction of partial P)
     bool p_pre_reduce = false;              // some matrix has more than kPreReduceParts partial-P slices
     bool p_pre_reduce_mean = false;         // the same for the products of the mean over the workers
-    int32_t k1_nv = 2;                      // column vectors per lane of the first sweep (see Tuning::k1_nv)
+    std::vector<psgd::Tile> tiles1m;        // mean_first: the first sweep's tiles, one column vector per lane ...
+    std::vector<psgd::MatDesc> mats_mean;   // ... and the same matrices with their column chunks
     float* mbar = nullptr;                  // device, N floats: mean over the workers of M (mean_first)
     bool mean_first = false;                // streaming kernels: products of the mean over the workers (where gram_fused holds)
     bool update_around = false;             // fused update: momentum and parameters go around the memory-side cache

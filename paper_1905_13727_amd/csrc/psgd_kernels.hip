@@ -172,30 +172,25 @@ __global__ __launch_bounds__(kBlock) void k_ef_right(const MatDesc* __restrict__
 // lane were 0 to 5 % slower on both.  Which sets take it: kMeanWorkers.
 // ADD = false: M_w is read from e (psgd_iterate), nothing is added and e is not written.
 // STREAM: the M_w of all workers do not fit the memory-side cache: e is read and M_w written around it, which leaves it to the mean.
-template <int R, int V, int NV, bool ADD, bool GBF, bool STREAM>
+template <int R, int V, bool ADD, bool GBF, bool STREAM>
 __device__ __forceinline__ void ef_right_mean_tile(const Tile& t, const MatDesc& d, const void* __restrict__ g,
                                                    float* __restrict__ e, const float* __restrict__ q,
                                                    float* __restrict__ ppart, float* __restrict__ mbar, int workers,
                                                    int64_t gstride, int64_t estride) {
     constexpr unsigned GS = GBF ? 2u : 4u;
-    constexpr int RS = 16 / (NV * V) * R <= kWave ? 16 / (NV * V) : 8;   // RS * R results fit the 64 lanes
+    constexpr int RS = 16 / V * R <= kWave ? 16 / V : 8;   // RS * R results fit the 64 lanes
     static_assert(RS * R <= kWave, "one lane per (row, rank) result of a step");
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ri = d.r;
     const float inv_w = 1.0f / (float)workers;
 
-    float qr[NV][V][R];
-    unsigned coff[NV], goff[NV];   // missing columns: out of range (loads read zero, stores are dropped)
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        const int jv = lane + kWave * v;
-        const bool valid = jv < t.nvec;
-        const int col = (t.vec0 + jv) * V;
-        load_factor_rows<R, V>(q + d.q_off + (int64_t)col * ri, ri, valid, qr[v]);
-        coff[v] = valid ? (unsigned)col * 4u : kOutOfRange;
-        goff[v] = valid ? (unsigned)col * GS : kOutOfRange;
-    }
+    float qr[V][R];
+    const bool valid = lane < t.nvec;   // a missing column: out of range (loads read zero, stores are dropped)
+    const int col = (t.vec0 + lane) * V;
+    load_factor_rows<R, V>(q + d.q_off + (int64_t)col * ri, ri, valid, qr);
+    const unsigned coff = valid ? (unsigned)col * 4u : kOutOfRange;
+    const unsigned goff = valid ? (unsigned)col * GS : kOutOfRange;
     int rb, rn;
     wave_rows(t.nrows, wave, &rb, &rn);
     const int64_t strip = d.off + (int64_t)(t.row0 + rb) * d.m;
@@ -204,45 +199,37 @@ __device__ __forceinline__ void ef_right_mean_tile(const Tile& t, const MatDesc&
     for (int i0 = 0; i0 < rn; i0 += RS) {
         const unsigned el0 = (unsigned)i0 * (unsigned)d.m;
         // a worker past the last one has empty descriptors: zeros are read, nothing is stored
-        auto load = [&](int w, float (&gv)[RS][NV][V], float (&ev)[RS][NV][V]) {
+        auto load = [&](int w, float (&gv)[RS][V], float (&ev)[RS][V]) {
             const int ww = w < workers ? w : 0;
             const int64_t n_el = w < workers ? elems : 0;
             const buf_rsrc er = make_rsrc(e + (int64_t)ww * estride + strip, n_el * 4);
             if constexpr (ADD) {
                 const buf_rsrc gr = make_rsrc(static_cast<const char*>(g) + ((int64_t)ww * gstride + strip) * GS, n_el * GS);
 #pragma unroll
-                for (int i = 0; i < RS; ++i)
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) buf_ld_grad<V, GBF>(gr, goff[v] + (el0 + (unsigned)i * (unsigned)d.m) * GS, gv[i][v]);
+                for (int i = 0; i < RS; ++i) buf_ld_grad<V, GBF>(gr, goff + (el0 + (unsigned)i * (unsigned)d.m) * GS, gv[i]);
             }
 #pragma unroll
-            for (int i = 0; i < RS; ++i)
-#pragma unroll
-                for (int v = 0; v < NV; ++v) buf_ldv<V>(er, coff[v] + (el0 + (unsigned)i * (unsigned)d.m) * 4u, ev[i][v], STREAM);
+            for (int i = 0; i < RS; ++i) buf_ldv<V>(er, coff + (el0 + (unsigned)i * (unsigned)d.m) * 4u, ev[i], STREAM);
         };
-        float sum[RS][NV][V], odd[RS][NV][V];   // over the even and the odd workers
+        float sum[RS][V], odd[RS][V];   // over the even and the odd workers
 #pragma unroll
         for (int i = 0; i < RS; ++i)
 #pragma unroll
-            for (int v = 0; v < NV; ++v)
-#pragma unroll
-                for (int x = 0; x < V; ++x) sum[i][v][x] = odd[i][v][x] = 0.f;
-        auto take = [&](int w, float (&gv)[RS][NV][V], float (&ev)[RS][NV][V], float (&to)[RS][NV][V]) {
+            for (int x = 0; x < V; ++x) sum[i][x] = odd[i][x] = 0.f;
+        auto take = [&](int w, float (&gv)[RS][V], float (&ev)[RS][V], float (&to)[RS][V]) {
             const buf_rsrc er = make_rsrc(e + (int64_t)(w < workers ? w : 0) * estride + strip, w < workers ? elems * 4 : 0);
 #pragma unroll
-            for (int i = 0; i < RS; ++i)
+            for (int i = 0; i < RS; ++i) {
+                if constexpr (ADD) {
 #pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    if constexpr (ADD) {
-#pragma unroll
-                        for (int x = 0; x < V; ++x) ev[i][v][x] += gv[i][v][x];
-                        buf_stv<V>(er, coff[v] + (el0 + (unsigned)i * (unsigned)d.m) * 4u, ev[i][v], STREAM);
-                    }
-#pragma unroll
-                    for (int x = 0; x < V; ++x) to[i][v][x] += ev[i][v][x];
+                    for (int x = 0; x < V; ++x) ev[i][x] += gv[i][x];
+                    buf_stv<V>(er, coff + (el0 + (unsigned)i * (unsigned)d.m) * 4u, ev[i], STREAM);
                 }
+#pragma unroll
+                for (int x = 0; x < V; ++x) to[i][x] += ev[i][x];
+            }
         };
-        float ga[RS][NV][V], ea[RS][NV][V], gb[RS][NV][V], eb[RS][NV][V];
+        float ga[RS][V], ea[RS][V], gb[RS][V], eb[RS][V];
         load(0, ga, ea);
         load(1, gb, eb);
         for (int w = 0; w < workers; w += 2) {
@@ -255,18 +242,13 @@ __device__ __forceinline__ void ef_right_mean_tile(const Tile& t, const MatDesc&
 #pragma unroll
         for (int i = 0; i < RS; ++i) {
 #pragma unroll
-            for (int v = 0; v < NV; ++v) {
-#pragma unroll
-                for (int x = 0; x < V; ++x) sum[i][v][x] = (sum[i][v][x] + odd[i][v][x]) * inv_w;
-                buf_stv<V>(mres, coff[v] + (el0 + (unsigned)i * (unsigned)d.m) * 4u, sum[i][v]);
-            }
+            for (int x = 0; x < V; ++x) sum[i][x] = (sum[i][x] + odd[i][x]) * inv_w;
+            buf_stv<V>(mres, coff + (el0 + (unsigned)i * (unsigned)d.m) * 4u, sum[i]);
 #pragma unroll
             for (int k = 0; k < R; ++k) {
                 float s = 0.f;
 #pragma unroll
-                for (int v = 0; v < NV; ++v)
-#pragma unroll
-                    for (int x = 0; x < V; ++x) s = fmaf(sum[i][v][x], qr[v][x][k], s);
+                for (int x = 0; x < V; ++x) s = fmaf(sum[i][x], qr[x][k], s);
                 part[i * R + k] = s;
             }
         }
@@ -277,7 +259,7 @@ __device__ __forceinline__ void ef_right_mean_tile(const Tile& t, const MatDesc&
     }
 }
 
-template <int R, int NV, bool ADD, bool GBF, bool STREAM>
+template <int R, bool ADD, bool GBF, bool STREAM>
 __global__ __launch_bounds__(kBlock) void k_ef_right_mean(const MatDesc* __restrict__ mats, const Tile* __restrict__ tiles,
                                                           const void* __restrict__ grad, float* __restrict__ err,
                                                           const float* __restrict__ q, float* __restrict__ ws,
@@ -285,9 +267,9 @@ __global__ __launch_bounds__(kBlock) void k_ef_right_mean(const MatDesc* __restr
                                                           int64_t estride) {
     const Tile t = tiles[blockIdx.x];
     const MatDesc d = mats[t.mat];
-    if (d.vec == 4) ef_right_mean_tile<R, 4, NV, ADD, GBF, STREAM>(t, d, grad, err, q, ws, mbar, workers, gstride, estride);
-    else if (d.vec == 2) ef_right_mean_tile<R, 2, NV, ADD, GBF, STREAM>(t, d, grad, err, q, ws, mbar, workers, gstride, estride);
-    else ef_right_mean_tile<R, 1, NV, ADD, GBF, STREAM>(t, d, grad, err, q, ws, mbar, workers, gstride, estride);
+    if (d.vec == 4) ef_right_mean_tile<R, 4, ADD, GBF, STREAM>(t, d, grad, err, q, ws, mbar, workers, gstride, estride);
+    else if (d.vec == 2) ef_right_mean_tile<R, 2, ADD, GBF, STREAM>(t, d, grad, err, q, ws, mbar, workers, gstride, estride);
+    else ef_right_mean_tile<R, 1, ADD, GBF, STREAM>(t, d, grad, err, q, ws, mbar, workers, gstride, estride);
 }
 
 // sum of `nparts` partial slices (stride `stride` floats) at `src`, in slice order, eight loads in flight
@@ -1158,7 +1140,7 @@ psgd_status upload_tables(psgd_plan* plan) {
         if (st != PSGD_OK) return st;
     }
     struct Piece { const void* src; size_t bytes; size_t at; };
-    Piece pieces[23] = {
+    Piece pieces[25] = {
         {plan->mats.data(), plan->mats.size() * sizeof(MatDesc), 0},
         {plan->tiles1.data(), plan->tiles1.size() * sizeof(Tile), 0},
         {plan->tiles3.data(), plan->tiles3.size() * sizeof(Tile), 0},
@@ -1182,6 +1164,8 @@ psgd_status upload_tables(psgd_plan* plan) {
         {plan->kept_slice_mat.data(), plan->kept_slice_mat.size() * sizeof(int32_t), 0},
         {plan->kept_slice_first.data(), plan->kept_slice_first.size() * sizeof(int64_t), 0},
         {plan->mat_tensor.data(), plan->mat_tensor.size() * sizeof(int32_t), 0},
+        {plan->mats_mean.data(), plan->mats_mean.size() * sizeof(MatDesc), 0},
+        {plan->tiles1m.data(), plan->tiles1m.size() * sizeof(Tile), 0},
     };
     size_t total = 0;
     for (Piece& pc : pieces) {
@@ -1232,6 +1216,8 @@ psgd_status upload_tables(psgd_plan* plan) {
     plan->dev.kept_slice_mat = reinterpret_cast<int32_t*>(b + pieces[20].at);
     plan->dev.kept_slice_first = reinterpret_cast<int64_t*>(b + pieces[21].at);
     plan->dev.mat_tensor = reinterpret_cast<int32_t*>(b + pieces[22].at);
+    plan->dev.mats_mean = reinterpret_cast<MatDesc*>(b + pieces[23].at);
+    plan->dev.tiles1m = reinterpret_cast<Tile*>(b + pieces[24].at);
     // the mean over the workers of M; without it every worker's M is multiplied by itself
     if (plan->mean_first && !plan->hr && plan->gram_fused &&
         hipMalloc(reinterpret_cast<void**>(&plan->mbar), (size_t)plan->sizes.n_mat_elems * sizeof(float)) != hipSuccess) {
@@ -1321,21 +1307,25 @@ psgd_status check_plan(psgd_plan* plan, void* stream) {
     return PSGD_OK;
 }
 
+// `mean`: err is the mean over the workers, on its own tiles
 template <int R>
 static void launch_ef_right(psgd_plan* plan, const void* grad, float* err, const float* q, float* ws,
-                            hipStream_t s, bool add, int workers) {
-    dim3 grid((unsigned)plan->tiles1.size(), (unsigned)workers);
+                            hipStream_t s, bool add, bool mean) {
+    dim3 grid((unsigned)(mean ? plan->tiles1m : plan->tiles1).size(), mean ? 1u : (unsigned)plan->workers);
+    const MatDesc* mats = mean ? plan->dev.mats_mean : plan->dev.mats;
+    const Tile* tiles = mean ? plan->dev.tiles1m : plan->dev.tiles1;
+    const bool one = mean || plan->tuning.k1_nv == 1;
 #define PSGD_LAUNCH_RIGHT(NVV, ADDV, GBFV)                                                                             \
-    hipLaunchKernelGGL((k_ef_right<R, NVV, ADDV, GBFV>), grid, dim3(kBlock), 0, s, plan->dev.mats, plan->dev.tiles1,   \
-                       grad, err, q, ws, plan->sizes.grad_stride, plan->sizes.err_stride)
+    hipLaunchKernelGGL((k_ef_right<R, NVV, ADDV, GBFV>), grid, dim3(kBlock), 0, s, mats, tiles, grad, err, q, ws,      \
+                       plan->sizes.grad_stride, plan->sizes.err_stride)
     if (!add) {   // the gradient is not read
-        if (plan->k1_nv == 1) PSGD_LAUNCH_RIGHT(1, false, false);
+        if (one) PSGD_LAUNCH_RIGHT(1, false, false);
         else PSGD_LAUNCH_RIGHT(2, false, false);
     } else if (plan->grad_dtype == PSGD_BF16) {
-        if (plan->k1_nv == 1) PSGD_LAUNCH_RIGHT(1, true, true);
+        if (one) PSGD_LAUNCH_RIGHT(1, true, true);
         else PSGD_LAUNCH_RIGHT(2, true, true);
     } else {
-        if (plan->k1_nv == 1) PSGD_LAUNCH_RIGHT(1, true, false);
+        if (one) PSGD_LAUNCH_RIGHT(1, true, false);
         else PSGD_LAUNCH_RIGHT(2, true, false);
     }
 #undef PSGD_LAUNCH_RIGHT
@@ -1344,27 +1334,21 @@ static void launch_ef_right(psgd_plan* plan, const void* grad, float* err, const
 template <int R>
 static void launch_ef_right_mean(psgd_plan* plan, const void* grad, float* err, const float* q, float* ws,
                                  hipStream_t s, bool add) {
-    dim3 grid((unsigned)plan->tiles1.size());
-#define PSGD_LAUNCH_MEAN(NVV, ADDV, GBFV, STREAMV)                                                                     \
-    hipLaunchKernelGGL((k_ef_right_mean<R, NVV, ADDV, GBFV, STREAMV>), grid, dim3(kBlock), 0, s, plan->dev.mats,       \
-                       plan->dev.tiles1, grad, err, q, ws, plan->mbar, plan->workers, plan->sizes.grad_stride,         \
+    dim3 grid((unsigned)plan->tiles1m.size());
+#define PSGD_LAUNCH_MEAN(ADDV, GBFV, STREAMV)                                                                          \
+    hipLaunchKernelGGL((k_ef_right_mean<R, ADDV, GBFV, STREAMV>), grid, dim3(kBlock), 0, s, plan->dev.mats_mean,       \
+                       plan->dev.tiles1m, grad, err, q, ws, plan->mbar, plan->workers, plan->sizes.grad_stride,        \
                        plan->sizes.err_stride)
-#define PSGD_LAUNCH_MEAN_NV(ADDV, GBFV, STREAMV)                         \
-    do {                                                                 \
-        if (plan->k1_nv == 1) PSGD_LAUNCH_MEAN(1, ADDV, GBFV, STREAMV);  \
-        else PSGD_LAUNCH_MEAN(2, ADDV, GBFV, STREAMV);                   \
-    } while (0)
     const bool bf = plan->grad_dtype == PSGD_BF16;
     if (plan->stream_hints) {
-        if (!add) PSGD_LAUNCH_MEAN_NV(false, false, true);
-        else if (bf) PSGD_LAUNCH_MEAN_NV(true, true, true);
-        else PSGD_LAUNCH_MEAN_NV(true, false, true);
+        if (!add) PSGD_LAUNCH_MEAN(false, false, true);
+        else if (bf) PSGD_LAUNCH_MEAN(true, true, true);
+        else PSGD_LAUNCH_MEAN(true, false, true);
     } else {
-        if (!add) PSGD_LAUNCH_MEAN_NV(false, false, false);
-        else if (bf) PSGD_LAUNCH_MEAN_NV(true, true, false);
-        else PSGD_LAUNCH_MEAN_NV(true, false, false);
+        if (!add) PSGD_LAUNCH_MEAN(false, false, false);
+        else if (bf) PSGD_LAUNCH_MEAN(true, true, false);
+        else PSGD_LAUNCH_MEAN(true, false, false);
     }
-#undef PSGD_LAUNCH_MEAN_NV
 #undef PSGD_LAUNCH_MEAN
 }
 
@@ -1463,20 +1447,21 @@ psgd_status launch_compress(psgd_plan* plan, const void* grad, float* err, float
     const bool mean = plan->mbar && plan->gram_fused;
     const int workers = mean ? 1 : plan->workers;   // of the partial P and Q
     const float* m = mean ? plan->mbar : err;
-    if (mean && again) PSGD_RANK_SWITCH(launch_ef_right, plan, plan->mbar, plan->mbar, q, ws, s, false, 1)
+    const MatDesc* mats = mean ? plan->dev.mats_mean : plan->dev.mats;   // with the column chunks of the partial P
+    if (mean && again) PSGD_RANK_SWITCH(launch_ef_right, plan, plan->mbar, plan->mbar, q, ws, s, false, true)
     else if (mean) PSGD_RANK_SWITCH(launch_ef_right_mean, plan, g, err, q, ws, s, add)
-    else PSGD_RANK_SWITCH(launch_ef_right, plan, g, err, q, ws, s, add, plan->workers)
+    else PSGD_RANK_SWITCH(launch_ef_right, plan, g, err, q, ws, s, add, false)
     PSGD_HIP(hipGetLastError(), "launch k_ef_right");
     PSGD_MARK(1);
 
     const int pre_reduced = (mean ? plan->p_pre_reduce_mean : plan->p_pre_reduce) ? 1 : 0;
     if (pre_reduced) {
-        hipLaunchKernelGGL(k_q_reduce, dim3((unsigned)plan->tilesp.size()), dim3(kBlock), 0, s, plan->dev.mats,
+        hipLaunchKernelGGL(k_q_reduce, dim3((unsigned)plan->tilesp.size()), dim3(kBlock), 0, s, mats,
                            plan->dev.tilesp, ws, static_cast<float*>(nullptr), workers, 1);
         PSGD_HIP(hipGetLastError(), "launch k_q_reduce (partial P)");
     }
     if (!plan->small_mats.empty()) {
-        hipLaunchKernelGGL(k_ortho, dim3((unsigned)plan->small_mats.size()), dim3(kOrthoBlock), 0, s, plan->dev.mats,
+        hipLaunchKernelGGL(k_ortho, dim3((unsigned)plan->small_mats.size()), dim3(kOrthoBlock), 0, s, mats,
                            plan->dev.small_mats, ws, p, workers, pre_reduced);
         PSGD_HIP(hipGetLastError(), "launch k_ortho");
     }
@@ -1485,7 +1470,7 @@ psgd_status launch_compress(psgd_plan* plan, const void* grad, float* err, float
         const dim3 ggrid((unsigned)plan->tiles_gram.size());
         slot_t* gmail = reinterpret_cast<slot_t*>(plan->dev.gram_mail);
 #define PSGD_LAUNCH_GRAM_CHOL(RR)                                                                                     \
-    hipLaunchKernelGGL((k_gram_chol<RR>), ggrid, dim3(kBlock), 0, s, plan->dev.mats, plan->dev.tiles_gram, ws, p, gmail, \
+    hipLaunchKernelGGL((k_gram_chol<RR>), ggrid, dim3(kBlock), 0, s, mats, plan->dev.tiles_gram, ws, p, gmail, \
                        plan->dev.gram_sync, workers, pre_reduced, (unsigned)plan->tuning.gram_spin)
         switch (plan->rank) {
             case 1: PSGD_LAUNCH_GRAM_CHOL(1); break;
@@ -1504,10 +1489,10 @@ psgd_status launch_compress(psgd_plan* plan, const void* grad, float* err, float
     } else if (!plan->tiles_gram.empty()) {
         const size_t float_bytes = (size_t)(plan->ws_ppart_floats + plan->ws_qpart_floats) * sizeof(float);
         double* gram = reinterpret_cast<double*>(static_cast<char*>(workspace) + (float_bytes + 255) / 256 * 256);
-        hipLaunchKernelGGL(k_gram, dim3((unsigned)plan->tiles_gram.size()), dim3(kBlock), 0, s, plan->dev.mats,
+        hipLaunchKernelGGL(k_gram, dim3((unsigned)plan->tiles_gram.size()), dim3(kBlock), 0, s, mats,
                            plan->dev.tiles_gram, ws, p, gram, workers, pre_reduced);
         PSGD_HIP(hipGetLastError(), "launch k_gram");
-        hipLaunchKernelGGL(k_chol_apply, dim3((unsigned)plan->tiles_gram.size()), dim3(kBlock), 0, s, plan->dev.mats,
+        hipLaunchKernelGGL(k_chol_apply, dim3((unsigned)plan->tiles_gram.size()), dim3(kBlock), 0, s, mats,
                            plan->dev.tiles_gram, gram, p);
         PSGD_HIP(hipGetLastError(), "launch k_chol_apply");
     }

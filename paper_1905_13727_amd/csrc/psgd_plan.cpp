@@ -149,6 +149,7 @@ static psgd_status build_hr_tables(psgd_plan* plan) {
     const int64_t W = plan->workers;
     const size_t nm = plan->mats.size();
     plan->tiles1.clear(); plan->tiles3.clear(); plan->tiles4.clear(); plan->tiles4u.clear(); plan->tilesp.clear();
+    plan->tiles1m.clear(); plan->mats_mean.clear();
     plan->small_mats.clear(); plan->tiles_gram.clear(); plan->tilesq.clear();
     plan->hr_tiles1.clear(); plan->hr_tiles3.clear(); plan->hr_tiles4.clear();
     plan->p_pre_reduce = plan->p_pre_reduce_mean = false;
@@ -273,7 +274,6 @@ psgd_status build_tables(psgd_plan* plan) {
             (int64_t(1) << 31))
             return PSGD_EUNSUPPORTED;
     std::vector<int32_t> nrb(nm, 0), ncc(nm, 0);
-    // the mean first: the sums over the workers take the registers of the second column vector
     plan->mean_first = plan->workers >= kMeanWorkers && plan->sizes.n_mat_elems >= kMeanElems;
     int64_t narrow = 0;   // elements in rows that are not multiples of 4: a small share (a first layer's rows of 27) does not count
     for (const MatDesc& d : plan->mats)
@@ -281,9 +281,13 @@ psgd_status build_tables(psgd_plan* plan) {
     if (narrow > plan->sizes.n_mat_elems / 16) plan->mean_first = false;
     if (tu.worker_mean >= 0) plan->mean_first = tu.worker_mean == 1 && plan->workers > 1;
     if (!tu.gram_fused) plan->mean_first = false;
-    // (not above eight workers: narrower chunks double the partial P, and the workspace is to stay within what psgd_step_static has)
-    plan->k1_nv = plan->mean_first && plan->workers <= 8 && !tu.k1_nv_set ? 1 : (int32_t)tu.k1_nv;
-    streaming_tiles(plan, 1, tu.k1_rows, plan->k1_nv, true, &plan->tiles1, nullptr, &ncc);
+    streaming_tiles(plan, 1, tu.k1_rows, tu.k1_nv, true, &plan->tiles1, nullptr, &ncc);
+    // The mean first: a list of its own with one column vector per lane, as the sums over the workers take the registers of the
+    // second.  Half as wide chunks at most double the partial P of one product, and there is one product instead of W >= 2: the
+    // slices lie within those of the workers' own products, whose list stays for when the mean cannot be had.
+    std::vector<int32_t> ncc_mean(nm, 0);
+    plan->tiles1m.clear();
+    if (plan->mean_first) streaming_tiles(plan, 1, tu.k1_rows, 1, true, &plan->tiles1m, nullptr, &ncc_mean);
     streaming_tiles(plan, 2, tu.k3_rows, tu.k3_nv, false, &plan->tiles3, &nrb, nullptr);
     streaming_tiles(plan, 3, tu.k4_rows, tu.k4_nv, false, &plan->tiles4, nullptr, nullptr);
 
@@ -354,12 +358,16 @@ psgd_status build_tables(psgd_plan* plan) {
     plan->sizes.workspace_bytes =
         std::max<int64_t>(256, round_up((pp + qp) * (int64_t)sizeof(float), 256) + gp * (int64_t)sizeof(double));
 
+    plan->mats_mean.clear();
+    if (plan->mean_first) plan->mats_mean = plan->mats;
+    for (size_t i = 0; i < plan->mats_mean.size(); ++i) plan->mats_mean[i].n_cchunk = ncc_mean[i];
+
     // the same slicing of the n x r panels, used when a matrix has many partial-P slices
     plan->tilesp.clear();
     plan->p_pre_reduce = plan->p_pre_reduce_mean = false;
     for (size_t i = 0; i < nm; ++i) {
         const MatDesc& d = plan->mats[i];
-        if (d.n_cchunk > 2 * kPreReduceParts) plan->p_pre_reduce_mean = true;   // half as wide chunks
+        if (ncc_mean[i] > 2 * kPreReduceParts) plan->p_pre_reduce_mean = true;   // half as wide chunks
         if (W * d.n_cchunk > kPreReduceParts) plan->p_pre_reduce = true;
         const int64_t total = (int64_t)d.n * d.r;
         for (int64_t e = 0; e < total; e += kWave) {
@@ -394,6 +402,7 @@ psgd_status build_tables(psgd_plan* plan) {
     // workers whole-list order loses 1-3 % in every sweep).
     const int64_t order = tu.xcd_order >= 0 ? tu.xcd_order : (W == 1 && plan->stream_hints ? 1 : group_tiles(plan));
     order_tiles(plan->tiles1, order);
+    order_tiles(plan->tiles1m, order);
     order_tiles(plan->tiles3, order);
     order_tiles(plan->tiles4, order);
     order_tiles(plan->tiles4u, order);
@@ -732,7 +741,7 @@ psgd_status psgd_plan_set_tuning(psgd_plan* plan, const char* key, int64_t value
     if (plan->uploaded) return PSGD_EINVAL;
     Tuning tu = plan->tuning;
     if (!strcmp(key, "k1_rows")) tu.k1_rows = value;
-    else if (!strcmp(key, "k1_nv")) { tu.k1_nv = value; tu.k1_nv_set = true; }
+    else if (!strcmp(key, "k1_nv")) tu.k1_nv = value;
     else if (!strcmp(key, "k3_rows")) tu.k3_rows = value;
     else if (!strcmp(key, "k3_nv")) tu.k3_nv = value;
     else if (!strcmp(key, "k4_rows")) tu.k4_rows = value;

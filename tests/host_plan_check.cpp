@@ -373,8 +373,66 @@ static void check_moved_to_matrix_cores() {
     }
 }
 
+// The mean over the workers first: the workspace and the work-lists of the other route, which runs where the mean cannot be
+// had, are those of a plan that never takes the mean.
+static void check_worker_mean() {
+    const std::vector<std::vector<psgd_shape>> sets = {
+        {{64, 27}, {64, 576}, {64, 576}, {64, 576}, {64, 576}, {128, 576}, {128, 1152}, {128, 1152}, {128, 1152},
+         {128, 64}, {256, 1152}, {256, 2304}, {256, 2304}, {256, 2304}, {256, 128}, {512, 2304}, {512, 4608},
+         {512, 4608}, {512, 4608}, {512, 256}, {10, 512}, {9610, 1}},
+        {{2048, 640}, {33, 1}}, {{1024, 800}, {800, 1024}}, {{600, 2048}, {33, 1}}, {{16, 70000}}, {{8, 140000}},
+        {{700, 63}, {700, 65}, {2400, 600}},
+    };
+    auto same = [](const std::vector<Tile>& a, const std::vector<Tile>& b) {
+        if (a.size() != b.size()) return false;
+        for (size_t i = 0; i < a.size(); ++i)
+            if (a[i].mat != b[i].mat || a[i].row0 != b[i].row0 || a[i].nrows != b[i].nrows || a[i].vec0 != b[i].vec0 ||
+                a[i].nvec != b[i].nvec || a[i].part != b[i].part)
+                return false;
+        return true;
+    };
+    for (auto& s : sets)
+        for (int rank : {1, 5, 8})
+            for (int W : {2, 3, 4, 5, 8, 9, 16})
+                for (int nv : {0, 1, 2}) {   // 0: as the planner has it
+                    psgd_plan *own = nullptr, *mean = nullptr;
+                    CHECK(psgd_plan_create(s.data(), (int)s.size(), rank, W, PSGD_F32, PSGD_F32, &own) == PSGD_OK);
+                    CHECK(psgd_plan_create(s.data(), (int)s.size(), rank, W, PSGD_F32, PSGD_F32, &mean) == PSGD_OK);
+                    CHECK(psgd_plan_set_tuning(own, "worker_mean", 0) == PSGD_OK && !own->mean_first);
+                    // by the rule: four workers, 2^20 elements (every set has them), rows of multiples of 4 but for a small share
+                    CHECK(mean->mean_first == (W >= kMeanWorkers));
+                    CHECK(mean->sizes.workspace_bytes == own->sizes.workspace_bytes);
+                    CHECK(psgd_plan_set_tuning(mean, "worker_mean", 1) == PSGD_OK && mean->mean_first);
+                    if (nv) CHECK(psgd_plan_set_tuning(own, "k1_nv", nv) == PSGD_OK && psgd_plan_set_tuning(mean, "k1_nv", nv) == PSGD_OK);
+                    CHECK(mean->sizes.workspace_bytes == own->sizes.workspace_bytes);
+                    CHECK(mean->p_pre_reduce == own->p_pre_reduce && same(mean->tiles1, own->tiles1));
+                    CHECK(same(mean->tiles3, own->tiles3) && same(mean->tiles4, own->tiles4));
+                    CHECK(own->tiles1m.empty() && mean->mats_mean.size() == mean->mats.size());
+                    for (size_t i = 0; i < mean->mats.size(); ++i) {
+                        const MatDesc &a = mean->mats[i], &b = own->mats[i], &m = mean->mats_mean[i];
+                        CHECK(a.n_cchunk == b.n_cchunk && a.ppart_off == b.ppart_off && a.qpart_off == b.qpart_off);
+                        CHECK(m.ppart_off == a.ppart_off && m.qpart_off == a.qpart_off && m.n_rblock == a.n_rblock && m.off == a.off);
+                        CHECK(m.n_cchunk <= W * a.n_cchunk);   // the slices of the mean's products lie within the workers' own
+                    }
+                    if (rank == 1 && W == 4 && !nv) {
+                        std::swap(mean->mats, mean->mats_mean);   // the launches over the mean see these descriptors
+                        check_cover(mean, mean->tiles1m, 1, 1);
+                    }
+                    psgd_plan_destroy(own);
+                    psgd_plan_destroy(mean);
+                }
+    {   // a set that fits the library-owned workspace
+        psgd_plan* plan = nullptr;
+        CHECK(psgd_plan_create(sets[0].data(), (int)sets[0].size(), 8, 8, PSGD_F32, PSGD_F32, &plan) == PSGD_OK);
+        CHECK(plan->mean_first && plan->sizes.workspace_bytes == 28875008);
+        CHECK(plan->sizes.workspace_bytes <= (int64_t)PSGD_STATIC_WORKSPACE_BYTES);
+        psgd_plan_destroy(plan);
+    }
+}
+
 int main() {
     check_moved_to_matrix_cores();
+    check_worker_mean();
     std::vector<std::vector<psgd_shape>> sets = {
         {{64, 27}, {64, 576}, {64, 576}},
         {{37, 91}, {7, 1}, {50, 650}, {130, 1028}, {5, 3}, {300, 2}, {1, 40}, {1031, 1}, {3, 4700}, {257, 260}},

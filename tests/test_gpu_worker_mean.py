@@ -79,3 +79,34 @@ def test_mean_route_equals_general_route(rank, workers, grad_bf16, call):
         for x, y in pairs:
             assert torch.isfinite(x).all() and float((x - y).norm()) <= 1e-5 * float(y.norm()) + 1e-30, (t, shape)
     assert float((a[4] - b[4]).norm()) <= 1e-6 * float(b[4].norm())
+
+
+@pytest.mark.parametrize("rank,workers", [(2, 3), (8, 9)])
+def test_without_room_for_the_one_launch_orthogonalisation_each_worker_is_multiplied_by_itself(rank, workers):
+    """2200 panels of one row block each: more than the device holds at once, so gram_fused does not hold and the mean is not
+    taken.  The plan then runs exactly what it runs with the mean switched off (rows of 65 vectors: one chunk of two
+    vectors per lane, two chunks of one)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1905_13727_amd import binding as B
+    dev = torch.device("cuda:0")
+    stream = torch.cuda.current_stream(dev).cuda_stream
+    outs = []
+    for mean in (1, 0):
+        plan = B.Plan([(9, 260)] * 2200, rank, workers)
+        plan.set_tuning("worker_mean", mean)
+        s = plan.sizes
+        gen = torch.Generator(device=dev)
+        gen.manual_seed(3)
+        grad = torch.randn(workers * s.grad_stride, generator=gen, device=dev)
+        err = torch.randn(workers * s.err_stride, generator=gen, device=dev)
+        q = torch.randn(s.q_elems, generator=gen, device=dev)
+        p, out = torch.zeros(s.p_elems, device=dev), torch.zeros(s.out_elems, device=dev)
+        ws = torch.full((s.workspace_bytes // 4 + 64,), float("nan"), device=dev)
+        plan.step(grad, err, q, p, out, ws, stream)
+        plan.check(stream)
+        assert torch.isfinite(out).all()
+        outs.append((q, p, out, err))
+        plan.destroy()
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)

@@ -60,3 +60,24 @@ def test_static_workspace_step_equals_psgd_step():
     assert lib.psgd_step_static(big._h, None, 1, 1, 1, 1, None) == B.PSGD_EINVAL
     for plan in (big, small, huge):
         plan.destroy()
+
+
+@pytest.mark.parametrize("workers", [4, 8])
+def test_resnet18_at_the_highest_vector_rank_fits_the_static_workspace(workers):
+    """Eight workers at rank 8 need 27.5 of the 32 MiB, whichever way the products are taken."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1905_13727_amd import binding as B, workloads as WL
+    dev = torch.device("cuda:0")
+    stream = torch.cuda.current_stream(dev).cuda_stream
+    plan = B.Plan(WL.resnet18().shapes, 8, workers)
+    assert plan.sizes.workspace_bytes <= 32 << 20
+    plan.check(stream)
+    a, b = _state(plan, dev, 5), _state(plan, dev, 5)
+    ws = torch.full((plan.sizes.workspace_bytes // 4 + 64,), float("nan"), device=dev)
+    plan.step(a["grad"], a["err"], a["q"], a["p"], a["out"], ws, stream)
+    plan.step_static(b["grad"], b["err"], b["q"], b["p"], b["out"], stream)
+    plan.check(stream)
+    for key in ("err", "q", "p", "out"):
+        assert torch.equal(a[key], b[key]), key
+    assert torch.isfinite(b["out"]).all() and b["out"].abs().max() > 0
