@@ -288,13 +288,19 @@ __device__ __forceinline__ float sum_parts(const float* __restrict__ src, int np
 }
 
 // the same for the r <= R values of one panel row at once: the loads of all columns and of several slices are in
-// flight together; per column the slices are added in slice order, as in sum_parts (bit-identical to it)
-template <int R>
+// flight together; per column slice c is added to chain c mod CHAINS in slice order, then the chains to each other
+// (one chain: bit-identical to sum_parts)
+template <int CHAINS, int R>
 __device__ __forceinline__ void sum_parts_row(const float* __restrict__ src, int r, int nparts, int64_t stride,
                                               float (&row)[R]) {
     constexpr int U = R <= 2 ? 8 : (R <= 4 ? 4 : 2);
+    constexpr int C = CHAINS < U ? CHAINS : U;
+    static_assert(U % C == 0, "a slice's chain does not depend on the step");
+    float sum[C][R];
 #pragma unroll
-    for (int k = 0; k < R; ++k) row[k] = 0.f;
+    for (int h = 0; h < C; ++h)
+#pragma unroll
+        for (int k = 0; k < R; ++k) sum[h][k] = 0.f;
     int c = 0;
     for (; c + U <= nparts; c += U) {
         float v[U][R];
@@ -305,12 +311,32 @@ __device__ __forceinline__ void sum_parts_row(const float* __restrict__ src, int
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int k = 0; k < R; ++k) row[k] += v[u][k];
+            for (int k = 0; k < R; ++k) sum[u % C][k] += v[u][k];
     }
-    for (; c < nparts; ++c)
+    if constexpr (C == 1) {
+        for (; c < nparts; ++c)
 #pragma unroll
-        for (int k = 0; k < R; ++k)
-            if (k < r) row[k] += src[(int64_t)c * stride + k];
+            for (int k = 0; k < R; ++k)
+                if (k < r) sum[0][k] += src[(int64_t)c * stride + k];
+    } else if (c < nparts) {   // the last U - 1 slices at most
+        float v[U][R];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int k = 0; k < R; ++k) v[u][k] = k < r && c + u < nparts ? src[(int64_t)(c + u) * stride + k] : 0.f;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int k = 0; k < R; ++k) sum[u % C][k] += v[u][k];
+    }
+#pragma unroll
+    for (int w = C / 2; w > 0; w /= 2)
+#pragma unroll
+        for (int h = 0; h < w; ++h)
+#pragma unroll
+            for (int k = 0; k < R; ++k) sum[h][k] += sum[h + w][k];
+#pragma unroll
+    for (int k = 0; k < R; ++k) row[k] = sum[0][k];
 }
 
 __global__ __launch_bounds__(kOrthoBlock) void k_ortho(const MatDesc* __restrict__ mats, const int32_t* __restrict__ which,
@@ -427,7 +453,7 @@ __global__ __launch_bounds__(kBlock) void k_gram(const MatDesc* __restrict__ mat
         for (int b = 0; b < kValuMaxRank; ++b) g[a][b] = 0.0;
     for (int i = t.row0 + tid; i < t.row0 + t.nrows; i += kBlock) {
         float row[kValuMaxRank];
-        sum_parts_row<kValuMaxRank>(ws + d.ppart_off + (int64_t)i * r, r, nparts, nr, row);
+        sum_parts_row<1>(ws + d.ppart_off + (int64_t)i * r, r, nparts, nr, row);
 #pragma unroll
         for (int k = 0; k < kValuMaxRank; ++k) {
             row[k] *= inv_w;
@@ -564,11 +590,15 @@ __global__ __launch_bounds__(kBlock) void k_chol_apply(const MatDesc* __restrict
 // of its matrix, factorises the sum and solves for its own rows of P_hat, which never left the registers.  This
 // saves a launch, a drain and refill of the machine, and the second reading of P.  The workgroups of a matrix wait
 // for each other, so they must be co-resident (checked when the tables are uploaded); every wait is bounded.
+// `mean`: the partial P are of one product, that of the mean over the workers, whose roundings don't average out over the
+// workers as those of their own products do; its column chunks are therefore added in four chains (two above rank 4).  P against 64 bits,
+// ResNet18-shaped set, each worker by itself / one chain / four: 4 workers, rank 2 5.8e-8 / 6.2e-8 / 5.6e-8; 16 workers, rank 4
+// 7.1e-8 / 7.0e-8 / 6.4e-8, and 673.8 / 672.6 us a step with one chain and four.  Sums in 64 bits were closer still and 3 us slower.
 template <int R>
 __global__ __launch_bounds__(kBlock) void k_gram_chol(const MatDesc* __restrict__ mats, const Tile* __restrict__ tiles,
                                                       const float* __restrict__ ws, float* __restrict__ p,
                                                       slot_t* __restrict__ mail_gram, unsigned* __restrict__ sync,
-                                                      int workers, int pre_reduced, unsigned spin_limit) {
+                                                      int workers, int pre_reduced, int mean, unsigned spin_limit) {
     constexpr int kMaxSlices = 16;
     constexpr int kAhead = 4;   // slots requested before the first is looked at
     constexpr int E = kValuMaxRank * kValuMaxRank;
@@ -595,7 +625,8 @@ __global__ __launch_bounds__(kBlock) void k_gram_chol(const MatDesc* __restrict_
 #pragma unroll
     for (int k = 0; k < R; ++k) row[k] = 0.f;
     if (have) {
-        sum_parts_row<R>(ws + d.ppart_off + (int64_t)i * r, r, nparts, nr, row);
+        if (mean) sum_parts_row<4>(ws + d.ppart_off + (int64_t)i * r, r, nparts, nr, row);
+        else sum_parts_row<1>(ws + d.ppart_off + (int64_t)i * r, r, nparts, nr, row);
 #pragma unroll
         for (int k = 0; k < R; ++k) row[k] *= inv_w;
     }
@@ -1471,7 +1502,7 @@ psgd_status launch_compress(psgd_plan* plan, const void* grad, float* err, float
         slot_t* gmail = reinterpret_cast<slot_t*>(plan->dev.gram_mail);
 #define PSGD_LAUNCH_GRAM_CHOL(RR)                                                                                     \
     hipLaunchKernelGGL((k_gram_chol<RR>), ggrid, dim3(kBlock), 0, s, mats, plan->dev.tiles_gram, ws, p, gmail, \
-                       plan->dev.gram_sync, workers, pre_reduced, (unsigned)plan->tuning.gram_spin)
+                       plan->dev.gram_sync, workers, pre_reduced, mean ? 1 : 0, (unsigned)plan->tuning.gram_spin)
         switch (plan->rank) {
             case 1: PSGD_LAUNCH_GRAM_CHOL(1); break;
             case 2: PSGD_LAUNCH_GRAM_CHOL(2); break;
