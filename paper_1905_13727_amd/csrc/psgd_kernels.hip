@@ -211,7 +211,7 @@ __device__ __forceinline__ void ef_right_mean_tile(const Tile& t, const MatDesc&
 #pragma unroll
             for (int i = 0; i < RS; ++i) buf_ldv<V>(er, coff + (el0 + (unsigned)i * (unsigned)d.m) * 4u, ev[i], STREAM);
         };
-        float sum[RS][V], odd[RS][V];   // over the even and the odd workers
+        float sum[RS][V], odd[RS][V];   // over the even and the odd workers, of M_w / W: the mean of finite values is finite
 #pragma unroll
         for (int i = 0; i < RS; ++i)
 #pragma unroll
@@ -226,7 +226,7 @@ __device__ __forceinline__ void ef_right_mean_tile(const Tile& t, const MatDesc&
                     buf_stv<V>(er, coff + (el0 + (unsigned)i * (unsigned)d.m) * 4u, ev[i], STREAM);
                 }
 #pragma unroll
-                for (int x = 0; x < V; ++x) to[i][x] += ev[i][x];
+                for (int x = 0; x < V; ++x) to[i][x] = fmaf(ev[i][x], inv_w, to[i][x]);
             }
         };
         float ga[RS][V], ea[RS][V], gb[RS][V], eb[RS][V];
@@ -242,7 +242,7 @@ __device__ __forceinline__ void ef_right_mean_tile(const Tile& t, const MatDesc&
 #pragma unroll
         for (int i = 0; i < RS; ++i) {
 #pragma unroll
-            for (int x = 0; x < V; ++x) sum[i][x] = (sum[i][x] + odd[i][x]) * inv_w;
+            for (int x = 0; x < V; ++x) sum[i][x] += odd[i][x];
             buf_stv<V>(mres, coff + (el0 + (unsigned)i * (unsigned)d.m) * 4u, sum[i]);
 #pragma unroll
             for (int k = 0; k < R; ++k) {

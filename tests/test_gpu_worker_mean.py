@@ -149,3 +149,32 @@ def test_p_is_no_further_from_64_bits_than_with_each_worker_by_itself(shape, ran
     # two sets of at least 512 rounding errors: their 2-norms scatter by 1 / sqrt(2 * 512) = 3 % each
     assert dist[0] <= 1.05 * dist[1], dist
     assert dist[1] < 2e-7 * rank ** 0.5, dist
+
+
+@pytest.mark.parametrize("size,workers", [(64, 4), (66, 5), (65, 13)])
+def test_large_values_do_not_overflow_in_the_mean(size, workers):
+    """Every M_w is 2e38 times the identity: the sum over the workers is beyond fp32's 3.4e38, the mean and all that follows are
+    not (P = 2e38 q, Q = 2e38 / sqrt(n), which also the sum of the workers' own Q stays below while W <= 1.7 sqrt(n))."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1905_13727_amd import binding as B
+    dev = torch.device("cuda:0")
+    stream = torch.cuda.current_stream(dev).cuda_stream
+    assert workers <= 3.4 / 2 * size ** 0.5
+    outs = []
+    for mean in (1, 0):
+        plan = B.Plan([(size, size)], 1, workers)
+        plan.set_tuning("worker_mean", mean)
+        s = plan.sizes
+        grad = torch.zeros(workers, s.grad_stride, device=dev)
+        grad[:, : size * size] = 2e38 * torch.eye(size, device=dev).reshape(-1)
+        err = torch.zeros(workers * s.err_stride, device=dev)
+        q, p = torch.full((s.q_elems,), 1e-3, device=dev), torch.zeros(s.p_elems, device=dev)
+        out = torch.zeros(s.out_elems, device=dev)
+        ws = torch.full((s.workspace_bytes // 4 + 64,), float("nan"), device=dev)
+        plan.step(grad, err, q, p, out, ws, stream)
+        plan.check(stream)
+        outs.append((q, p, out, err))
+    for a, b in zip(*outs):
+        assert torch.isfinite(a).all() and torch.isfinite(b).all()
+        assert float((a.double() - b.double()).norm()) <= 1e-6 * float(b.double().norm())
