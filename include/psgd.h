@@ -142,8 +142,9 @@ PSGD_API psgd_status psgd_plan_offsets(const psgd_plan* plan, int32_t tensor, in
  *                 of at least k tiles, -1 (default) the planner's choice: groups of 4096 / workers
  *                 tiles (128 .. 2048); the whole list for one worker and a set beyond the cache
  *   stream_hints  cache policy of the second and third sweep: -1 (default) by the size of M over all
- *                 workers (non-temporal accesses to M and the error memory above 320 MB), 0 never,
- *                 1 always
+ *                 workers (non-temporal accesses to M and the error memory above 320 MB; below it, one worker,
+ *                 to the momentum and parameters of the fused update where the three together exceed 320 MB),
+ *                 0 never, 1 always (M and the error memory)
  *   gram_fused    orthogonalisation over row blocks: 1 (default) Gram matrices and factorisation in one launch where the
  *                 device holds all row blocks of the launch at once, 0 in two launches, 2 (TEST ONLY) in one
  *                 launch unconditionally: its waits may then time out, see psgd_plan_check

@@ -373,6 +373,18 @@ static void check_moved_to_matrix_cores() {
     }
 }
 
+// stream_hints = 0 asks for no cache policy, also not for the momentum and parameters of the fused update.
+static void check_update_around() {
+    const psgd_shape s = {7168, 4096};
+    psgd_plan* plan = nullptr;
+    CHECK(psgd_plan_create(&s, 1, 2, 1, PSGD_F32, PSGD_F32, &plan) == PSGD_OK);
+    for (int64_t hints : {-1, 0, 1, -1}) {
+        CHECK(psgd_plan_set_tuning(plan, "stream_hints", hints) == PSGD_OK);
+        CHECK(plan->update_around == (hints < 0) && plan->tiles4u.empty() == (hints < 0));
+    }
+    psgd_plan_destroy(plan);
+}
+
 // The mean over the workers first: the workspace and the work-lists of the other route, which runs where the mean cannot be
 // had, are those of a plan that never takes the mean.
 static void check_worker_mean() {
@@ -432,6 +444,7 @@ static void check_worker_mean() {
 
 int main() {
     check_moved_to_matrix_cores();
+    check_update_around();
     check_worker_mean();
     std::vector<std::vector<psgd_shape>> sets = {
         {{64, 27}, {64, 576}, {64, 576}},
