@@ -927,10 +927,11 @@ __global__ __launch_bounds__(kBlock) void k_q_reduce(const MatDesc* __restrict__
 
 // STREAM (see left_tile): M is read with non-temporal loads and the new error memory written with non-temporal stores;
 // otherwise it is Delta' that is written with non-temporal stores
-// OBF: Delta' is stored as bf16; with UPD, where Delta' is not stored: momentum and parameters are read and written with
-// non-temporal accesses.  They are touched once a step, and on a set whose M fits the memory-side cache while M, momentum and
-// parameters together do not, they would push M and the error memory out (rule and figures: the planner, update_around).
-template <int R, int V, int NV, bool UPD, bool STREAM, bool OBF>
+// OBF: Delta' is stored as bf16
+// AROUND (with UPD): momentum and parameters are read and written with non-temporal accesses.  They are touched once a step, and
+// on a set whose M fits the memory-side cache while M, momentum and parameters together do not, they would push M and the
+// error memory out (rule and figures: the planner, update_around).
+template <int R, int V, int NV, bool UPD, bool STREAM, bool OBF, bool AROUND>
 __device__ __forceinline__ void decomp_tile(const Tile& t, const MatDesc& d, float* __restrict__ e,
                                             const float* __restrict__ p, const float* __restrict__ q,
                                             void* __restrict__ out, bool write_out, const UpdateArgs& upd) {
@@ -970,7 +971,7 @@ __device__ __forceinline__ void decomp_tile(const Tile& t, const MatDesc& d, flo
                             else ldv<V>(e + row + col[v], x[u][v]);
                             if constexpr (UPD) {
                                 if (write_out) {
-                                    if constexpr (OBF) {
+                                    if constexpr (AROUND) {
                                         ldv_stream<V>(upd.mom + row + col[v], mo[u][v]);
                                         ldv_stream<V>(upd.param + row + col[v], pa[u][v]);
                                     } else {
@@ -1006,7 +1007,7 @@ __device__ __forceinline__ void decomp_tile(const Tile& t, const MatDesc& d, flo
                             if (write_out) {
                                 if constexpr (UPD) {
                                     momentum_step<V>(mo[u][v], pa[u][v], dl, upd.lr, upd.lam);
-                                    if constexpr (OBF) {
+                                    if constexpr (AROUND) {
                                         stv_stream<V>(upd.mom + row + col[v], mo[u][v]);
                                         stv_stream<V>(upd.param + row + col[v], pa[u][v]);
                                     } else {
@@ -1027,7 +1028,7 @@ __device__ __forceinline__ void decomp_tile(const Tile& t, const MatDesc& d, flo
 
 // The slices of the vector region are handled here when gradients and output are fp32 (`grad`, `outv` typed
 // accordingly); with bf16 data a kernel of its own does them and vec_here is 0.
-template <int R, int NV, bool UPD, bool STREAM, bool OBF>
+template <int R, int NV, bool UPD, bool STREAM, bool OBF, bool AROUND>
 __global__ __launch_bounds__(kBlock) void k_decomp(const MatDesc* __restrict__ mats, const Tile* __restrict__ tiles,
                                                    float* __restrict__ err, const float* __restrict__ p,
                                                    const float* __restrict__ q, const float* __restrict__ grad,
@@ -1056,9 +1057,9 @@ __global__ __launch_bounds__(kBlock) void k_decomp(const MatDesc* __restrict__ m
     }
     const MatDesc d = mats[t.mat];
     float* e = err + (int64_t)w * estride;
-    if (d.vec == 4) decomp_tile<R, 4, NV, UPD, STREAM, OBF>(t, d, e, p, q, outv, w == 0, upd);
-    else if (d.vec == 2) decomp_tile<R, 2, NV, UPD, STREAM, OBF>(t, d, e, p, q, outv, w == 0, upd);
-    else decomp_tile<R, 1, NV, UPD, STREAM, OBF>(t, d, e, p, q, outv, w == 0, upd);
+    if (d.vec == 4) decomp_tile<R, 4, NV, UPD, STREAM, OBF, AROUND>(t, d, e, p, q, outv, w == 0, upd);
+    else if (d.vec == 2) decomp_tile<R, 2, NV, UPD, STREAM, OBF, AROUND>(t, d, e, p, q, outv, w == 0, upd);
+    else decomp_tile<R, 1, NV, UPD, STREAM, OBF, AROUND>(t, d, e, p, q, outv, w == 0, upd);
 }
 
 // ---- host side ------------------------------------------------------------------------------------
@@ -1413,25 +1414,25 @@ static void launch_decomp(psgd_plan* plan, float* err, const float* p, const flo
     dim3 grid((unsigned)(own_tiles ? plan->tiles4u.size() : plan->tiles4.size()), (unsigned)plan->workers);
     // bf16 gradients or output: the vector region has a kernel of its own
     const int vec_here = plan->grad_dtype == PSGD_F32 && plan->out_dtype == PSGD_F32 ? 1 : 0;
-#define PSGD_LAUNCH_DECOMP(NVV, UPDV, STREAMV, OBFV)                                                                    \
-    hipLaunchKernelGGL((k_decomp<R, NVV, UPDV, STREAMV, OBFV>), grid, dim3(kBlock), 0, s, plan->dev.mats,               \
+#define PSGD_LAUNCH_DECOMP(NVV, UPDV, STREAMV, OBFV, AROUNDV)                                                            \
+    hipLaunchKernelGGL((k_decomp<R, NVV, UPDV, STREAMV, OBFV, AROUNDV>), grid, dim3(kBlock), 0, s, plan->dev.mats,      \
                        tiles, err, p, q, static_cast<const float*>(grad), out, plan->workers,                           \
                        plan->sizes.grad_stride, plan->sizes.err_stride, plan->sizes.n_mat_elems, upd, vec_here)
-#define PSGD_LAUNCH_DECOMP_NV(UPDV, STREAMV, OBFV)                               \
-    do {                                                                         \
-        if (plan->tuning.k4_nv == 1) PSGD_LAUNCH_DECOMP(1, UPDV, STREAMV, OBFV); \
-        else PSGD_LAUNCH_DECOMP(2, UPDV, STREAMV, OBFV);                         \
+#define PSGD_LAUNCH_DECOMP_NV(UPDV, STREAMV)                                            \
+    do {                                                                                \
+        if (plan->tuning.k4_nv == 1) PSGD_LAUNCH_DECOMP(1, UPDV, STREAMV, false, false); \
+        else PSGD_LAUNCH_DECOMP(2, UPDV, STREAMV, false, false);                        \
     } while (0)
     if (upd.mom) {   // Delta' is not stored
-        if (plan->stream_hints) PSGD_LAUNCH_DECOMP_NV(true, true, false);
-        else if (plan->update_around) PSGD_LAUNCH_DECOMP_NV(true, false, true);
-        else PSGD_LAUNCH_DECOMP_NV(true, false, false);
+        if (plan->stream_hints) PSGD_LAUNCH_DECOMP_NV(true, true);
+        else if (plan->update_around) PSGD_LAUNCH_DECOMP(1, true, false, false, true);   // one column vector per lane (planner)
+        else PSGD_LAUNCH_DECOMP_NV(true, false);
     } else if (plan->out_dtype == PSGD_BF16) {   // one column vector per lane (planner)
-        if (plan->stream_hints) PSGD_LAUNCH_DECOMP(1, false, true, true);
-        else PSGD_LAUNCH_DECOMP(1, false, false, true);
+        if (plan->stream_hints) PSGD_LAUNCH_DECOMP(1, false, true, true, false);
+        else PSGD_LAUNCH_DECOMP(1, false, false, true, false);
     } else {
-        if (plan->stream_hints) PSGD_LAUNCH_DECOMP_NV(false, true, false);
-        else PSGD_LAUNCH_DECOMP_NV(false, false, false);
+        if (plan->stream_hints) PSGD_LAUNCH_DECOMP_NV(false, true);
+        else PSGD_LAUNCH_DECOMP_NV(false, false);
     }
 #undef PSGD_LAUNCH_DECOMP_NV
 #undef PSGD_LAUNCH_DECOMP

@@ -299,7 +299,7 @@ psgd_status build_tables(psgd_plan* plan) {
     // 254 / 246; rows of 800, 39 M elements 326 / 286; with inputs that change from step to step the first is 259 / 242.
     // Below the line ordinary accesses and 64 rows stay (21 M elements: 209 against 217).
     plan->update_around = plan->workers == 1 && 3 * plan->sizes.n_mat_elems * (int64_t)sizeof(float) > kStreamHintBytes &&
-                          plan->sizes.n_mat_elems * (int64_t)sizeof(float) <= kStreamHintBytes && tu.stream_hints < 0;
+                          plan->sizes.n_mat_elems * (int64_t)sizeof(float) <= kStreamHintBytes && tu.stream_hints < 0 && tu.k4_nv == 1;
     plan->tiles4u.clear();
     if (tu.k4_rows == 0 && !plan->update_around && plan->workers == 1 && !small_set(plan) &&
         plan->sizes.n_mat_elems * (int64_t)sizeof(float) <= kStreamHintBytes)
