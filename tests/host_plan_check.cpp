@@ -426,6 +426,7 @@ static void check_worker_mean() {
                         CHECK(m.ppart_off == a.ppart_off && m.qpart_off == a.qpart_off && m.n_rblock == a.n_rblock && m.off == a.off);
                         CHECK(m.n_cchunk <= W * a.n_cchunk);   // the slices of the mean's products lie within the workers' own
                     }
+                    for (const Tile& t : mean->tiles1m) CHECK(t.nrows <= 64 / mean->mats[t.mat].vec);   // small sets too: one launch over all workers
                     if (rank == 1 && W == 4 && !nv) {
                         std::swap(mean->mats, mean->mats_mean);   // the launches over the mean see these descriptors
                         check_cover(mean, mean->tiles1m, 1, 1);
