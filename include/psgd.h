@@ -150,8 +150,8 @@ PSGD_API psgd_status psgd_plan_offsets(const psgd_plan* plan, int32_t tensor, in
  *                 launch unconditionally: its waits may then time out, see psgd_plan_check
  *   gram_spin     polls before a wait in that launch gives up, 1 .. 2^24 (default 2^18)
  *   worker_mean   streaming kernels, where gram_fused holds: products of the mean over the workers' M instead of each
- *                 worker's own; -1 (default) from four workers and 2^20 elements on when the rows of 15 in 16 elements are multiples
- *                 of 4, 0 never, 1 with any two workers
+ *                 worker's own; -1 (default) from four workers and 2^20 elements on (2^16 per worker above sixteen workers) when
+ *                 the rows of 15 in 16 elements are multiples of 4, 0 never, 1 with any two workers
  *   ortho_rows    panels of at most this many rows (0 .. 1024) are orthogonalised by one workgroup with modified
  *                 Gram-Schmidt in LDS instead of Cholesky-QR over row blocks; default 0: none
  *   bf16_valu     bf16 gradients / output at rank <= 8: 1 streaming kernels, 0 matrix-core kernels, -1 (default) the

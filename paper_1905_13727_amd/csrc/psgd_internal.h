@@ -23,14 +23,18 @@ constexpr int kPanelFloats = 12288;  // n*r up to this: Gram-Schmidt by one work
 constexpr int kGramRows = 256;     // rows per workgroup of the Gram / apply kernels (Cholesky-QR over row blocks)
 constexpr int kPreReduceParts = 16; // more partial-P slices than this: a reduction kernel runs before the orthogonalisation
 constexpr int kOrthoMaxRows = 1024; // largest value of the tuning key ortho_rows: panels with more rows always take the multi-workgroup route
-// Streaming kernels: from this many workers on, on sets of at least kMeanElems elements whose rows are all multiples of 4, the
-// products are taken of the mean over the workers.  Whole steps, us, each worker by itself / the mean first: ResNet18-shaped set, 16
-// workers 733 / 673, 4 workers 179 / 165, 1.1 M elements and 8 workers 75 / 70.  The other side of the line: two workers save no
-// bytes (24 M elements 318 / 330); three gain without the update (144 / 134) and lose with it (164 / 175); narrower accesses lose at
-// 20 M elements in odd rows (3 workers, 260 / 304) and in the LSTM-shaped set's rows of 650 (4 workers, 720 / 761); on small sets
-// the serial walk over the workers is too long (five matrices: 4 workers 24.4 / 26.7, 16 workers 24.3 / 37.1).
+// Streaming kernels: from this many workers on, on sets of at least kMeanElems elements (kMeanElemsPerWorker for every worker above
+// sixteen workers) with 15 in 16 of them in rows that are multiples of 4, the products are taken of the mean over the workers.
+// Whole steps, us, each worker by itself / the mean first: ResNet18-shaped set, rank 4, 16 workers 730 / 670, 8 workers 372 / 348, 4
+// workers 215 / 205; 24 matrices of 9 M elements, 5 workers 205 / 191; two transformer layers (42 M elements), 4 workers 729 / 657, bf16
+// gradients, rank 2 643 / 590; 1.1 M elements (ResNet18-shaped), 8 workers 76.6 / 68.0, 4 workers 44.2 / 44.2, 16 workers 153.7 / 153.5.
+// The other side of the line: two workers save no bytes (24 M elements 318 / 330); three gain without the update (144 / 134) and
+// lose with it (164 / 175); narrower accesses lose at 20 M elements in odd rows (3 workers, 260 / 304) and in the LSTM-shaped set's
+// rows of 650 (4 workers, 720 / 761); on small sets the serial walk over the workers is too long (five matrices: 4 workers 24.4 / 26.7, 16
+// workers 24.3 / 37.1; 32 workers: 1.1 M elements 287 / 293 and 149 / 158, 2.0 M 255 / 278, but 2.1 M 471 / 457, 2.8 M 487 / 416).
 constexpr int kMeanWorkers = 4;
 constexpr int64_t kMeanElems = int64_t(1) << 20;
+constexpr int64_t kMeanElemsPerWorker = int64_t(1) << 16;
 constexpr int kFlatTileElems = 1024;        // baselines: elements of a flattened matrix per workgroup of the elementwise sweep (one 16-byte access per
                                             // lane and array: the smallest slices were the fastest, 8192 -> 1024: 34.7 -> 28.7 us on the ResNet18 set)
 constexpr int kFactorAlignElems = 4;        // P and Q of a matrix start at multiples of 4 floats (vector loads of factor rows)

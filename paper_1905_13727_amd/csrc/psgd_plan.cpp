@@ -277,7 +277,8 @@ psgd_status build_tables(psgd_plan* plan) {
             (int64_t(1) << 31))
             return PSGD_EUNSUPPORTED;
     std::vector<int32_t> nrb(nm, 0), ncc(nm, 0);
-    plan->mean_first = plan->workers >= kMeanWorkers && plan->sizes.n_mat_elems >= kMeanElems;
+    plan->mean_first = plan->workers >= kMeanWorkers &&
+                       plan->sizes.n_mat_elems >= std::max<int64_t>(kMeanElems, plan->workers * kMeanElemsPerWorker);
     int64_t narrow = 0;   // elements in rows that are not multiples of 4: a small share (a first layer's rows of 27) does not count
     for (const MatDesc& d : plan->mats)
         if (d.vec != 4) narrow += (int64_t)d.n * d.m;

@@ -385,6 +385,27 @@ static void check_update_around() {
     psgd_plan_destroy(plan);
 }
 
+// Both sides of every line of the rule by which the products are taken of the mean over the workers.
+static void check_mean_rule() {
+    struct { std::vector<psgd_shape> shapes; int workers; bool mean; } cases[] = {
+        {{{1024, 1024}}, 3, false}, {{{1024, 1024}}, 4, true}, {{{1023, 1024}}, 4, false},
+        {{{1024, 1024}}, 16, true}, {{{1024, 1024}}, 17, false}, {{{1088, 1024}}, 17, true}, {{{1087, 1024}}, 17, false},
+        {{{2047, 1024}}, 32, false}, {{{2048, 1024}}, 32, true},
+        {{{1024, 1025}}, 4, false}, {{{1024, 1026}}, 4, false},
+        // a sixteenth of the elements at most in rows that are not multiples of 4
+        {{{1500, 1024}, {1600, 64}}, 4, true}, {{{1500, 1024}, {1600, 63}}, 4, true}, {{{1500, 1024}, {1650, 63}}, 4, false},
+    };
+    for (auto& c : cases)
+        for (psgd_dtype gd : {PSGD_F32, PSGD_BF16}) {
+            psgd_plan* plan = nullptr;
+            CHECK(psgd_plan_create(c.shapes.data(), (int)c.shapes.size(), 2, c.workers, gd, PSGD_F32, &plan) == PSGD_OK);
+            CHECK(plan->mean_first == c.mean);
+            CHECK(psgd_plan_set_tuning(plan, "worker_mean", 1) == PSGD_OK && plan->mean_first);
+            CHECK(psgd_plan_set_tuning(plan, "gram_fused", 0) == PSGD_OK && !plan->mean_first && plan->tiles1m.empty());
+            psgd_plan_destroy(plan);
+        }
+}
+
 // The mean over the workers first: the workspace and the work-lists of the other route, which runs where the mean cannot be
 // had, are those of a plan that never takes the mean.
 static void check_worker_mean() {
@@ -446,6 +467,7 @@ static void check_worker_mean() {
 int main() {
     check_moved_to_matrix_cores();
     check_update_around();
+    check_mean_rule();
     check_worker_mean();
     std::vector<std::vector<psgd_shape>> sets = {
         {{64, 27}, {64, 576}, {64, 576}},
