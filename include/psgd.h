@@ -18,9 +18,10 @@
  *                                                  starting Q of the next
  *
  * All data buffers are DEVICE pointers owned by the caller (allocate them with
- * any allocator; the tests use PyTorch).  The library owns only the plan and
- * its small device-side descriptor tables.  No entry point throws or aborts;
- * every failure is a psgd_status.
+ * any allocator; the tests use PyTorch).  The library owns only the plan, its
+ * small device-side descriptor tables and, for some plans of several workers,
+ * one buffer of N floats (psgd_plan_worker_mean says which).  No entry point
+ * throws or aborts; every failure is a psgd_status.
  *
  * Flat layout (all offsets in elements, reported by psgd_plan_sizes /
  * psgd_plan_offsets):
@@ -83,8 +84,9 @@ typedef struct {
     int64_t compressed_elems;/* sum r_i (n_i + m_i) + L: what PowerSGD exchanges (Appendix F tables) */
     int64_t bytes_min;       /* algorithmic HBM bytes per step if every M element moved once:
                                 read g, read e, write e' per worker, write Delta' once */
-    int64_t bytes_stream;    /* same with the two extra reads of M forced by the two global
-                                reductions (after P, after Q) */
+    int64_t bytes_stream;    /* same with the extra write and the two extra reads of M forced by the two
+                                global reductions (after P, after Q), each worker multiplied by itself; the
+                                products of the mean (psgd_plan_worker_mean) move 4 W - 8 bytes per element less */
     int64_t kept_elems;      /* Random Block / Random K baselines (Appendix G): sum over the matrices of
                                 min((n_i + m_i) * rank, n_i * m_i), the length of their packed value / index buffers */
 } psgd_sizes;
@@ -352,6 +354,15 @@ PSGD_API psgd_status psgd_plan_read_trace(psgd_plan* plan, uint64_t* out, int64_
 #define PSGD_PATH_RESIDENT 1
 #define PSGD_PATH_MATRIX_CORES 2
 PSGD_API psgd_status psgd_plan_path(const psgd_plan* plan, int32_t* path);
+
+/* Whether the products of this plan are taken of the mean over the workers' M (tuning key worker_mean; the values differ
+ * from those of each worker's own products by rounding only), and the device memory the plan holds for that mean, which no
+ * field of psgd_sizes counts.  *taken = 1 or 0; *bytes = 4 N or 0.  Before the plan's first GPU call both are the planner's
+ * choice: what that call will allocate, and use if the device holds the one-launch orthogonalisation.  After it they are what
+ * holds: 0 and 0 where the device does not hold it or the memory could not be had (the step is then as with worker_mean =
+ * 0), and 0 and 4 N after psgd_plan_check has switched the one-launch orthogonalisation off.  A plan that runs only the
+ * baselines of Appendix G holds the memory too; worker_mean = 0 avoids it.  Either output may be NULL; PSGD_EINVAL for a NULL plan. */
+PSGD_API psgd_status psgd_plan_worker_mean(const psgd_plan* plan, int32_t* taken, int64_t* bytes);
 
 /* Static, never NULL. */
 PSGD_API const char* psgd_status_string(psgd_status status);

@@ -75,6 +75,8 @@ def load_library(path: Optional[str] = None):
     lib.psgd_random_k_step.argtypes = [vp, vp, vp, vp, vp, vp, vp]
     lib.psgd_plan_path.restype = C.c_int
     lib.psgd_plan_path.argtypes = [vp, C.POINTER(i32)]
+    lib.psgd_plan_worker_mean.restype = C.c_int
+    lib.psgd_plan_worker_mean.argtypes = [vp, C.POINTER(i32), C.POINTER(i64)]
     lib.psgd_plan_kept.restype = C.c_int
     lib.psgd_plan_kept.argtypes = [vp, i32, C.POINTER(i64), C.POINTER(i64)]
     lib.psgd_step_static.restype = C.c_int
@@ -202,6 +204,12 @@ class Plan:
         r = C.c_int32()
         self._check(self._lib.psgd_plan_path(self._h, C.byref(r)), "psgd_plan_path")
         return ("streaming", "resident", "matrix cores")[r.value]
+
+    def worker_mean(self):
+        """(whether the products are taken of the mean over the workers, device bytes the plan holds for that mean)."""
+        taken, n = C.c_int32(), C.c_int64()
+        self._check(self._lib.psgd_plan_worker_mean(self._h, C.byref(taken), C.byref(n)), "psgd_plan_worker_mean")
+        return bool(taken.value), n.value
 
     def kept(self, tensor: int):
         off, n = C.c_int64(), C.c_int64()

@@ -726,6 +726,14 @@ psgd_status psgd_plan_path(const psgd_plan* plan, int32_t* path) {
     return PSGD_OK;
 }
 
+psgd_status psgd_plan_worker_mean(const psgd_plan* plan, int32_t* taken, int64_t* bytes) {
+    if (!plan) return PSGD_EINVAL;
+    const bool held = plan->uploaded ? plan->mbar != nullptr : plan->mean_first;
+    if (taken) *taken = held && (!plan->uploaded || plan->gram_fused) ? 1 : 0;
+    if (bytes) *bytes = held ? plan->sizes.n_mat_elems * (int64_t)sizeof(float) : 0;
+    return PSGD_OK;
+}
+
 psgd_status psgd_random_block_step(psgd_plan* plan, const void* grad, float* err, const int64_t* starts, float* vals,
                                    void* out, void* hip_stream) {
     if (!plan || !grad || !err || !starts || !vals || !out) return PSGD_EINVAL;

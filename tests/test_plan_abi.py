@@ -198,3 +198,19 @@ def test_worker_mean_out_of_range_is_refused_on_every_kernel_set(rank):
         assert ei.value.status == B.PSGD_EINVAL
     for good in (0, 1, -1):
         plan.set_tuning("worker_mean", good)
+
+
+def test_worker_mean_and_its_memory():
+    """psgd_plan_worker_mean before any GPU call: the planner's choice, and the memory it will ask for."""
+    resnet = WL.resnet18_shapes()
+    n = 4 * B.Plan(resnet, 2, 4).sizes.n_mat_elems
+    assert B.Plan(resnet, 2, 4).worker_mean() == (True, n) and B.Plan(resnet, 2, 16).worker_mean() == (True, n)
+    assert B.Plan(resnet, 2, 1).worker_mean() == (False, 0) and B.Plan(resnet, 2, 3).worker_mean() == (False, 0)
+    assert B.Plan([(2048, 2048)], 16, 4).worker_mean() == (False, 0)      # matrix-core kernels
+    for key, value in (("worker_mean", 0), ("gram_fused", 0)):
+        plan = B.Plan(resnet, 2, 4)
+        plan.set_tuning(key, value)
+        assert plan.worker_mean() == (False, 0)
+    lib = B.load_library()
+    assert lib.psgd_plan_worker_mean(None, None, None) == B.PSGD_EINVAL
+    assert lib.psgd_plan_worker_mean(plan._h, None, None) == B.PSGD_OK
