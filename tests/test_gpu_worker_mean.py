@@ -18,6 +18,29 @@ SHAPES = [(64, 576), (17, 1028), (33, 650), (2, 130), (65, 257), (1, 3), (130, 6
     (3, 3, False, "hints"), (2, 2, False, "step"),
 ])
 def test_mean_route_equals_general_route(rank, workers, grad_bf16, call):
+    _mean_route_equals_general_route(SHAPES, rank, workers, grad_bf16, call)
+
+
+@pytest.mark.parametrize("rank,workers,grad_bf16,call", [
+    (4, 9, True, "step"), (2, 16, False, "iterate"), (3, 12, False, "iterations"), (8, 9, True, "hints"),
+    (2, 11, True, "iterate"), (1, 10, False, "hints iterate"), (5, 16, True, "hints iterations"),
+])
+def test_mean_route_equals_general_route_above_eight_workers(rank, workers, grad_bf16, call):
+    _mean_route_equals_general_route(SHAPES, rank, workers, grad_bf16, call)
+
+
+# 33 column chunks at each access width: the partial P are reduced before the orthogonalisation; 32: they are not
+WIDE = [(40, 8448), (40, 4162), (40, 2081), (40, 8192)]
+
+
+@pytest.mark.parametrize("shapes,rank,workers,grad_bf16,call", [
+    (WIDE, 2, 4, False, "step"), (WIDE, 8, 5, True, "iterations"), (WIDE[3:], 4, 4, False, "split"), (WIDE[:1], 1, 16, False, "iterate"),
+])
+def test_mean_route_equals_general_route_on_long_rows(shapes, rank, workers, grad_bf16, call):
+    _mean_route_equals_general_route(shapes, rank, workers, grad_bf16, call)
+
+
+def _mean_route_equals_general_route(SHAPES, rank, workers, grad_bf16, call):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_1905_13727_amd import binding as B
@@ -29,7 +52,7 @@ def test_mean_route_equals_general_route(rank, workers, grad_bf16, call):
         plan.set_tuning("resident", 0)
         plan.set_tuning("gram_fused", fused)
         plan.set_tuning("worker_mean", fused)   # small sets and odd rows do not take it by themselves
-        if call == "hints":
+        if "hints" in call:
             plan.set_tuning("stream_hints", 1)
         s = plan.sizes
         gen = torch.Generator(device=dev)
@@ -46,16 +69,16 @@ def test_mean_route_equals_general_route(rank, workers, grad_bf16, call):
         p = torch.zeros(s.p_elems, device=dev)
         out = torch.zeros(s.out_elems, device=dev)
         ws = torch.full((s.workspace_bytes // 4 + 64,), float("nan"), device=dev)
-        if call == "iterations":
+        if "iterations" in call:
             plan.step_iterations(grad, err, q, p, out, ws, 3, stream)
         elif call == "update":
             param = torch.zeros(s.out_elems, device=dev)
             plan.step_update(grad, err, q, p, out, param, 0.1, 0.9, ws, stream)
-        elif call in ("split", "iterate"):
+        elif call == "split" or "iterate" in call:
             plan.compress(grad, err, q, p, ws, stream)
             M = grad.view(workers, -1)[:, : s.n_mat_elems].float() + err0.view(workers, -1)
             assert torch.equal(err.view(workers, -1)[:, live], M[:, live])   # M_w itself is left for the next call
-            if call == "iterate":   # on whatever M the caller holds by then
+            if "iterate" in call:   # on whatever M the caller holds by then
                 scale = torch.linspace(0.5, 1.5, workers, device=dev).repeat_interleave(s.err_stride)
                 err, err0 = err * scale, err0 * scale
                 ws.fill_(float("nan"))
@@ -64,10 +87,11 @@ def test_mean_route_equals_general_route(rank, workers, grad_bf16, call):
         else:
             plan.step(grad, err, q, p, out, ws, stream)
         plan.check(stream)
+        assert plan.worker_mean() == (bool(fused), 4 * s.n_mat_elems if fused else 0)   # the route that is meant
         assert torch.equal(err.view(workers, -1)[:, ~live], err0.view(workers, -1)[:, ~live])   # gaps are not touched
         outs.append((plan, q, p, out, err.view(workers, -1)[:, live]))
     a, b = outs
-    # Per matrix: both are fp32 sums over at most 1028 terms in different orders, far below 1e-6 of the largest entry;
+    # Per matrix: both are fp32 sums over at most 8448 terms in different orders, far below 1e-6 of the largest entry;
     # the orthogonalisation multiplies by the panels' condition (random 1 x 3 ... 300 x 5 matrices at full rank: up to a few hundred).
     for t, shape in enumerate(SHAPES):
         off, p_off, q_off, r = a[0].offsets(t)
@@ -105,7 +129,7 @@ def test_without_room_for_the_one_launch_orthogonalisation_each_worker_is_multip
         ws = torch.full((s.workspace_bytes // 4 + 64,), float("nan"), device=dev)
         plan.step(grad, err, q, p, out, ws, stream)
         plan.check(stream)
-        assert torch.isfinite(out).all()
+        assert plan.worker_mean() == (False, 0) and torch.isfinite(out).all()
         outs.append((q, p, out, err))
         plan.destroy()
     for a, b in zip(*outs):
@@ -178,3 +202,27 @@ def test_large_values_do_not_overflow_in_the_mean(size, workers):
     for a, b in zip(*outs):
         assert torch.isfinite(a).all() and torch.isfinite(b).all()
         assert float((a.double() - b.double()).norm()) <= 1e-6 * float(b.double().norm())
+
+
+@pytest.mark.parametrize("workers,rank,grad_bf16", [(4, 2, False), (8, 8, False), (5, 3, True)])
+def test_default_rule_against_the_oracle(workers, rank, grad_bf16):
+    """A set that takes the mean by the planner's own rule, three steps with error feedback, to the parity bar (1e-5)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import numpy as np
+    from paper_1905_13727_amd import workloads as WL
+    from gpu_harness import GpuRun, OracleRun, compare
+    shapes = [(512, 1152), (64, 27), (128, 4608), (33,)]
+    wl = WL.Workload("mean", shapes, WL.tiny().planted_rank, WL.tiny().singular_values, WL.tiny().sigma)
+    factors, q0 = WL.planted_factors(wl, 0), WL.initial_q(wl, rank, 0)
+    gpu = GpuRun(shapes, rank, workers, q0, grad_bf16=grad_bf16)
+    ora = OracleRun(shapes, rank, workers, q0)
+    for t in range(3):
+        grads = [WL.gradients(wl, factors, 0, t, w) for w in range(workers)]
+        if grad_bf16:
+            grads = [[torch.from_numpy(np.asarray(g, dtype=np.float32)).bfloat16().float().numpy() for g in gw] for gw in grads]
+        prev = ora.errs
+        rg, ro = gpu.step(grads), ora.step(grads)
+        worst = compare(rg, ro, shapes, workers, rank, grads, prev)
+        assert max(worst.values()) <= 1e-5, (t, worst)
+    assert gpu.plan.worker_mean()[0]
