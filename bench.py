@@ -120,6 +120,29 @@ def device_gradients(wl, lay, plan, workers, seed, torch, dev, dtype=None):
     return grad
 
 
+def byte_models(s, W, gsz, osz, mean, fused_update=False, iterations=1):
+    """Algorithmic bytes per launch of each kernel (what the kernel itself has to move), and of a whole streaming step.
+    mean: the products are taken of the mean over the workers (psgd_plan_worker_mean)."""
+    payload_mat, L = s.payload_elems - s.n_vec_elems, s.n_vec_elems
+    m_bytes = payload_mat * 4 * (1 if mean else W)                          # what the products read after the first sweep
+    kernel_bytes = {
+        "k_ef_right": payload_mat * (W * (gsz + 8) + (4 if mean else 0)),   # read g, read e, write M (and the mean)
+        "k_left": m_bytes,                                                  # read M
+        "k_decomp": payload_mat * (W * 8 + osz) + L * (W * gsz + osz),      # read M, write e', write Delta' once
+        "k_resident": int(s.bytes_min),                           # read g, e; write e', Delta': each once
+        "k_ef_add_zero": int(s.bytes_min),                        # baselines: read g, e; write M; write Delta' = 0 once
+        "k_kept_entries": int(s.kept_elems) * (W * 8 + 8),        # read, write M at the kept entries; Delta', values
+    }
+    if fused_update:      # Delta' is not stored; momentum and parameters are read and written instead
+        extra = (payload_mat + L) * (16 - osz)
+        kernel_bytes["k_resident"] += extra
+        kernel_bytes["k_decomp"] += extra
+    if iterations > 1:    # the library's event pairs then hold the last round, whose P = M Q only reads M
+        kernel_bytes["k_ef_right"] = m_bytes
+    # bytes_stream: each worker multiplied by itself
+    return kernel_bytes, int(s.bytes_stream) - (payload_mat * (4 * W - 8) if mean else 0)
+
+
 def cpu_baseline(wl, rank, workers, budget_s, compressor="powersgd"):
     """The oracle as it stands, timed on the host cores on a bounded sample of the same workload."""
     from oracle import powersgd_oracle as O
@@ -383,22 +406,9 @@ def main():
 
     payload_mat = s.payload_elems - s.n_vec_elems
     L = s.n_vec_elems
-    # algorithmic bytes per launch of each kernel (fp32): what the kernel itself has to move
     gsz, osz = (2 if gdt == "bf16" else 4), (2 if odt == "bf16" else 4)
-    kernel_bytes = {
-        "k_ef_right": payload_mat * W * (gsz + 8),                          # read g, read e, write M
-        "k_left": payload_mat * W * 4,                                      # read M
-        "k_decomp": payload_mat * (W * 8 + osz) + L * (W * gsz + osz),      # read M, write e', write Delta' once
-        "k_resident": int(s.bytes_min),                           # read g, e; write e', Delta': each once
-        "k_ef_add_zero": int(s.bytes_min),                        # baselines: read g, e; write M; write Delta' = 0 once
-        "k_kept_entries": int(s.kept_elems) * (W * 8 + 8),        # read, write M at the kept entries; Delta', values
-    }
-    if args.update == "fused":   # Delta' is not stored; momentum and parameters are read and written instead
-        extra = (payload_mat + L) * (16 - osz)
-        kernel_bytes["k_resident"] += extra
-        kernel_bytes["k_decomp"] += extra
-    if args.iterations > 1:      # the library's event pairs then hold the last round, whose P = M Q only reads M
-        kernel_bytes["k_ef_right"] = payload_mat * W * 4
+    mean = plan.worker_mean()[0]
+    kernel_bytes, stream_bytes = byte_models(s, W, gsz, osz, mean, args.update == "fused", args.iterations)
     dom = max(kernel_bytes, key=lambda k: kavg.get(k, 0.0))
     achieved = kernel_bytes[dom] / (kavg[dom] * 1e-3) / 1e9 if kavg[dom] > 0 else 0.0
     grad_bytes = W * (payload_mat + L) * gsz
@@ -446,16 +456,16 @@ def main():
                    "iterations": args.iterations},
         # Byte models of the whole step over the timed (warm, back-to-back) steps.  min_model: every element of g, e
         # read once and of e', Delta' written once - what a resident step moves.  stream_model: the same plus the two
-        # re-reads of M that the method's two global reductions force on kernels that cannot keep M on chip - what a
-        # streaming or matrix-core step moves; a resident step does not move these bytes, so the model is not
-        # reported for it.
+        # re-reads of M (of its mean over the workers, where the products are taken of that) that the method's two
+        # global reductions force on kernels that cannot keep M on chip - what a streaming or matrix-core step moves; a
+        # resident step does not move these bytes, so the model is not reported for it.
         "min_model": {"bytes_per_step": int(s.bytes_min),
                       "GBps": round(s.bytes_min / (ms_per_step * 1e-3) / 1e9, 2),
                       "frac_of_hbm_peak": round(s.bytes_min / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)},
         "stream_model": None if (resident or sparse) else {
-            "bytes_per_step": int(s.bytes_stream),
-            "GBps": round(s.bytes_stream / (ms_per_step * 1e-3) / 1e9, 2),
-            "frac_of_hbm_peak": round(s.bytes_stream / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)},
+            "bytes_per_step": stream_bytes,
+            "GBps": round(stream_bytes / (ms_per_step * 1e-3) / 1e9, 2),
+            "frac_of_hbm_peak": round(stream_bytes / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)},
         # cold: caches flushed before every step, outside the timing - gradients and error memory come from HBM as
         # they would after a real backward pass.  The primary regime; `value` and `roofline.frac` are the timed
         # region's (warm), the cold fractions stand beside them.
@@ -465,7 +475,7 @@ def main():
             "value": round(grad_bytes / (cold_ms["median"] * 1e-3) / 1e9, 3), "unit": "GB/s",
             "min_model_frac_of_hbm_peak": round(s.bytes_min / (cold_ms["median"] * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
             "stream_model_frac_of_hbm_peak": None if (resident or sparse) else
-                round(s.bytes_stream / (cold_ms["median"] * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)},
+                round(stream_bytes / (cold_ms["median"] * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)},
         "event_ms_per_step": round(event_ms_per_step, 5),
         "kernel_ms": {k: round(v, 5) for k, v in kavg.items()},
         "kernel_ms_event_pairs": {k: round(v, 5) for k, v in kavg_events.items()},

@@ -214,3 +214,21 @@ def test_worker_mean_and_its_memory():
     lib = B.load_library()
     assert lib.psgd_plan_worker_mean(None, None, None) == B.PSGD_EINVAL
     assert lib.psgd_plan_worker_mean(plan._h, None, None) == B.PSGD_OK
+
+
+@pytest.mark.parametrize("workers,gsz", [(4, 4), (16, 4), (16, 2), (1, 4)])
+def test_bench_byte_models_follow_the_route(workers, gsz):
+    """The kernels' bytes add up to those of the step, for each worker by itself and for the mean over the workers."""
+    import sys
+    sys.path.insert(0, ROOT)
+    import bench
+    plan = B.Plan(WL.resnet18_shapes(), 4, workers, B.PSGD_BF16 if gsz == 2 else B.PSGD_F32, B.PSGD_F32)
+    s, n = plan.sizes, 11164352
+    vec = 9610 * (workers * gsz + 4)
+    for mean, per_element in ((False, workers * (gsz + 20) + 4), (True, workers * (gsz + 16) + 12)):
+        kernels, step = bench.byte_models(s, workers, gsz, 4, mean)
+        assert step == n * per_element + vec
+        assert sum(kernels[k] for k in ("k_ef_right", "k_left", "k_decomp")) == step
+        assert kernels["k_left"] == 4 * n * (1 if mean else workers)
+        again, _ = bench.byte_models(s, workers, gsz, 4, mean, iterations=2)
+        assert again["k_ef_right"] == 4 * n * (1 if mean else workers)
