@@ -39,9 +39,9 @@ MEASURED_TRAFFIC = {
     ("lstm", 4, 1, "k_ef_right"): 391825784,          # profiles/streaming_lstm_r4.md
     ("lstm", 4, 1, "k_left"): 132707849,
     ("lstm", 4, 1, "k_decomp"): 400357535,
-    ("resnet18", 2, 16, "k_ef_right"): 2169938454,    # profiles/streaming_resnet18_w16_r2.md
-    ("resnet18", 2, 16, "k_left"): 726187992,
-    ("resnet18", 2, 16, "k_decomp"): 1479685687,
+    ("resnet18", 2, 16, "k_ef_right"): 2190327983,    # profiles/streaming_resnet18_w16_r2.md
+    ("resnet18", 2, 16, "k_left"): 45550010,
+    ("resnet18", 2, 16, "k_decomp"): 1479782888,
     ("resnet18", 2, 1, "k_ef_add_zero"): 178776239,   # profiles/baseline_random_*_resnet18_r2.md
 }
 # The 24-layer transformer-shaped set: the counter runs end in a crash of the profiler once the process holds
