@@ -288,19 +288,13 @@ __device__ __forceinline__ float sum_parts(const float* __restrict__ src, int np
 }
 
 // the same for the r <= R values of one panel row at once: the loads of all columns and of several slices are in
-// flight together; per column slice c is added to chain c mod CHAINS in slice order, then the chains to each other
-// (one chain: bit-identical to sum_parts)
-template <int CHAINS, int R>
+// flight together; per column the slices are added in slice order, as in sum_parts (bit-identical to it)
+template <int R>
 __device__ __forceinline__ void sum_parts_row(const float* __restrict__ src, int r, int nparts, int64_t stride,
                                               float (&row)[R]) {
     constexpr int U = R <= 2 ? 8 : (R <= 4 ? 4 : 2);
-    constexpr int C = CHAINS < U ? CHAINS : U;
-    static_assert(U % C == 0, "a slice's chain does not depend on the step");
-    float sum[C][R];
 #pragma unroll
-    for (int h = 0; h < C; ++h)
-#pragma unroll
-        for (int k = 0; k < R; ++k) sum[h][k] = 0.f;
+    for (int k = 0; k < R; ++k) row[k] = 0.f;
     int c = 0;
     for (; c + U <= nparts; c += U) {
         float v[U][R];
@@ -311,14 +305,26 @@ __device__ __forceinline__ void sum_parts_row(const float* __restrict__ src, int
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int k = 0; k < R; ++k) sum[u % C][k] += v[u][k];
+            for (int k = 0; k < R; ++k) row[k] += v[u][k];
     }
-    if constexpr (C == 1) {
-        for (; c < nparts; ++c)
+    for (; c < nparts; ++c)
 #pragma unroll
-            for (int k = 0; k < R; ++k)
-                if (k < r) sum[0][k] += src[(int64_t)c * stride + k];
-    } else if (c < nparts) {   // the last U - 1 slices at most
+        for (int k = 0; k < R; ++k)
+            if (k < r) row[k] += src[(int64_t)c * stride + k];
+}
+
+// the same in several chains per column: slice c is added to chain c mod C in slice order, then the chains to each other
+template <int R>
+__device__ __forceinline__ void sum_parts_row_chains(const float* __restrict__ src, int r, int nparts, int64_t stride,
+                                                     float (&row)[R]) {
+    constexpr int U = R <= 2 ? 8 : (R <= 4 ? 4 : 2);
+    constexpr int C = U < 4 ? U : 4;
+    float sum[C][R];
+#pragma unroll
+    for (int h = 0; h < C; ++h)
+#pragma unroll
+        for (int k = 0; k < R; ++k) sum[h][k] = 0.f;
+    for (int c = 0; c < nparts; c += U) {   // slices past the last are zeros
         float v[U][R];
 #pragma unroll
         for (int u = 0; u < U; ++u)
@@ -453,7 +459,7 @@ __global__ __launch_bounds__(kBlock) void k_gram(const MatDesc* __restrict__ mat
         for (int b = 0; b < kValuMaxRank; ++b) g[a][b] = 0.0;
     for (int i = t.row0 + tid; i < t.row0 + t.nrows; i += kBlock) {
         float row[kValuMaxRank];
-        sum_parts_row<1>(ws + d.ppart_off + (int64_t)i * r, r, nparts, nr, row);
+        sum_parts_row<kValuMaxRank>(ws + d.ppart_off + (int64_t)i * r, r, nparts, nr, row);
 #pragma unroll
         for (int k = 0; k < kValuMaxRank; ++k) {
             row[k] *= inv_w;
@@ -590,15 +596,15 @@ __global__ __launch_bounds__(kBlock) void k_chol_apply(const MatDesc* __restrict
 // of its matrix, factorises the sum and solves for its own rows of P_hat, which never left the registers.  This
 // saves a launch, a drain and refill of the machine, and the second reading of P.  The workgroups of a matrix wait
 // for each other, so they must be co-resident (checked when the tables are uploaded); every wait is bounded.
-// `mean`: the partial P are of one product, that of the mean over the workers, whose roundings don't average out over the
+// MEAN: the partial P are of one product, that of the mean over the workers, whose roundings don't average out over the
 // workers as those of their own products do; its column chunks are therefore added in four chains (two above rank 4).  P against 64 bits,
 // ResNet18-shaped set, each worker by itself / one chain / four: 4 workers, rank 2 5.8e-8 / 6.2e-8 / 5.6e-8; 16 workers, rank 4
 // 7.1e-8 / 7.0e-8 / 6.4e-8, and 673.8 / 672.6 us a step with one chain and four.  Sums in 64 bits were closer still and 3 us slower.
-template <int R>
+template <int R, bool MEAN>
 __global__ __launch_bounds__(kBlock) void k_gram_chol(const MatDesc* __restrict__ mats, const Tile* __restrict__ tiles,
                                                       const float* __restrict__ ws, float* __restrict__ p,
                                                       slot_t* __restrict__ mail_gram, unsigned* __restrict__ sync,
-                                                      int workers, int pre_reduced, int mean, unsigned spin_limit) {
+                                                      int workers, int pre_reduced, unsigned spin_limit) {
     constexpr int kMaxSlices = 16;
     constexpr int kAhead = 4;   // slots requested before the first is looked at
     constexpr int E = kValuMaxRank * kValuMaxRank;
@@ -625,8 +631,8 @@ __global__ __launch_bounds__(kBlock) void k_gram_chol(const MatDesc* __restrict_
 #pragma unroll
     for (int k = 0; k < R; ++k) row[k] = 0.f;
     if (have) {
-        if (mean) sum_parts_row<4>(ws + d.ppart_off + (int64_t)i * r, r, nparts, nr, row);
-        else sum_parts_row<1>(ws + d.ppart_off + (int64_t)i * r, r, nparts, nr, row);
+        if constexpr (MEAN) sum_parts_row_chains<R>(ws + d.ppart_off + (int64_t)i * r, r, nparts, nr, row);
+        else sum_parts_row<R>(ws + d.ppart_off + (int64_t)i * r, r, nparts, nr, row);
 #pragma unroll
         for (int k = 0; k < R; ++k) row[k] *= inv_w;
     }
@@ -1138,22 +1144,30 @@ void free_tables(psgd_plan* plan) {
 static psgd_status gram_fused_check_device(psgd_plan* plan) {
     plan->gram_fused = false;
     if (plan->hr || !plan->tuning.gram_fused || plan->tiles_gram.empty()) return PSGD_OK;
-    int dev = 0, cus = 0, occ = 0;
+    int dev = 0, cus = 0, occ = 0, occ_mean = 0;
     if (hipGetDevice(&dev) != hipSuccess) return PSGD_EHIP;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return PSGD_EHIP;
     hipError_t e = hipErrorInvalidValue;
+#define PSGD_GRAM_OCCUPANCY(RR)                                                                          \
+    case RR:                                                                                             \
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_gram_chol<RR, false>, kBlock, 0);       \
+        if (e == hipSuccess && plan->mean_first)                                                         \
+            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_mean, k_gram_chol<RR, true>, kBlock, 0); \
+        break
     switch (plan->rank) {
-        case 1: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_gram_chol<1>, kBlock, 0); break;
-        case 2: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_gram_chol<2>, kBlock, 0); break;
-        case 3: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_gram_chol<3>, kBlock, 0); break;
-        case 4: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_gram_chol<4>, kBlock, 0); break;
-        case 5: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_gram_chol<5>, kBlock, 0); break;
-        case 6: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_gram_chol<6>, kBlock, 0); break;
-        case 7: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_gram_chol<7>, kBlock, 0); break;
-        case 8: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_gram_chol<8>, kBlock, 0); break;
+        PSGD_GRAM_OCCUPANCY(1);
+        PSGD_GRAM_OCCUPANCY(2);
+        PSGD_GRAM_OCCUPANCY(3);
+        PSGD_GRAM_OCCUPANCY(4);
+        PSGD_GRAM_OCCUPANCY(5);
+        PSGD_GRAM_OCCUPANCY(6);
+        PSGD_GRAM_OCCUPANCY(7);
+        PSGD_GRAM_OCCUPANCY(8);
         default: break;
     }
+#undef PSGD_GRAM_OCCUPANCY
     if (e != hipSuccess) return hip_fail(plan, e, "occupancy(k_gram_chol)");
+    if (plan->mean_first) occ = std::min(occ, occ_mean);   // either may run: the mean's memory may not be had
     // gram_fused = 2 skips the test (diagnostic: lets a test see the waits time out)
     plan->gram_fused = plan->tuning.gram_fused == 2 || (int64_t)cus * occ >= (int64_t)plan->tiles_gram.size();
     return PSGD_OK;
@@ -1501,20 +1515,26 @@ psgd_status launch_compress(psgd_plan* plan, const void* grad, float* err, float
         hipError_t ge = hipSuccess;
         const dim3 ggrid((unsigned)plan->tiles_gram.size());
         slot_t* gmail = reinterpret_cast<slot_t*>(plan->dev.gram_mail);
-#define PSGD_LAUNCH_GRAM_CHOL(RR)                                                                                     \
-    hipLaunchKernelGGL((k_gram_chol<RR>), ggrid, dim3(kBlock), 0, s, mats, plan->dev.tiles_gram, ws, p, gmail, \
-                       plan->dev.gram_sync, workers, pre_reduced, mean ? 1 : 0, (unsigned)plan->tuning.gram_spin)
+#define PSGD_LAUNCH_GRAM_CHOL(RR, MEANV)                                                                              \
+    hipLaunchKernelGGL((k_gram_chol<RR, MEANV>), ggrid, dim3(kBlock), 0, s, mats, plan->dev.tiles_gram, ws, p, gmail, \
+                       plan->dev.gram_sync, workers, pre_reduced, (unsigned)plan->tuning.gram_spin)
+#define PSGD_GRAM_CHOL_CASE(RR)                       \
+    case RR:                                          \
+        if (mean) PSGD_LAUNCH_GRAM_CHOL(RR, true);    \
+        else PSGD_LAUNCH_GRAM_CHOL(RR, false);        \
+        break
         switch (plan->rank) {
-            case 1: PSGD_LAUNCH_GRAM_CHOL(1); break;
-            case 2: PSGD_LAUNCH_GRAM_CHOL(2); break;
-            case 3: PSGD_LAUNCH_GRAM_CHOL(3); break;
-            case 4: PSGD_LAUNCH_GRAM_CHOL(4); break;
-            case 5: PSGD_LAUNCH_GRAM_CHOL(5); break;
-            case 6: PSGD_LAUNCH_GRAM_CHOL(6); break;
-            case 7: PSGD_LAUNCH_GRAM_CHOL(7); break;
-            case 8: PSGD_LAUNCH_GRAM_CHOL(8); break;
+            PSGD_GRAM_CHOL_CASE(1);
+            PSGD_GRAM_CHOL_CASE(2);
+            PSGD_GRAM_CHOL_CASE(3);
+            PSGD_GRAM_CHOL_CASE(4);
+            PSGD_GRAM_CHOL_CASE(5);
+            PSGD_GRAM_CHOL_CASE(6);
+            PSGD_GRAM_CHOL_CASE(7);
+            PSGD_GRAM_CHOL_CASE(8);
             default: ge = hipErrorInvalidValue; break;
         }
+#undef PSGD_GRAM_CHOL_CASE
 #undef PSGD_LAUNCH_GRAM_CHOL
         if (ge == hipSuccess) ge = hipGetLastError();
         PSGD_HIP(ge, "launch k_gram_chol");
