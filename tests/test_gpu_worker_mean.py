@@ -226,3 +226,51 @@ def test_default_rule_against_the_oracle(workers, rank, grad_bf16):
         worst = compare(rg, ro, shapes, workers, rank, grads, prev)
         assert max(worst.values()) <= 1e-5, (t, worst)
     assert gpu.plan.worker_mean()[0]
+
+
+@pytest.mark.parametrize("iterations,workers,grad_bf16", [(1, 4, False), (3, 9, True)])
+def test_mean_route_replayed_from_a_hip_graph(iterations, workers, grad_bf16):
+    """Captured once, replayed with new gradients and other work in between: the bits of the same steps launched directly."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1905_13727_amd import binding as B
+    dev = torch.device("cuda:0")
+    plan = B.Plan(SHAPES, 2, workers, B.PSGD_BF16 if grad_bf16 else B.PSGD_F32, B.PSGD_F32)
+    plan.set_tuning("worker_mean", 1)
+    plan.check(None)
+    s = plan.sizes
+    assert plan.worker_mean() == (True, 4 * s.n_mat_elems)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(9)
+    dt = torch.bfloat16 if grad_bf16 else torch.float32
+    grads = [torch.randn(workers * s.grad_stride, generator=gen, device=dev).to(dt) for _ in range(4)]
+    q0 = torch.randn(s.q_elems, generator=gen, device=dev)
+    g_in, q, p = torch.zeros_like(grads[0]), q0.clone(), torch.zeros(s.p_elems, device=dev)
+    err, out = torch.zeros(workers * s.err_stride, device=dev), torch.zeros(s.out_elems, device=dev)
+    ws = torch.zeros(s.workspace_bytes // 4 + 64, device=dev)
+
+    def step():
+        plan.step_iterations(g_in, err, q, p, out, ws, iterations, torch.cuda.current_stream().cuda_stream)
+
+    def snapshot():
+        torch.cuda.synchronize()
+        return [x.clone() for x in (err, q, p, out)]
+
+    want = []
+    for g in grads:
+        g_in.copy_(g)
+        step()
+        want.append(snapshot())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    err.zero_(), out.zero_(), ws.fill_(float("nan")), q.copy_(q0)
+    for g, w in zip(grads, want):
+        g_in.copy_(g)
+        graph.replay()
+        noise = torch.randn(1 << 20, device=dev).mul_(2)   # unrelated work between the replays
+        got = snapshot()
+        assert torch.isfinite(noise).all() and all(torch.isfinite(x).all() for x in got)
+        for a, b in zip(got, w):
+            assert torch.equal(a, b)
+    plan.check(None)
