@@ -136,7 +136,8 @@ PSGD_API psgd_status psgd_plan_offsets(const psgd_plan* plan, int32_t tensor, in
  *   k1_rows, k1_nv / k3_rows, k3_nv / k4_rows, k4_nv
  *                 rows per workgroup tile and column vectors per lane of the three sweeps of the
  *                 streaming path (P = M Q; Q = M^T P_hat; decompression); rows 0 (default):
- *                 chosen per matrix by the planner
+ *                 chosen per matrix by the planner; k1_nv: products of each worker's M (of the mean
+ *                 over the workers always one vector per lane)
  *   hr_k1_rows, hr_k1_cols, hr_k3_rows, hr_k4_rows   tile shapes of the matrix-core path
  *                 (hr_k4_rows 0, the default: 64, 256 or 512 rows by rank <= 16, <= 32, <= 64)
  *   xcd_order     order of the tile lists over the accelerator dies: 0 plain, 1 one contiguous range
@@ -237,8 +238,9 @@ PSGD_API psgd_status psgd_iterate(psgd_plan* plan, float* err, float* q, float* 
  * ends).  The call allocates and frees nothing and otherwise behaves exactly like psgd_step with that workspace.
  * Conditions: the plan's tables are on the device already (psgd_plan_check, or any earlier GPU call on the plan,
  * puts them there; that upload makes all the allocations of a plan) - else PSGD_EINVAL; the plan's
- * workspace_bytes fit - else PSGD_EUNSUPPORTED (the ResNet18-shaped set up to 16 workers and the LSTM-shaped set
- * fit, the 24-layer transformer-shaped set does not); the current device is the plan's.  All plans on a GPU share
+ * workspace_bytes fit - else PSGD_EUNSUPPORTED (fp32, ranks up to 8: the ResNet18-shaped set fits with up to 8 workers
+ * and up to rank 4 with 16, the LSTM-shaped set with one or two workers; the 24-layer transformer-shaped set with bf16 data
+ * fits at ranks 2 and 4 and not at 16 or 32); the current device is the plan's.  All plans on a GPU share
  * the one array and it keeps whatever the last call left there (the kernels read nothing of it that they have
  * not written in the same call): calls that overlap in time on one GPU, from any plan or stream, race. */
 #define PSGD_STATIC_WORKSPACE_BYTES (32u << 20)

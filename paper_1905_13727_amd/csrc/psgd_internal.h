@@ -28,10 +28,11 @@ constexpr int kOrthoMaxRows = 1024; // largest value of the tuning key ortho_row
 // Whole steps, us, each worker by itself / the mean first: ResNet18-shaped set, rank 4, 16 workers 730 / 670, 8 workers 372 / 348, 4
 // workers 215 / 205; 24 matrices of 9 M elements, 5 workers 205 / 191; two transformer layers (42 M elements), 4 workers 729 / 657, bf16
 // gradients, rank 2 643 / 590; 1.1 M elements (ResNet18-shaped), 8 workers 76.6 / 68.0, 4 workers 44.2 / 44.2, 16 workers 153.7 / 153.5.
-// The other side of the line: two workers save no bytes (24 M elements 318 / 330); three gain without the update (144 / 134) and
-// lose with it (164 / 175); narrower accesses lose at 20 M elements in odd rows (3 workers, 260 / 304) and in the LSTM-shaped set's
-// rows of 650 (4 workers, 720 / 761); on small sets the serial walk over the workers is too long (five matrices: 4 workers 24.4 / 26.7, 16
-// workers 24.3 / 37.1; 32 workers: 1.1 M elements 287 / 293 and 149 / 158, 2.0 M 255 / 278, but 2.1 M 471 / 457, 2.8 M 487 / 416).
+// The other side of the line: two workers save no bytes (24 M elements 219 / 244); narrower accesses lose at 20 M elements in odd
+// rows (3 workers, 294 / 341) and in the LSTM-shaped set's rows of 650 (4 workers, 719 / 756); on small sets the serial walk over many
+// workers is too long (32 workers: 1.1 M elements 287 / 293 and 149 / 158, 2.0 M 255 / 278, but 2.1 M 471 / 457, 2.8 M 487 / 416).  Three
+// workers (ResNet18-shaped 168 / 157, with the update 198 / 193) and sets below 2^20 elements (0.7 M, 4 workers 38.7 / 35.8; five matrices,
+// 16 workers 36.5 / 36.9) have not been measured over a range, and stay with each worker by itself.
 constexpr int kMeanWorkers = 4;
 constexpr int64_t kMeanElems = int64_t(1) << 20;
 constexpr int64_t kMeanElemsPerWorker = int64_t(1) << 16;
@@ -210,7 +211,7 @@ struct psgd_plan {
     std::vector<psgd::Tile> tiles1m;        // mean_first: the first sweep's tiles, one column vector per lane ...
     std::vector<psgd::MatDesc> mats_mean;   // ... and the same matrices with their column chunks
     float* mbar = nullptr;                  // device, N floats: mean over the workers of M (mean_first)
-    bool mean_first = false;                // streaming kernels: products of the mean over the workers (where gram_fused holds)
+    bool mean_first = false;                // streaming kernels: the planner's choice of the mean (taken where mbar is there and gram_fused holds)
     bool update_around = false;             // fused update: momentum and parameters go around the memory-side cache
     bool stream_hints = false;              // see Tuning::stream_hints
     bool gram_fused = false;                // Cholesky-QR panels: one launch (k_gram_chol) instead of two (set at upload)

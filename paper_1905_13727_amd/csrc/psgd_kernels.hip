@@ -165,11 +165,11 @@ __global__ __launch_bounds__(kBlock) void k_ef_right(const MatDesc* __restrict__
 // several workers a wavefront therefore walks its rows once for all of them: every M_w = g_w + e_w is stored in
 // e_w's place as before, their mean goes to a buffer of its own, and the products are taken of the mean, once
 // instead of once per worker.  What follows (Q = M^T P_hat, further iterations) reads 4 bytes per element instead of
-// 4 W.  HBM-bound: 12 W + 4 bytes per element.  A step is RS rows of NV vectors, 16 elements per lane and array;
+// 4 W.  HBM-bound: 12 W + 4 bytes per element.  A step is RS rows of one vector, 16 elements per lane and array;
 // two workers' loads are in flight in two register sets that are consumed in turn, and the even and the odd workers
-// are summed apart.  ResNet18-shaped set, whole step: 16 workers, rank 4: 732 -> 672 us (first sweep 404 us, 5.4 TB/s,
-// second 10 us where it read 715 MB); 4 workers, rank 2: 213.5 -> 202.5 us.  Tiles of 8 or 32 rows and two vectors per
-// lane were 0 to 5 % slower on both.  Which sets take it: kMeanWorkers.
+// are summed apart.  ResNet18-shaped set, whole step: 16 workers, rank 4: 731 -> 672 us (at rank 2 the first sweep 396 us, 5.5 TB/s,
+// the second 8 us where it read 715 MB); 4 workers, rank 2: 212.9 -> 202.7 us.  Tiles of 8 or 32 rows and two vectors per
+// lane (691 us at 16 workers) were 0 to 5 % slower on both.  Which sets take it: kMeanWorkers.
 // ADD = false: M_w is read from e (psgd_iterate), nothing is added and e is not written.
 // STREAM: the M_w of all workers do not fit the memory-side cache: e is read and M_w written around it, which leaves it to the mean.
 template <int R, int V, bool ADD, bool GBF, bool STREAM>
