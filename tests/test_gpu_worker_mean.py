@@ -24,8 +24,9 @@ def test_mean_route_equals_general_route(rank, workers, grad_bf16, call):
 @pytest.mark.parametrize("rank,workers,grad_bf16,call", [
     (4, 9, True, "step"), (2, 16, False, "iterate"), (3, 12, False, "iterations"), (8, 9, True, "hints"),
     (2, 11, True, "iterate"), (1, 10, False, "hints iterate"), (5, 16, True, "hints iterations"),
+    (3, 9, False, "ortho step"), (8, 4, False, "ortho iterations"),
 ])
-def test_mean_route_equals_general_route_above_eight_workers(rank, workers, grad_bf16, call):
+def test_mean_route_equals_general_route_above_eight_workers_and_with_short_panels_apart(rank, workers, grad_bf16, call):
     _mean_route_equals_general_route(SHAPES, rank, workers, grad_bf16, call)
 
 
@@ -52,6 +53,8 @@ def _mean_route_equals_general_route(SHAPES, rank, workers, grad_bf16, call):
         plan.set_tuning("resident", 0)
         plan.set_tuning("gram_fused", fused)
         plan.set_tuning("worker_mean", fused)   # small sets and odd rows do not take it by themselves
+        if "ortho" in call:   # panels of at most 64 rows by one workgroup, the others over row blocks
+            plan.set_tuning("ortho_rows", 64)
         if "hints" in call:
             plan.set_tuning("stream_hints", 1)
         s = plan.sizes
