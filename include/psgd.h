@@ -19,8 +19,9 @@
  *
  * All data buffers are DEVICE pointers owned by the caller (allocate them with
  * any allocator; the tests use PyTorch).  The library owns only the plan, its
- * small device-side descriptor tables and, for some plans of several workers,
- * one buffer of N floats (psgd_plan_worker_mean says which).  No entry point
+ * small device-side descriptor tables and, for some plans, partial sums of at
+ * most 64 MiB (psgd_plan_one_sweep) or one buffer of N floats
+ * (psgd_plan_worker_mean).  No entry point
  * throws or aborts; every failure is a psgd_status.
  *
  * Flat layout (all offsets in elements, reported by psgd_plan_sizes /
@@ -152,6 +153,10 @@ PSGD_API psgd_status psgd_plan_offsets(const psgd_plan* plan, int32_t tensor, in
  *                 device holds all row blocks of the launch at once, 0 in two launches, 2 (TEST ONLY) in one
  *                 launch unconditionally: its waits may then time out, see psgd_plan_check
  *   gram_spin     polls before a wait in that launch gives up, 1 .. 2^24 (default 2^18)
+ *   one_sweep     streaming kernels, rank <= 4, where gram_fused holds: P = M Q and Q = M^T P_hat in one walk over M instead of
+ *                 two (psgd_plan_one_sweep); -1 (default) wherever every row fits one workgroup's registers (6144 elements, 4096
+ *                 with several workers, 3072 of even and 4096 of odd lengths) and the partial sums 64 MiB, unless another key asks
+ *                 for kernels of the two walks (k1_*, k3_*, ortho_rows, worker_mean, gram_fused = 0, 1 or 2), 0 never, 1 also then
  *   worker_mean   streaming kernels, where gram_fused holds: products of the mean over the workers' M instead of each
  *                 worker's own; -1 (default) from four workers and 2^20 elements on (2^16 per worker above sixteen workers) when
  *                 the rows of 15 in 16 elements are multiples of 4, 0 never, 1 with any two workers
@@ -174,7 +179,8 @@ PSGD_API psgd_status psgd_plan_set_tuning(psgd_plan* plan, const char* key, int6
  *   hip_stream            a hipStream_t (NULL = the default stream)
  * Everything is enqueued on hip_stream; the call does not synchronise, allocate
  * or read back, except that a plan's first GPU call allocates and uploads its
- * descriptor tables (one hipMalloc, one synchronous copy; where the tuning key
+ * descriptor tables (one hipMalloc, one synchronous copy; where one_sweep holds, a
+ * second hipMalloc for its partial sums, without which M is walked twice; else, where
  * worker_mean holds, a second hipMalloc of 4 N bytes for the mean over the workers of
  * M, without which, should it fail, each worker's M is multiplied by itself).
  * Vector-shaped tensors are not touched by this call. */
@@ -210,8 +216,9 @@ PSGD_API psgd_status psgd_decompress(psgd_plan* plan, const float* p, const floa
  * psgd_plan_check (below) reports it and moves the plan to the kernels that
  * need no co-residency.  A caller that may share the GPU checks every step,
  * or sets the tuning keys resident = 0 and gram_fused = 0.
- * Where worker_mean holds the streaming kernels also keep the mean over the
- * workers of M in plan-owned memory (only where gram_fused holds).
+ * Where worker_mean or one_sweep holds the streaming kernels also keep the mean
+ * over the workers of M, or partial sums, in plan-owned memory (only where
+ * gram_fused holds).
  * The plan's first GPU call (any entry point) uploads its tables (device
  * allocations and one copy).  After that this call, psgd_compress and psgd_decompress
  * only launch kernels on hip_stream: no allocation, no memset, no host
@@ -310,7 +317,8 @@ PSGD_API psgd_status psgd_plan_kept(const psgd_plan* plan, int32_t tensor, int64
  * end to accumulate the elapsed times: use it for measurement runs only.
  * psgd_plan_kernel_times copies the accumulated milliseconds per kernel (array
  * of PSGD_N_KERNELS doubles, order given by psgd_kernel_name) and the number of
- * accumulated steps, then clears the accumulators.  A plan in resident mode
+ * accumulated steps, then clears the accumulators.  Where psgd_plan_one_sweep
+ * holds, the first entry is k_one_sweep and the second k_solve.  A plan in resident mode
  * (see psgd_step) runs one kernel per step, index PSGD_KERNEL_RESIDENT; the
  * baseline steps (psgd_random_block_step, psgd_random_k_step) fill the last two
  * entries and wait for the stream at their end like psgd_decompress. */
@@ -365,6 +373,14 @@ PSGD_API psgd_status psgd_plan_path(const psgd_plan* plan, int32_t* path);
  * 0), and 0 and 4 N after psgd_plan_check has switched the one-launch orthogonalisation off.  A plan that runs only the
  * baselines of Appendix G holds the memory too; worker_mean = 0 avoids it.  Either output may be NULL; PSGD_EINVAL for a NULL plan. */
 PSGD_API psgd_status psgd_plan_worker_mean(const psgd_plan* plan, int32_t* taken, int64_t* bytes);
+
+/* Whether this plan's steps go through M once per iteration before the decompression (tuning key one_sweep; the values differ
+ * from those of the two walks by rounding only), and the device memory the plan holds for the partial sums, which no field of
+ * psgd_sizes counts.  Before the plan's first GPU call both are the planner's choice, after it what holds: 0 and 0 where the
+ * device does not hold the one-launch orthogonalisation or the memory could not be had.  With several workers the products are
+ * then of the mean over the workers (psgd_plan_worker_mean says 1, and 0 bytes).  A plan in resident mode uses it in
+ * psgd_compress and psgd_iterate.  Either output may be NULL; PSGD_EINVAL for a NULL plan. */
+PSGD_API psgd_status psgd_plan_one_sweep(const psgd_plan* plan, int32_t* taken, int64_t* bytes);
 
 /* Static, never NULL. */
 PSGD_API const char* psgd_status_string(psgd_status status);

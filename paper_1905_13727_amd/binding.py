@@ -75,6 +75,8 @@ def load_library(path: Optional[str] = None):
     lib.psgd_random_k_step.argtypes = [vp, vp, vp, vp, vp, vp, vp]
     lib.psgd_plan_path.restype = C.c_int
     lib.psgd_plan_path.argtypes = [vp, C.POINTER(i32)]
+    lib.psgd_plan_one_sweep.restype = C.c_int
+    lib.psgd_plan_one_sweep.argtypes = [vp, C.POINTER(i32), C.POINTER(i64)]
     lib.psgd_plan_worker_mean.restype = C.c_int
     lib.psgd_plan_worker_mean.argtypes = [vp, C.POINTER(i32), C.POINTER(i64)]
     lib.psgd_plan_kept.restype = C.c_int
@@ -204,6 +206,12 @@ class Plan:
         r = C.c_int32()
         self._check(self._lib.psgd_plan_path(self._h, C.byref(r)), "psgd_plan_path")
         return ("streaming", "resident", "matrix cores")[r.value]
+
+    def one_sweep(self):
+        """(M is walked once per iteration before the decompression, bytes the plan holds for it)."""
+        taken, n = C.c_int32(), C.c_int64()
+        self._check(self._lib.psgd_plan_one_sweep(self._h, C.byref(taken), C.byref(n)), "psgd_plan_one_sweep")
+        return bool(taken.value), n.value
 
     def worker_mean(self):
         """(whether the products are taken of the mean over the workers, device bytes the plan holds for that mean)."""

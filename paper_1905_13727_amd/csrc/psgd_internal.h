@@ -108,7 +108,44 @@ struct RTile {
     int64_t elem0, nelem;  // vector tiles: slice of the vector region
 };
 
+// P = M Q and S = M^T P in one walk over M (k_one_sweep, k_solve)
+constexpr int kOneMaxRank = 4;
+constexpr int kOneMaxWaves = 8;     // wavefronts of a workgroup, and of a row
+constexpr int kOneRows = 2;         // rows of a step
+constexpr int64_t kOneMaxBytes = int64_t(64) << 20;   // plan-owned partial sums
+// Column vectors a lane owns (12 columns; fewer with several workers, whose steps take the registers of two more sets of rows, and of
+// rows that are read element by element), and steps whose loads are in flight: what 256 registers hold beside the lane's fp64
+// sums (rank 4: 96 of them).  LSTM-shaped set, rank 4, k_one_sweep: 12 columns, one step 69 us; 6 columns and two wavefronts to a
+// row, three steps 78.  24 matrices, three workers, two iterations: 8 / 6 / 8 columns, two steps 182 us a pass, 12 and one step 196.
+constexpr int one_nv(int v, bool mean) { return (v == 1 ? 8 : (!mean ? 12 : (v == 2 ? 6 : 8))) / v; }
+constexpr int one_depth(int r, bool mean) { return mean || r <= 2 ? 2 : 1; }
+// floats of Q a lane needs, in sets of four
+constexpr int one_q_floats(int r, int v, bool mean) { return (one_nv(v, mean) * v * r + 3) / 4 * 4; }
+// column vectors of a lane whose sums are added over the workgroup's groups at a time (at most 16 doubles a lane)
+constexpr int one_deposit(int r, int v, bool mean) {
+    int n = 16 / (v * r) < 1 ? 1 : 16 / (v * r);
+    while (one_nv(v, mean) % n) --n;
+    return n;
+}
+struct OneMat {
+    int64_t off, p_off, q_off;   // as in MatDesc
+    int64_t s_off, g_off;        // in doubles: [n_blocks][m][r] of partial S, [n_blocks][R (R + 1) / 2] of partial Gram matrices
+    int32_t n, m, r, vec;
+    int32_t n_blocks;            // row blocks
+    int32_t waves_log2;          // wavefronts that share a row
+};
+struct OneTile {
+    int32_t mat, row0, nrows, block;
+};
+struct SolveTile {
+    int32_t mat;
+    int32_t first, count;        // rows of P (`rows`), else rows of Q
+    int16_t rows, cols_log2;     // rows of Q per workgroup, 2^cols_log2
+};
+
 struct Tuning {
+    int64_t one_sweep = -1; // P = M Q and Q = M^T P_hat in one walk over M: -1 by the rule at build_one_sweep, 0 never, 1 also where another key
+                            // asks for a kernel of the two walks
     int64_t k1_rows = 0;    // rows per workgroup tile, P = M Q; 0: by the access width of the matrix (16 / 32 / 64; twice
                             // that for small sets)
     int64_t k1_nv = 2;      // column vectors per lane (<= kMaxVecPerLaneK1); products of the mean over the workers: always one
@@ -125,9 +162,9 @@ struct Tuning {
                                 // memory (and temporal instead of non-temporal stores of Delta'); matrix-core path:
                                 // non-temporal loads of M in sweep 2.
                                 // -1: when M of all workers exceeds kStreamHintBytes; 0: never; 1: always
-    int64_t gram_fused = 1; // Cholesky-QR panels: 1 = Gram matrices and factorisation in one launch when the device holds a matrix's
+    int64_t gram_fused = -1; // Cholesky-QR panels of the two walks: 1 = Gram matrices and factorisation in one launch when the device holds a matrix's
                             // row blocks at once; 0 = always the two launches; 2 = one launch whatever the device holds
-                            // (diagnostic: the waits may time out, which psgd_plan_check then reports)
+                            // (diagnostic: the waits may time out, which psgd_plan_check then reports); -1 as 1, and one walk may be taken instead
     int64_t gram_spin = 1 << 18;   // polls of one slot in that launch before a wait gives up
     int64_t ortho_rows = 0;        // panels of at most this many rows (and kPanelFloats values) are orthogonalised by one workgroup
                                    // with Gram-Schmidt in LDS (k_ortho), the others by Cholesky-QR over row blocks; 0: none (a
@@ -148,6 +185,9 @@ struct Tuning {
 };
 
 struct DeviceTables {
+    OneMat* one_mats = nullptr;
+    OneTile* one_tiles = nullptr;
+    SolveTile* solve_tiles = nullptr;
     MatDesc* mats = nullptr;
     MatDesc* mats_mean = nullptr;
     Tile* tiles1 = nullptr;
@@ -219,6 +259,15 @@ struct psgd_plan {
     int64_t ws_ppart_floats = 0;            // workspace: partial P region (floats)
     int64_t ws_qpart_floats = 0;            // workspace: partial Q region, starts after partial P
     psgd::Tuning tuning;
+    // one walk over M per iteration
+    bool one_sweep = false;                 // taken (after the upload: the partial sums' memory is there)
+    int32_t one_waves = 0;                  // wavefronts of a workgroup
+    int32_t one_lds_bytes = 0;
+    int64_t one_s_doubles = 0, one_bytes = 0;   // partial S, and partial S and Gram matrices: plan-owned
+    double* one_part = nullptr;             // device
+    std::vector<psgd::OneMat> one_mats;
+    std::vector<psgd::OneTile> one_tiles;
+    std::vector<psgd::SolveTile> solve_tiles;
     // resident path
     bool resident_ok = false;               // planner found a tiling that fits the chip
     int32_t res_strip_rows = 0;
@@ -268,6 +317,10 @@ psgd_status launch_compress(psgd_plan* plan, const void* grad, float* err, float
 psgd_status launch_decompress(psgd_plan* plan, const float* p, const float* q, float* err,
                               const void* grad, void* out, void* workspace, void* stream,
                               const UpdateArgs& upd = UpdateArgs());
+// P and the partial S and Gram matrices, then P_hat and Q from them (one walk over M)
+psgd_status launch_one_sweep(psgd_plan* plan, const void* grad, float* err, const float* q, float* p, void* stream, bool add);
+psgd_status launch_solve(psgd_plan* plan, float* q, float* p, void* stream);
+psgd_status one_sweep_prepare(psgd_plan* plan);   // once per plan, at the upload
 psgd_status set_profiling(psgd_plan* plan, bool enable);
 // workers: those that have partial Q of their own
 psgd_status launch_q_reduce(psgd_plan* plan, float* ws, float* q, void* stream, int workers);

@@ -1136,6 +1136,8 @@ void free_tables(psgd_plan* plan) {
     }
     if (plan->mbar) (void)hipFree(plan->mbar);
     plan->mbar = nullptr;
+    if (plan->one_part) (void)hipFree(plan->one_part);
+    plan->one_part = nullptr;
     plan->uploaded = false;
 }
 
@@ -1186,7 +1188,7 @@ psgd_status upload_tables(psgd_plan* plan) {
         if (st != PSGD_OK) return st;
     }
     struct Piece { const void* src; size_t bytes; size_t at; };
-    Piece pieces[25] = {
+    Piece pieces[28] = {
         {plan->mats.data(), plan->mats.size() * sizeof(MatDesc), 0},
         {plan->tiles1.data(), plan->tiles1.size() * sizeof(Tile), 0},
         {plan->tiles3.data(), plan->tiles3.size() * sizeof(Tile), 0},
@@ -1212,6 +1214,9 @@ psgd_status upload_tables(psgd_plan* plan) {
         {plan->mat_tensor.data(), plan->mat_tensor.size() * sizeof(int32_t), 0},
         {plan->mats_mean.data(), plan->mats_mean.size() * sizeof(MatDesc), 0},
         {plan->tiles1m.data(), plan->tiles1m.size() * sizeof(Tile), 0},
+        {plan->one_mats.data(), plan->one_mats.size() * sizeof(OneMat), 0},
+        {plan->one_tiles.data(), plan->one_tiles.size() * sizeof(OneTile), 0},
+        {plan->solve_tiles.data(), plan->solve_tiles.size() * sizeof(SolveTile), 0},
     };
     size_t total = 0;
     for (Piece& pc : pieces) {
@@ -1264,8 +1269,26 @@ psgd_status upload_tables(psgd_plan* plan) {
     plan->dev.mat_tensor = reinterpret_cast<int32_t*>(b + pieces[22].at);
     plan->dev.mats_mean = reinterpret_cast<MatDesc*>(b + pieces[23].at);
     plan->dev.tiles1m = reinterpret_cast<Tile*>(b + pieces[24].at);
+    plan->dev.one_mats = reinterpret_cast<OneMat*>(b + pieces[25].at);
+    plan->dev.one_tiles = reinterpret_cast<OneTile*>(b + pieces[26].at);
+    plan->dev.solve_tiles = reinterpret_cast<SolveTile*>(b + pieces[27].at);
+    // One walk over M: its partial sums are plan-owned, which is no new restriction where gram_fused holds (calls of one plan must
+    // not overlap there); elsewhere, and where the memory cannot be had, M is walked twice.
+    if (plan->one_sweep) {
+        if (!plan->gram_fused || hipMalloc(reinterpret_cast<void**>(&plan->one_part), (size_t)plan->one_bytes) != hipSuccess) {
+            plan->one_part = nullptr;
+            plan->one_sweep = false;
+            (void)hipGetLastError();
+        } else {
+            psgd_status st = one_sweep_prepare(plan);
+            if (st != PSGD_OK) {   // a later call uploads again
+                free_tables(plan);
+                return st;
+            }
+        }
+    }
     // the mean over the workers of M; without it every worker's M is multiplied by itself
-    if (plan->mean_first && !plan->hr && plan->gram_fused &&
+    if (plan->mean_first && !plan->hr && !plan->one_sweep && plan->gram_fused &&
         hipMalloc(reinterpret_cast<void**>(&plan->mbar), (size_t)plan->sizes.n_mat_elems * sizeof(float)) != hipSuccess) {
         plan->mbar = nullptr;
         (void)hipGetLastError();
@@ -1487,6 +1510,15 @@ psgd_status launch_compress(psgd_plan* plan, const void* grad, float* err, float
 
     PSGD_MARK(0);
     plan->compress_marked = plan->profiling;
+    if (plan->one_sweep) {
+        st = launch_one_sweep(plan, g, err, q, p, stream, add);
+        if (st != PSGD_OK) return st;
+        PSGD_MARK(1);
+        st = launch_solve(plan, q, p, stream);
+        if (st != PSGD_OK) return st;
+        for (int i = 2; i <= 4; ++i) PSGD_MARK(i);   // no second walk, no reduction of Q
+        return PSGD_OK;
+    }
     // Several workers: the products are taken of the mean over the workers.  It lives in plan-owned memory, which is
     // no new restriction where gram_fused holds (calls of one plan must not overlap there); elsewhere, and where that
     // memory could not be had, every worker's M is multiplied by itself.

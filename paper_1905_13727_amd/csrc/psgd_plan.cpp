@@ -144,7 +144,7 @@ static psgd_status build_hr_tables(psgd_plan* plan) {
     const Tuning& tu = plan->tuning;
     if (tu.hr_k3_rows < 64 || tu.hr_k1_rows < 64 || tu.hr_k1_rows > 256 || tu.hr_k1_rows % 64 != 0 ||
         tu.hr_k1_cols < 64 || tu.hr_k1_cols % 64 != 0 || (tu.hr_k4_rows != 0 && (tu.hr_k4_rows < 16 || tu.hr_k4_rows > 1024)) ||
-        tu.stream_hints < -1 || tu.stream_hints > 1 || tu.xcd_order < -1 || tu.gram_fused < 0 || tu.gram_fused > 2 || tu.gram_spin < 1 ||
+        tu.stream_hints < -1 || tu.stream_hints > 1 || tu.xcd_order < -1 || tu.gram_fused < -1 || tu.gram_fused > 2 || tu.gram_spin < 1 ||
         tu.gram_spin > (1 << 24))
         return PSGD_EINVAL;
     for (const MatDesc& d : plan->mats)   // 16-byte accesses along the rows, 31-bit byte offsets within a tile
@@ -244,6 +244,125 @@ static psgd_status build_hr_tables(psgd_plan* plan) {
     return PSGD_OK;
 }
 
+// One walk over M (k_one_sweep): what a row costs its workgroup, in elements: halfway between its own and those that the lanes
+// of its wavefronts could take (a row of 139 elements keeps a wavefront for 512 waiting almost as long as a full one does).  With
+// blocks of equal elements instead, sets of many matrices lost up to 16 % to the other route that now gain (60 matrices of 15 M
+// elements, rank 4: 100 us by the other route, 115 with equal elements, 87 with equal costs).
+static int64_t one_row_cost(const OneMat& o, bool mean) {
+    return (o.m + ((int64_t)kWave << o.waves_log2) * one_nv(o.vec, mean) * o.vec) / 2;
+}
+
+// Row blocks per matrix for `slots` workgroups: all on the device at once (a second generation of workgroups adds its first loads
+// and last sums, 6 us, and was never faster), and within that as little in the largest as can be.  Returns that one's cost.
+static int64_t one_sweep_blocks(const psgd_plan* plan, int waves, int64_t slots, std::vector<int64_t>* blocks) {
+    const bool mean = plan->workers > 1;
+    int64_t total = 0;
+    for (const OneMat& o : plan->one_mats) total += o.n * one_row_cost(o, mean);
+    auto blocks_of = [&](const OneMat& o, int64_t cost) {
+        const int64_t groups = waves >> o.waves_log2;
+        const int64_t most = ceil_div(o.n, groups * kOneRows * one_depth(plan->rank, mean));   // a full pipeline for every group
+        return std::min(most, ceil_div(o.n * one_row_cost(o, mean), cost));
+    };
+    int64_t cost = std::max<int64_t>(1, ceil_div(total, slots));
+    for (;;) {
+        int64_t tiles = 0;
+        for (const OneMat& o : plan->one_mats) tiles += blocks_of(o, cost);
+        if (tiles <= slots || cost >= total) break;
+        cost += ceil_div(cost, 64);
+    }
+    blocks->clear();
+    int64_t largest = 0;
+    for (const OneMat& o : plan->one_mats) {
+        blocks->push_back(blocks_of(o, cost));
+        largest = std::max(largest, ceil_div(o.n, blocks->back()) * one_row_cost(o, mean));
+    }
+    return largest;
+}
+
+// Whether a plan's sets go through one walk over M per iteration instead of two (see k_one_sweep), and its tables.  Ranks up to
+// kOneMaxRank, every row short enough for the registers of one workgroup, partial sums of at most kOneMaxBytes.  Whole steps, us, two
+// walks / one: LSTM-shaped set, rank 4, 1 / 2 / 4 workers 171 / 337 / 718 and 157 / 287 / 632; rank 1, 2, 3 167, 169, 171 and 149, 154, 153;
+// two transformer layers (42 M elements), rank 2, bf16, 1 / 2 workers 183 / 365 and 168 / 305; 24 matrices of 9 M, 3 workers, two
+// iterations 209 / 172; 3 to 80 matrices of 0.04 to 24 M elements in rows of any length, 1 and 3 workers: 1.00 to 1.33 and 1.09 to 1.41
+// times as fast; ResNet18-shaped, 0.7 to 2.8 M, 2 and 4 workers 1.07 to 1.24 times.  Beyond rank 4 the registers hold less of a row: at rank
+// 6 and 8 it gained 3 % on the LSTM-shaped set and nothing elsewhere.
+static void build_one_sweep(psgd_plan* plan) {
+    plan->one_sweep = false;
+    plan->one_mats.clear(); plan->one_tiles.clear(); plan->solve_tiles.clear();
+    const Tuning& tu = plan->tuning;
+    const int R = plan->rank;
+    const int64_t W = plan->workers;
+    const bool mean = W > 1;
+    // keys that ask for a particular kernel of the two walks, or for its tiles, get it
+    const bool two = tu.k1_rows || tu.k1_nv != 2 || tu.k3_rows || tu.k3_nv != 1 || tu.ortho_rows || tu.gram_fused >= 0 || tu.worker_mean >= 0;
+    if (!tu.one_sweep || (tu.one_sweep < 0 && two) || R > kOneMaxRank || plan->mats.empty()) return;
+    int max_log2 = 0;
+    for (const MatDesc& d : plan->mats) {
+        const int64_t lanes = ceil_div(d.m / d.vec, one_nv(d.vec, mean));
+        int l2 = 0;
+        while ((1 << l2) <= kOneMaxWaves && ((int64_t)kWave << l2) < lanes) ++l2;
+        if ((1 << l2) > kOneMaxWaves || (int64_t)d.n * d.r * 4 >= (int64_t(1) << 31)) {
+            plan->one_mats.clear();
+            return;
+        }
+        max_log2 = std::max(max_log2, l2);
+        OneMat o{};
+        o.off = d.off; o.p_off = d.p_off; o.q_off = d.q_off;
+        o.n = d.n; o.m = d.m; o.r = d.r; o.vec = d.vec; o.waves_log2 = l2;
+        plan->one_mats.push_back(o);
+    }
+    // Two workgroups of four wavefronts on a compute unit, or one of eight, which writes half the partial S (LSTM-shaped set, rank 4, 1 / 2
+    // workers 159 / 302 and 157 / 287 us) but divides the matrices more coarsely (80 matrices of 24 M elements 128 / 133): the
+    // cheaper by the time of the largest block, of the partial S written and read, and of the longest sum over blocks.
+    const double bytes = (double)W * ((plan->grad_dtype == PSGD_BF16 ? 2 : 4) + 8);
+    double best = 0;
+    std::vector<int64_t> blocks, trial;
+    for (int waves : {4, 8}) {
+        if ((1 << max_log2) > waves) continue;
+        const int64_t slots = (int64_t)kResCUs * (kOneMaxWaves / waves);
+        const int64_t cost = one_sweep_blocks(plan, waves, slots, &trial);
+        double partial = 0;
+        int64_t longest = 0;
+        for (size_t i = 0; i < trial.size(); ++i) {
+            partial += 16.0 * trial[i] * plan->one_mats[i].m * plan->one_mats[i].r;
+            longest = std::max(longest, trial[i]);
+        }
+        const double us = ((double)cost * slots * bytes + partial) / 6e6 + 0.025 * longest + (waves == 8 ? 2.0 : 0.0);
+        if (blocks.empty() || us < best) {
+            best = us;
+            blocks = trial;
+            plan->one_waves = waves;
+        }
+    }
+    const int64_t NG = R * (R + 1) / 2;
+    int64_t sd = 0, gd = 0, lds = 0;
+    for (size_t i = 0; i < plan->one_mats.size(); ++i) {
+        OneMat& o = plan->one_mats[i];
+        o.n_blocks = (int32_t)blocks[i];
+        o.s_off = sd;
+        sd += (int64_t)o.n_blocks * o.m * o.r;
+        o.g_off = gd;
+        gd += (int64_t)o.n_blocks * NG;
+        lds = std::max<int64_t>(lds, ((int64_t)kWave << o.waves_log2) * one_q_floats(R, o.vec, mean) * (int64_t)sizeof(float));
+        lds = std::max<int64_t>(lds, (int64_t)one_deposit(R, o.vec, mean) * o.vec * R * (plan->one_waves * kWave + 1) * (int64_t)sizeof(double));
+        for (int64_t b = 0; b < o.n_blocks; ++b) {
+            int64_t r0, rn;
+            even_split(o.n, o.n_blocks, b, &r0, &rn);
+            plan->one_tiles.push_back({(int32_t)i, (int32_t)r0, (int32_t)rn, (int32_t)b});
+        }
+        // columns of Q per workgroup: fewer, with more threads to a column, where there are many blocks to add
+        const int cl = o.n_blocks >= 16 ? 4 : (o.n_blocks >= 4 ? 6 : 8);
+        for (int64_t c = 0; c < o.m; c += 1 << cl)
+            plan->solve_tiles.push_back({(int32_t)i, (int32_t)c, (int32_t)std::min<int64_t>(1 << cl, o.m - c), 0, (int16_t)cl});
+        for (int64_t c = 0; c < o.n; c += kBlock)
+            plan->solve_tiles.push_back({(int32_t)i, (int32_t)c, (int32_t)std::min<int64_t>(kBlock, o.n - c), 1, 8});
+    }
+    plan->one_s_doubles = round_up(sd, 32);
+    plan->one_lds_bytes = (int32_t)lds;
+    plan->one_bytes = (plan->one_s_doubles + gd) * (int64_t)sizeof(double);
+    plan->one_sweep = plan->one_bytes <= kOneMaxBytes;
+}
+
 psgd_status build_tables(psgd_plan* plan) {
     const Tuning& tu = plan->tuning;
     // Ranks above 8 run on the matrix-core kernels; bf16 data at the lower ranks on either (bf16_valu).  The planner's
@@ -260,14 +379,15 @@ psgd_status build_tables(psgd_plan* plan) {
             if (d.m % 4 != 0 || d.m > kHrMaxCols || d.n > kHrMaxRows) hr_low = false;
     }
     plan->hr = plan->rank > kValuMaxRank || hr_low;
+    plan->one_sweep = false;
     if (plan->hr) return build_hr_tables(plan);
     if (plan->out_dtype != PSGD_F32 && tu.k4_nv != 1) return PSGD_EINVAL;   // bf16 output: one column vector per lane
     if (tu.k1_rows < 0 || tu.k3_rows < 0 || tu.k4_rows < 0 || tu.k1_nv < 1 ||
         tu.k1_nv > kMaxVecPerLaneK1 || tu.k3_nv < 1 || tu.k3_nv > kMaxVecPerLaneK3 || tu.k4_nv < 1 ||
         tu.k4_nv > kMaxVecPerLaneK3 || tu.res_rows < 0 || tu.res_rows > kResRows || tu.resident < 0 || tu.resident > 2 ||
         tu.res_spin < 1 || tu.res_spin > (int64_t(1) << 30) || tu.res_max_blocks < 0 || tu.res_max_blocks > 65535 ||
-        tu.stream_hints < -1 || tu.stream_hints > 1 || tu.xcd_order < -1 || tu.gram_fused < 0 || tu.gram_fused > 2 || tu.gram_spin < 1 ||
-        tu.gram_spin > (1 << 24) || tu.ortho_rows < 0 || tu.ortho_rows > kOrthoMaxRows)
+        tu.stream_hints < -1 || tu.stream_hints > 1 || tu.xcd_order < -1 || tu.gram_fused < -1 || tu.gram_fused > 2 || tu.gram_spin < 1 ||
+        tu.gram_spin > (1 << 24) || tu.ortho_rows < 0 || tu.ortho_rows > kOrthoMaxRows || tu.one_sweep < -1 || tu.one_sweep > 1)
         return PSGD_EINVAL;
     const size_t nm = plan->mats.size();
     // k_ef_right and k_left address the rows of a wavefront's strip (a quarter of the tile's rows) with 31-bit
@@ -284,7 +404,7 @@ psgd_status build_tables(psgd_plan* plan) {
         if (d.vec != 4) narrow += (int64_t)d.n * d.m;
     if (narrow > plan->sizes.n_mat_elems / 16) plan->mean_first = false;
     if (tu.worker_mean >= 0) plan->mean_first = tu.worker_mean == 1 && plan->workers > 1;
-    if (!tu.gram_fused) plan->mean_first = false;
+    if (tu.gram_fused == 0) plan->mean_first = false;
     streaming_tiles(plan, 1, tu.k1_rows, tu.k1_nv, true, &plan->tiles1, nullptr, &ncc);
     // The mean first: a list of its own with one column vector per lane, as the sums over the workers take the registers of the
     // second.  Half as wide chunks at most double the partial P of one product, and there is one product instead of W >= 2: the
@@ -397,6 +517,7 @@ psgd_status build_tables(psgd_plan* plan) {
     }
     plan->stream_hints = tu.stream_hints < 0 ? W * plan->sizes.n_mat_elems * (int64_t)sizeof(float) > kStreamHintBytes
                                              : tu.stream_hints != 0;
+    build_one_sweep(plan);
     build_resident(plan, (int64_t)kResCUs * kResBlocksPerCU);
     plan->sizes.workspace_bytes =
         std::max<int64_t>(plan->sizes.workspace_bytes, plan->res_ws_floats * (int64_t)sizeof(float));
@@ -728,9 +849,21 @@ psgd_status psgd_plan_path(const psgd_plan* plan, int32_t* path) {
 
 psgd_status psgd_plan_worker_mean(const psgd_plan* plan, int32_t* taken, int64_t* bytes) {
     if (!plan) return PSGD_EINVAL;
+    if (plan->one_sweep) {   // the mean is formed as M is walked, and held nowhere
+        if (taken) *taken = plan->workers > 1 ? 1 : 0;
+        if (bytes) *bytes = 0;
+        return PSGD_OK;
+    }
     const bool held = plan->uploaded ? plan->mbar != nullptr : plan->mean_first;
     if (taken) *taken = held && (!plan->uploaded || plan->gram_fused) ? 1 : 0;
     if (bytes) *bytes = held ? plan->sizes.n_mat_elems * (int64_t)sizeof(float) : 0;
+    return PSGD_OK;
+}
+
+psgd_status psgd_plan_one_sweep(const psgd_plan* plan, int32_t* taken, int64_t* bytes) {
+    if (!plan) return PSGD_EINVAL;
+    if (taken) *taken = plan->one_sweep ? 1 : 0;
+    if (bytes) *bytes = plan->one_sweep ? plan->one_bytes : 0;
     return PSGD_OK;
 }
 
@@ -770,6 +903,7 @@ psgd_status psgd_plan_set_tuning(psgd_plan* plan, const char* key, int64_t value
     else if (!strcmp(key, "gram_fused")) tu.gram_fused = value;
     else if (!strcmp(key, "gram_spin")) tu.gram_spin = value;
     else if (!strcmp(key, "ortho_rows")) tu.ortho_rows = value;
+    else if (!strcmp(key, "one_sweep")) tu.one_sweep = value;
     else if (!strcmp(key, "res_rows")) tu.res_rows = value;
     else if (!strcmp(key, "res_trace")) tu.res_trace = value;
     else if (!strcmp(key, "res_spin")) tu.res_spin = value;
