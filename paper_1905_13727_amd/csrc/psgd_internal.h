@@ -87,6 +87,11 @@ constexpr int kResMaxRank = 4;
 constexpr int kResCUs = 256;         // MI355X compute units: the planner's provisional figure (it runs without a device); the
                                      // tiling is laid out again for the device's own count when the tables are uploaded
 constexpr int kResBlocksPerCU = 2;   // 256-thread workgroups per compute unit (8 wavefronts, 2 per SIMD)
+// Resident step fused with the update: from this many elements on momentum and parameters go around the caches (stream_hints < 0).
+// Four states of a set in turn, us, ordinary / around: ResNet18-shaped, 11.2 M elements, rank 2 / 4 70.4 / 80.8 and 62.7 / 72.5; 6.3 M,
+// rank 1 45.9 and 39.4; 3.9 M, rank 2 32.1 and 34.9; 2.8 M, rank 4 34.5 and 36.8; five matrices 15.9 and 16.8.  One state alone over and over,
+// which the memory-side cache then holds, loses by it above the line: 11.2 M 58.4 / 67.1 and 62.7 / 72.8, 6.3 M 35.8 and 38.7.
+constexpr int64_t kResAroundElems = 4000000;
 constexpr int kResTracePoints = 16;  // diagnostic timestamps per workgroup of the resident kernel
 
 // One wavefront's share of the resident kernel.

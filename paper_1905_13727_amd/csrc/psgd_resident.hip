@@ -58,6 +58,7 @@ struct ResArgs {
     unsigned long long* trace;   // diagnostic: kResTracePoints timestamps per workgroup, or nullptr
     unsigned spin;               // polls before a wait gives up
     int32_t iters;               // subspace iterations per step (ITER kernels; 1 otherwise)
+    int32_t update_around;       // UPD kernels: momentum and parameters are read and written around the caches
     UpdateArgs upd;              // UPD kernels: momentum / parameter buffers and step sizes (Algorithm 2's last lines)
 };
 
@@ -109,8 +110,9 @@ __device__ __forceinline__ void gram_schmidt_rows(float (&P)[kResRowsPerLane][R]
 // ---- the step, for a workgroup whose tiles use V-wide row accesses ---------------------------------------
 // ITER: several subspace iterations on the resident tile (Appendix G.7): P = M Q, orthogonalise, Q = M^T P_hat
 // repeated a.iters times before the decompression, each round under its own mailbox tag epoch0 + round.
+// UPD: the momentum / parameter update taken along: 1, or 2 with non-temporal accesses to them (update_around).
 // RT: rows of the tile the code is written out for (the strips of the plan are no taller).
-template <int R, int V, bool UPD, bool ITER, int RT>
+template <int R, int V, int UPD, bool ITER, int RT>
 __device__ __forceinline__ void resident_body(const ResArgs& a, const RTile& t, float* lds, unsigned epoch0) {
     const int lane_id = threadIdx.x & (kWave - 1);
     const int lane = lane_id;
@@ -442,22 +444,61 @@ __device__ __forceinline__ void resident_body(const ResArgs& a, const RTile& t, 
     // ---------------- phase C ----------------
     float (&qb)[V][R] = qr;
     trace_mark(a, 5);
-    constexpr int CG = UPD ? 4 : 1;   // rows whose momentum / parameter loads are in flight together
+    if constexpr (UPD) {
+        // Momentum and parameters of the next CG rows are requested before those of the current ones are stored: loads and stores
+        // of a wavefront complete in order, so a request behind the stores waits for their acknowledgement as well.  Strip
+        // descriptors (rows past the strip and lanes without columns: zeros are read, stores dropped) keep branches away from the
+        // accesses, so that the waits count what is outstanding.  ResNet18-shaped set, rank 4, momentum and parameters that other work
+        // has pushed out of the caches in between: 88.0 us with four rows requested, updated and stored in turn, 83.4 with twelve, 81.0
+        // with four ahead of four (six 81.0, eight 83.2, three 82.5), 72.5 with momentum and parameters read and written around the
+        // caches as well (the loads alone 80.3, the stores alone 81.2, e' too 78.8).  Which sets do: kResAroundElems.
+        constexpr int CG = 4;
+        const int64_t strip = d.off + (int64_t)t.row0 * d.m;
+        const int64_t bytes = (int64_t)nrows * d.m * 4;
+        const buf_rsrc eres = make_rsrc(a.err + strip, bytes), mres = make_rsrc(a.upd.mom + strip, bytes), xres = make_rsrc(a.upd.param + strip, bytes);
+        const unsigned coff = valid ? (unsigned)col * 4u : kOutOfRange;
+        float mo[2][CG][V], pa[2][CG][V];
+        auto request = [&](int i0, float (&m)[CG][V], float (&x)[CG][V]) {
 #pragma unroll
-    for (int i0 = 0; i0 < RT; i0 += CG) {
-        float mo[CG][V], pa[CG][V];
-        if constexpr (UPD) {
+            for (int u = 0; u < CG; ++u) {
+                const unsigned off = coff + (unsigned)(i0 + u) * (unsigned)d.m * 4u;
+                buf_ldv<V>(mres, off, m[u], UPD == 2);
+                buf_ldv<V>(xres, off, x[u], UPD == 2);
+            }
+        };
+        request(0, mo[0], pa[0]);
 #pragma unroll
-            for (int u = 0; u < CG; ++u)
-                if (i0 + u < RT && i0 + u < nrows && valid) {
-                    ldv<V>(a.upd.mom + tile_off + (int64_t)(i0 + u) * d.m, mo[u]);
-                    ldv<V>(a.upd.param + tile_off + (int64_t)(i0 + u) * d.m, pa[u]);
+        for (int i0 = 0; i0 < RT; i0 += CG) {
+            if (i0 >= nrows) break;   // uniform: strips of small sets are a third as tall
+            const int b = (i0 / CG) & 1;
+            if (i0 + CG < RT) request(i0 + CG, mo[b ^ 1], pa[b ^ 1]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < CG; ++u) {
+                const int i = i0 + u;
+                float dl[V], en[V];
+#pragma unroll
+                for (int x = 0; x < V; ++x) dl[x] = 0.f;
+#pragma unroll
+                for (int k = 0; k < R; ++k) {
+                    const float pk = lane_bcast(pr[k], i);
+#pragma unroll
+                    for (int x = 0; x < V; ++x) dl[x] = fmaf(pk, qb[x][k], dl[x]);
                 }
-        }
 #pragma unroll
-        for (int u = 0; u < CG; ++u) {
-            const int i = i0 + u;
-            if (i < RT && i < nrows) {
+                for (int x = 0; x < V; ++x) en[x] = M[i][x] - dl[x];
+                momentum_step<V>(mo[b][u], pa[b][u], dl, a.upd.lr, a.upd.lam);
+                const unsigned off = coff + (unsigned)i * (unsigned)d.m * 4u;
+                buf_stv<V>(eres, off, en);
+                buf_stv<V>(mres, off, mo[b][u], UPD == 2);
+                buf_stv<V>(xres, off, pa[b][u], UPD == 2);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+            if (i < nrows) {
                 float pk[R];
 #pragma unroll
                 for (int k = 0; k < R; ++k) pk[k] = lane_bcast(pr[k], i);
@@ -469,16 +510,10 @@ __device__ __forceinline__ void resident_body(const ResArgs& a, const RTile& t, 
 #pragma unroll
                         for (int k = 0; k < R; ++k) s = fmaf(pk[k], qb[x][k], s);
                         dl[x] = s;
-                        en[x] = M[i < RT ? i : 0][x] - s;
+                        en[x] = M[i][x] - s;
                     }
                     stv<V>(a.err + tile_off + (int64_t)i * d.m, en);
-                    if constexpr (UPD) {
-                        momentum_step<V>(mo[u], pa[u], dl, a.upd.lr, a.upd.lam);
-                        stv<V>(a.upd.mom + tile_off + (int64_t)i * d.m, mo[u]);
-                        stv<V>(a.upd.param + tile_off + (int64_t)i * d.m, pa[u]);
-                    } else {
-                        stv_stream<V>(a.out + tile_off + (int64_t)i * d.m, dl);   // written once: around the caches, which keep e
-                    }
+                    stv_stream<V>(a.out + tile_off + (int64_t)i * d.m, dl);   // written once: around the caches, which keep e
                 }
             }
         }
@@ -500,7 +535,7 @@ __device__ __forceinline__ void resident_body(const ResArgs& a, const RTile& t, 
     trace_mark(a, 6);
 }
 
-template <int R, bool UPD, bool ITER, int RT>
+template <int R, int UPD, bool ITER, int RT>
 __global__ __launch_bounds__(kBlock, 2) void k_resident(ResArgs a) {
     __shared__ float lds[kWavesPerBlock * 4 * R * kWave];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -534,19 +569,22 @@ template <int R, int RT>
 static hipError_t launch_k_resident_rt(const ResArgs& a, int blocks, hipStream_t s, int* max_blocks_per_cu) {
     if (max_blocks_per_cu) {
         // every variant must be co-resident
-        int occ[3] = {0, 0, 0};
-        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ[0], k_resident<R, false, false, RT>, kBlock, 0);
+        int occ[4] = {0, 0, 0, 0};
+        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ[0], k_resident<R, 0, false, RT>, kBlock, 0);
         if (e != hipSuccess) return e;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ[1], k_resident<R, true, false, RT>, kBlock, 0);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ[1], k_resident<R, 1, false, RT>, kBlock, 0);
         if (e != hipSuccess) return e;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ[2], k_resident<R, false, true, RT>, kBlock, 0);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ[2], k_resident<R, 0, true, RT>, kBlock, 0);
         if (e != hipSuccess) return e;
-        *max_blocks_per_cu = std::min(occ[0], std::min(occ[1], occ[2]));
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ[3], k_resident<R, 2, false, RT>, kBlock, 0);
+        if (e != hipSuccess) return e;
+        *max_blocks_per_cu = std::min(std::min(occ[0], occ[1]), std::min(occ[2], occ[3]));
         return hipSuccess;
     }
-    if (a.upd.mom) hipLaunchKernelGGL((k_resident<R, true, false, RT>), dim3((unsigned)blocks), dim3(kBlock), 0, s, a);
-    else if (a.iters > 1) hipLaunchKernelGGL((k_resident<R, false, true, RT>), dim3((unsigned)blocks), dim3(kBlock), 0, s, a);
-    else hipLaunchKernelGGL((k_resident<R, false, false, RT>), dim3((unsigned)blocks), dim3(kBlock), 0, s, a);
+    if (a.upd.mom && a.update_around) hipLaunchKernelGGL((k_resident<R, 2, false, RT>), dim3((unsigned)blocks), dim3(kBlock), 0, s, a);
+    else if (a.upd.mom) hipLaunchKernelGGL((k_resident<R, 1, false, RT>), dim3((unsigned)blocks), dim3(kBlock), 0, s, a);
+    else if (a.iters > 1) hipLaunchKernelGGL((k_resident<R, 0, true, RT>), dim3((unsigned)blocks), dim3(kBlock), 0, s, a);
+    else hipLaunchKernelGGL((k_resident<R, 0, false, RT>), dim3((unsigned)blocks), dim3(kBlock), 0, s, a);
     return hipGetLastError();
 }
 
@@ -613,6 +651,7 @@ psgd_status launch_resident_step(psgd_plan* plan, const void* grad, float* err, 
     hipStream_t s = static_cast<hipStream_t>(stream);
     ResArgs a{};
     a.upd = upd;
+    a.update_around = plan->tuning.stream_hints < 0 && plan->sizes.n_mat_elems >= kResAroundElems ? 1 : 0;
     a.mats = plan->dev.res_mats;
     a.tiles = plan->dev.res_tiles;
     a.grad = static_cast<const float*>(grad);
