@@ -156,7 +156,9 @@ PSGD_API psgd_status psgd_plan_offsets(const psgd_plan* plan, int32_t tensor, in
  *   one_sweep     streaming kernels, rank <= 4, where gram_fused holds: P = M Q and Q = M^T P_hat in one walk over M instead of
  *                 two (psgd_plan_one_sweep); -1 (default) wherever every row fits one workgroup's registers (6144 elements, 4096
  *                 with several workers, 3072 of even and 4096 of odd lengths) and the partial sums 64 MiB, unless another key asks
- *                 for kernels of the two walks (k1_*, k3_*, ortho_rows, worker_mean, gram_fused = 0, 1 or 2), 0 never, 1 also then
+ *                 for kernels of the two walks (k1_*, k3_*, ortho_rows, worker_mean, gram_fused = 0, 1 or 2), 0 never, 1 also then.
+ *                 Matrix-core kernels at rank 4, one worker, bf16 gradients, M above 320 MB and rows of at most 8192 elements: psgd_step
+ *                 the same way unless bf16_valu or an hr_* key is set (1: also then and on smaller sets)
  *   worker_mean   streaming kernels, where gram_fused holds: products of the mean over the workers' M instead of each
  *                 worker's own; -1 (default) from four workers and 2^20 elements on (2^16 per worker above sixteen workers) when
  *                 the rows of 15 in 16 elements are multiples of 4, 0 never, 1 with any two workers
@@ -204,7 +206,9 @@ PSGD_API psgd_status psgd_decompress(psgd_plan* plan, const float* p, const floa
  * M = g + e on chip for the whole step, so each element is read and written
  * once.  Its sums run in another (fixed) order than the split calls, so the
  * two agree to rounding, not bit for bit; each is reproducible from run to
- * run.  Otherwise psgd_step is exactly the two calls in sequence.  Resident
+ * run.  The same holds for the matrix-core plans that one_sweep names; their
+ * psgd_step uses out as scratch before it is written.  Otherwise psgd_step is
+ * exactly the two calls in sequence.  Resident
  * mode, and the one-launch orthogonalisation over row blocks (tuning key
  * gram_fused), keep hand-over words in plan-owned device memory: do not run
  * two calls of the same plan concurrently on different streams.  Both are
@@ -379,7 +383,8 @@ PSGD_API psgd_status psgd_plan_worker_mean(const psgd_plan* plan, int32_t* taken
  * psgd_sizes counts.  Before the plan's first GPU call both are the planner's choice, after it what holds: 0 and 0 where the
  * device does not hold the one-launch orthogonalisation or the memory could not be had.  With several workers the products are
  * then of the mean over the workers (psgd_plan_worker_mean says 1, and 0 bytes).  A plan in resident mode uses it in
- * psgd_compress and psgd_iterate.  Either output may be NULL; PSGD_EINVAL for a NULL plan. */
+ * psgd_compress and psgd_iterate, a matrix-core plan in psgd_step alone (with 0 bytes held, and as the two calls where out is not
+ * aligned to 16 bytes or overlaps grad).  Either output may be NULL; PSGD_EINVAL for a NULL plan. */
 PSGD_API psgd_status psgd_plan_one_sweep(const psgd_plan* plan, int32_t* taken, int64_t* bytes);
 
 /* Static, never NULL. */

@@ -629,12 +629,14 @@ __device__ __forceinline__ void buf_store_out4(buf_rsrc r, unsigned off, v4f v) 
 
 // OM: what becomes of Delta': 0 stored as fp32, 1 stored as bf16, 2 not stored but folded into the momentum and
 // parameter buffers (Algorithm 2's last two lines)
-template <int NT, int OM, bool STREAM>
+// G: e still holds the error memory and M = g + e is formed here, from bf16 gradients (k_one_sweep_wide)
+template <int NT, int OM, bool STREAM, bool G = false>
 __global__ __launch_bounds__(kBlock, 2) void k_hr_decomp(const MatDesc* __restrict__ mats, const Tile* __restrict__ tiles,
                                                          float* __restrict__ err, const float* __restrict__ p,
                                                          const float* __restrict__ q, void* __restrict__ out,
-                                                         int64_t estride, UpdateArgs upd) {
+                                                         int64_t estride, UpdateArgs upd, const void* __restrict__ grad) {
     constexpr bool BF = OM == 1;
+    typedef typename grad4<true>::raw graw_t;
     constexpr bool UPD = OM == 2;
     constexpr int KK = 4 * NT;   // instructions per 16 x 16 block (K = 16 NT in steps of 4)
     constexpr int CB = kHrDecompBlocks;
@@ -685,6 +687,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_hr_decomp(const MatDesc* __restri
     const buf_rsrc mres = make_rsrc(UPD ? upd.mom + d.off + ebase : nullptr, (UPD && w == 0) ? (int64_t)rn * m * 4 : 0);
     const buf_rsrc xres = make_rsrc(UPD ? upd.param + d.off + ebase : nullptr, (UPD && w == 0) ? (int64_t)rn * m * 4 : 0);
     const buf_rsrc pres = make_rsrc(p + d.p_off + (int64_t)r_begin * ri, (int64_t)rn * ri * 4);
+    const buf_rsrc gres = make_rsrc(G ? static_cast<const char*>(grad) + (d.off + ebase) * 2 : nullptr, G ? (int64_t)rn * m * 2 : 0);   // one worker
     // lane offsets in elements, relative to the first row of the strip; out of range where the column (of M) or
     // the rank index (of P_hat) does not exist
     const int h = lane >> 5, j = lane & 31;
@@ -701,26 +704,34 @@ __global__ __launch_bounds__(kBlock, 2) void k_hr_decomp(const MatDesc* __restri
     auto e_off = [&](int i, int step_el, int bytes) -> unsigned {
         return eo == kOutOfRange ? kOutOfRange : (eo + (unsigned)(2 * i * m) + (unsigned)step_el) * (unsigned)bytes;
     };
-    auto load_step = [&](int r_rel, v4f (&mv)[CB], float (&bp)[KK]) {
+    auto load_step = [&](int r_rel, v4f (&mv)[CB], graw_t (&gv)[G ? CB : 1], float (&bp)[KK]) {
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk)
             bp[kk] = buf_load_f32(pres, po[kk] == kOutOfRange ? kOutOfRange : (po[kk] + (unsigned)(r_rel * ri)) * 4u);
 #pragma unroll
         for (int i = 0; i < CB; ++i) mv[i] = buf_load_v4f_policy<AUX>(eres, e_off(i, r_rel * m, 4));
+        if constexpr (G) {
+#pragma unroll
+            for (int i = 0; i < CB; ++i) gv[i] = buf_load_grad4_raw<true>(gres, e_off(i, r_rel * m, 2));
+        }
     };
 
     float (*dt)[kHrDecompStride] = Ds[wave];
     v4f mvn[CB];
+    graw_t gvn[G ? CB : 1];
     float bpn[KK];
-    load_step(0, mvn, bpn);
+    load_step(0, mvn, gvn, bpn);
     for (int r_rel = 0; r_rel < rn; r_rel += 16) {
         v4f mv[CB];
         float bp[KK];
 #pragma unroll
-        for (int i = 0; i < CB; ++i) mv[i] = mvn[i];
+        for (int i = 0; i < CB; ++i) {
+            if constexpr (G) mv[i] = grad4_widen(gvn[i]) + mvn[i];
+            else mv[i] = mvn[i];
+        }
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) bp[kk] = bpn[kk];
-        load_step(r_rel + 16, mvn, bpn);   // past the strip's last row: out of range, nothing is fetched
+        load_step(r_rel + 16, mvn, gvn, bpn);   // past the strip's last row: out of range, nothing is fetched
         // at two and four rank tiles the Q operands are fetched from LDS at every step instead of being kept
         // in registers for the whole strip (64 or 128 of them)
         v4f mo[UPD ? CB : 1], pa[UPD ? CB : 1];
@@ -832,11 +843,22 @@ static void hr_launch_right(psgd_plan* plan, const void* grad, float* err, const
 
 template <int NT>
 static void hr_launch_decomp(psgd_plan* plan, float* err, const float* p, const float* q, void* out, hipStream_t s,
-                             const UpdateArgs& upd) {
+                             const UpdateArgs& upd, const void* grad, bool add_g) {
     dim3 grid((unsigned)plan->hr_tiles4.size(), (unsigned)plan->workers);
 #define HR_DECOMP(OMV, STREAMV)                                                                                                \
     hipLaunchKernelGGL((k_hr_decomp<NT, OMV, STREAMV>), grid, dim3(kBlock), 0, s, plan->dev.mats, plan->dev.hr_tiles4, err, p, q, \
-                       out, plan->sizes.err_stride, upd)
+                       out, plan->sizes.err_stride, upd, grad)
+    if constexpr (NT == 1) {
+        if (add_g) {   // k_one_sweep_wide: one worker, a set beyond the memory-side cache, no update
+#define HR_DECOMP_G(OMV)                                                                                                         \
+    hipLaunchKernelGGL((k_hr_decomp<1, OMV, true, true>), grid, dim3(kBlock), 0, s, plan->dev.mats, plan->dev.hr_tiles4, err, p, q, \
+                       out, plan->sizes.err_stride, upd, grad)
+            if (plan->out_dtype == PSGD_BF16) HR_DECOMP_G(1);
+            else HR_DECOMP_G(0);
+#undef HR_DECOMP_G
+            return;
+        }
+    }
     if (plan->stream_hints) {
         if (upd.mom) HR_DECOMP(2, true);
         else if (plan->out_dtype == PSGD_BF16) HR_DECOMP(1, true);
@@ -939,20 +961,40 @@ psgd_status launch_vector_mean(psgd_plan* plan, const void* grad, void* out, voi
 }
 
 psgd_status hr_decompress(psgd_plan* plan, const float* p, const float* q, float* err, const void* grad, void* out,
-                          void* stream, const UpdateArgs& upd) {
+                          void* stream, const UpdateArgs& upd, bool add_g) {
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int nt = plan->hr_nt;
     HR_MARK(5);
     if (!plan->hr_tiles4.empty()) {
-        if (nt == 1) hr_launch_decomp<1>(plan, err, p, q, out, s, upd);
-        else if (nt == 2) hr_launch_decomp<2>(plan, err, p, q, out, s, upd);
-        else hr_launch_decomp<4>(plan, err, p, q, out, s, upd);
+        if (nt == 1) hr_launch_decomp<1>(plan, err, p, q, out, s, upd, grad, add_g);
+        else if (nt == 2) hr_launch_decomp<2>(plan, err, p, q, out, s, upd, grad, add_g);
+        else hr_launch_decomp<4>(plan, err, p, q, out, s, upd, grad, add_g);
         HR_CHECK("launch k_hr_decomp");
     }
     psgd_status vs = launch_vector_mean(plan, grad, out, stream, upd);
     if (vs != PSGD_OK) return vs;
     HR_MARK(6);
     return finish_profiled_step(plan);
+}
+
+// psgd_step in one walk that leaves e alone, then the decompression of g + e; out is scratch until the latter writes it
+psgd_status hr_step_wide(psgd_plan* plan, const void* grad, float* err, float* q, float* p, void* out, void* workspace, void* stream) {
+    if (!plan->uploaded) {
+        psgd_status st = upload_tables(plan);
+        if (st != PSGD_OK) return st;
+    }
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    HR_MARK(0);
+    plan->compress_marked = plan->profiling;
+    double* spart = static_cast<double*>(out);
+    double* gpart = static_cast<double*>(workspace);
+    psgd_status st = launch_one_sweep_wide(plan, grad, err, q, p, spart, gpart, stream);
+    if (st != PSGD_OK) return st;
+    HR_MARK(1);
+    st = launch_solve(plan, q, p, spart, gpart, stream);
+    if (st != PSGD_OK) return st;
+    for (int i = 2; i <= 4; ++i) HR_MARK(i);
+    return hr_decompress(plan, p, q, err, grad, out, stream, UpdateArgs(), true);
 }
 
 }  // namespace psgd

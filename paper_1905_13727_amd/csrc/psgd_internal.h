@@ -124,6 +124,11 @@ constexpr int64_t kOneMaxBytes = int64_t(64) << 20;   // plan-owned partial sums
 // row, three steps 78.  24 matrices, three workers, two iterations: 8 / 6 / 8 columns, two steps 182 us a pass, 12 and one step 196.
 constexpr int one_nv(int v, bool mean) { return (v == 1 ? 8 : (!mean ? 12 : (v == 2 ? 6 : 8))) / v; }
 constexpr int one_depth(int r, bool mean) { return mean || r <= 2 ? 2 : 1; }
+// k_one_sweep_wide: column vectors (of four) a lane owns, rows whose loads are in flight, and shared memory: Q of a row as floats, after it
+// one column vector's sums of every lane
+constexpr int kOneWideNV = 4, kOneWideDepth = 2;
+constexpr int kOneWideLds = kOneMaxWaves * kWave * kOneWideNV * 4 * kOneMaxRank * 4;
+static_assert(4 * kOneMaxRank * (kOneMaxWaves * kWave + 1) * 8 <= kOneWideLds, "the sums fit where Q was");
 // floats of Q a lane needs, in sets of four
 constexpr int one_q_floats(int r, int v, bool mean) { return (one_nv(v, mean) * v * r + 3) / 4 * 4; }
 // column vectors of a lane whose sums are added over the workgroup's groups at a time (at most 16 doubles a lane)
@@ -266,6 +271,7 @@ struct psgd_plan {
     psgd::Tuning tuning;
     // one walk over M per iteration
     bool one_sweep = false;                 // taken (after the upload: the partial sums' memory is there)
+    bool one_wide = false;                  // matrix-core plans: psgd_step's own walk (k_one_sweep_wide)
     int32_t one_waves = 0;                  // wavefronts of a workgroup
     int32_t one_lds_bytes = 0;
     int64_t one_s_doubles = 0, one_bytes = 0;   // partial S, and partial S and Gram matrices: plan-owned
@@ -324,7 +330,10 @@ psgd_status launch_decompress(psgd_plan* plan, const float* p, const float* q, f
                               const UpdateArgs& upd = UpdateArgs());
 // P and the partial S and Gram matrices, then P_hat and Q from them (one walk over M)
 psgd_status launch_one_sweep(psgd_plan* plan, const void* grad, float* err, const float* q, float* p, void* stream, bool add);
-psgd_status launch_solve(psgd_plan* plan, float* q, float* p, void* stream);
+psgd_status launch_solve(psgd_plan* plan, float* q, float* p, const double* spart, const double* gpart, void* stream);
+psgd_status launch_one_sweep_wide(psgd_plan* plan, const void* grad, float* err, const float* q, float* p, double* spart, double* gpart,
+                                  void* stream);
+psgd_status hr_step_wide(psgd_plan* plan, const void* grad, float* err, float* q, float* p, void* out, void* workspace, void* stream);
 psgd_status one_sweep_prepare(psgd_plan* plan);   // once per plan, at the upload
 psgd_status set_profiling(psgd_plan* plan, bool enable);
 // workers: those that have partial Q of their own
@@ -333,7 +342,7 @@ psgd_status finish_profiled_step(psgd_plan* plan);
 psgd_status hr_compress(psgd_plan* plan, const void* grad, float* err, float* q, float* p, void* workspace,
                         void* stream, bool add);
 psgd_status hr_decompress(psgd_plan* plan, const float* p, const float* q, float* err, const void* grad, void* out,
-                          void* stream, const UpdateArgs& upd);
+                          void* stream, const UpdateArgs& upd, bool add_g = false);
 psgd_status launch_vector_mean(psgd_plan* plan, const void* grad, void* out, void* stream, const UpdateArgs& upd);
 psgd_status check_plan(psgd_plan* plan, void* stream);
 psgd_status static_workspace(psgd_plan* plan, void** ws);

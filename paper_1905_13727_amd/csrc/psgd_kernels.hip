@@ -1287,6 +1287,13 @@ psgd_status upload_tables(psgd_plan* plan) {
             }
         }
     }
+    if (plan->one_wide) {
+        psgd_status st = one_sweep_prepare(plan);
+        if (st != PSGD_OK) {
+            free_tables(plan);
+            return st;
+        }
+    }
     // the mean over the workers of M; without it every worker's M is multiplied by itself
     if (plan->mean_first && !plan->hr && !plan->one_sweep && plan->gram_fused &&
         hipMalloc(reinterpret_cast<void**>(&plan->mbar), (size_t)plan->sizes.n_mat_elems * sizeof(float)) != hipSuccess) {
@@ -1514,7 +1521,7 @@ psgd_status launch_compress(psgd_plan* plan, const void* grad, float* err, float
         st = launch_one_sweep(plan, g, err, q, p, stream, add);
         if (st != PSGD_OK) return st;
         PSGD_MARK(1);
-        st = launch_solve(plan, q, p, stream);
+        st = launch_solve(plan, q, p, plan->one_part, plan->one_part + plan->one_s_doubles, stream);
         if (st != PSGD_OK) return st;
         for (int i = 2; i <= 4; ++i) PSGD_MARK(i);   // no second walk, no reduction of Q
         return PSGD_OK;

@@ -52,17 +52,27 @@ __device__ __forceinline__ float graw_at(const graw<V, BF>& g, int x) {
 
 constexpr int pow2_at_least(int n) { return n <= 1 ? 1 : 2 * pow2_at_least((n + 1) / 2); }
 
-// N <= 8 sums over the 64 lanes at once: lane l < N returns the sum of x[l] (lane_sums is the one for more).  The values are handed
+__device__ __forceinline__ float lane_read(float v, int src_lane) {
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(src_lane << 2, __float_as_int(v)));
+}
+__device__ __forceinline__ double lane_read(double v, int src_lane) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_ds_bpermute(src_lane << 2, (int)(b & 0xffffffffLL));
+    const int hi = __builtin_amdgcn_ds_bpermute(src_lane << 2, (int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// N <= 8 sums over the 64 lanes at once, in float or double: lane l < N returns the sum of x[l] (lane_sums is the one for more).  The values are handed
 // over in halves between partners whose lane bit differs; the lane bits that chose nothing are added up afterwards.
-template <int N>
-__device__ __forceinline__ float few_lane_sums(const float (&x)[N]) {
+template <int N, typename T>
+__device__ __forceinline__ T few_lane_sums(const T (&x)[N]) {
     static_assert(N >= 1 && N <= 8, "one result per lane of eight");
     constexpr int NP = pow2_at_least(N);
     const int lane = threadIdx.x & (kWave - 1);
     const bool b2 = (lane & 4) != 0, b1 = (lane & 2) != 0, b0 = (lane & 1) != 0;
-    float a[NP];
+    T a[NP];
 #pragma unroll
-    for (int j = 0; j < NP; ++j) a[j] = j < N ? x[j] : 0.f;
+    for (int j = 0; j < NP; ++j) a[j] = j < N ? x[j] : T(0);
     if constexpr (NP >= 8) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) a[j] = (b2 ? a[j + 4] : a[j]) + dpp_mov<0x141>(b2 ? a[j] : a[j + 4]);   // row_half_mirror
@@ -71,14 +81,14 @@ __device__ __forceinline__ float few_lane_sums(const float (&x)[N]) {
 #pragma unroll
         for (int j = 0; j < 2; ++j) a[j] = (b1 ? a[j + 2] : a[j]) + dpp_mov<0x1B>(b1 ? a[j] : a[j + 2]);    // quad_perm [3,2,1,0]
     }
-    float v = a[0];
+    T v = a[0];
     if constexpr (NP >= 2) v = (b0 ? a[1] : a[0]) + dpp_mov<0xB1>(b0 ? a[0] : a[1]);                        // quad_perm [1,0,3,2]
     if constexpr (NP < 2) v += dpp_mov<0xB1>(v);
     if constexpr (NP < 4) v += dpp_mov<0x4E>(v);    // quad_perm [2,3,0,1]
     v += dpp_mov<0x128>(v);                         // row_ror:8
     if constexpr (NP < 8) v += dpp_mov<0x124>(v);   // row_ror:4
-    v += __int_as_float(__builtin_amdgcn_ds_bpermute((lane ^ 16) << 2, __float_as_int(v)));
-    return v + __int_as_float(__builtin_amdgcn_ds_bpermute((lane ^ 32) << 2, __float_as_int(v)));
+    v += lane_read(v, lane ^ 16);
+    return v + lane_read(v, lane ^ 32);
 }
 
 // LDS written by this wavefront is read by others after it; global loads stay in flight across it
@@ -103,14 +113,15 @@ extern __shared__ __attribute__((aligned(16))) char one_lds[];
 // memory-side cache (LSTM-shaped set, 4 workers: the step 632 -> 675 us); leaving M unstored and forming g + e again in the
 // decompression (159 -> 192).
 // ADD = false: M is read from e (another iteration), nothing is added or stored.  MEAN: several workers, products of their mean.
-template <int R, int V, bool ADD, bool GBF, bool STORE, bool MEAN>
+// PT: the type the products are summed in (float; double where the rows are so long and the lanes' chains with them that rounding shows).
+template <int R, int V, int NV, int RS, int D, typename PT, bool ADD, bool GBF, bool STORE, bool MEAN>
 __device__ __forceinline__ void one_sweep_tile(const OneTile& t, const OneMat& d, const void* __restrict__ grad,
                                                float* __restrict__ err, const float* __restrict__ q, float* __restrict__ p,
                                                double* __restrict__ spart, double* __restrict__ gpart, int workers,
-                                               int64_t gstride, int64_t estride, float (*xsum)[kOneMaxWaves][kOneRows * kOneMaxRank],
+                                               int64_t gstride, int64_t estride, PT (*xsum)[kOneMaxWaves][kOneRows * kOneMaxRank],
                                                double (*xgram)[R * (R + 1) / 2]) {
     constexpr unsigned GS = GBF ? 2u : 4u;
-    constexpr int NV = one_nv(V, MEAN), NC = NV * V, RS = kOneRows, N = RS * R, D = one_depth(R, MEAN);
+    constexpr int NC = NV * V, N = RS * R;
     constexpr int NG = R * (R + 1) / 2;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -128,11 +139,10 @@ __device__ __forceinline__ void one_sweep_tile(const OneTile& t, const OneMat& d
 
     // A descriptor per row, built with scalar instructions: columns past the row's end are out of range (zeros are read, stores
     // dropped), a row past the strip has an empty range; the lanes' offsets never change.
-    unsigned coff[NV], goff[NV];
+    unsigned coff[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
         coff[v] = (unsigned)((gl + glanes * v) * V) * 4u;
-        goff[v] = (unsigned)((gl + glanes * v) * V) * GS;
     }
     const int64_t strip = d.off + (int64_t)row0 * m;
     const int nw = MEAN ? workers : 1;
@@ -146,7 +156,7 @@ __device__ __forceinline__ void one_sweep_tile(const OneTile& t, const OneMat& d
                 const int row = step * RS + i;
                 const buf_rsrc gg = make_rsrc(static_cast<const char*>(grad) + ((int64_t)w * gstride + strip + (int64_t)row * m) * GS, row < rn ? (int64_t)m * GS : 0);
 #pragma unroll
-                for (int v = 0; v < NV; ++v) ld_graw<V, GBF>(gg, goff[v], g[i][v]);
+                for (int v = 0; v < NV; ++v) ld_graw<V, GBF>(gg, coff[v] * GS / 4u, g[i][v]);
             }
         }
 #pragma unroll
@@ -167,12 +177,12 @@ __device__ __forceinline__ void one_sweep_tile(const OneTile& t, const OneMat& d
 #pragma unroll
             for (int k = 0; k < R; ++k) S[v][x][k] = 0.0;
     double gsum = 0.0;
-    int ga = 0, gb = 0;   // this lane's pair of columns of the Gram matrix: a <= b
+    int gab = 0;   // this lane's pair of columns a <= b of the Gram matrix: a + 16 b
     {
         int l = lane < NG ? lane : 0;
 #pragma unroll
         for (int a = 0; a < R; ++a) {
-            if (l >= 0 && l < R - a) { ga = a; gb = a + l; }
+            if (l >= 0 && l < R - a) gab = a + 16 * (a + l);
             l -= R - a;
         }
     }
@@ -191,7 +201,9 @@ __device__ __forceinline__ void one_sweep_tile(const OneTile& t, const OneMat& d
     }
     // Q of the whole row, four floats of a lane's NC * R together, lane by lane (past NC * R: not read)
     float* qs = reinterpret_cast<float*>(one_lds);
-    auto q_at = [&](int c) { return ((c >> 2) * glanes + gl) * 4 + (c & 3); };
+    // (sizeof(PT) == 8: at a distance known when compiling, which an instruction's offset holds; else 16 addresses in registers)
+    const int qdist = sizeof(PT) == 8 ? kOneMaxWaves * kWave : glanes;
+    auto q_at = [&](int c) { return ((c >> 2) * qdist + gl) * 4 + (c & 3); };
     for (int v = group; v < NV; v += ngroups) {
         float f[V][R];
         const int jv = gl + glanes * v;
@@ -213,28 +225,33 @@ __device__ __forceinline__ void one_sweep_tile(const OneTile& t, const OneMat& d
                 for (int x = 0; x < V; ++x) M[i][v][x] = 0.f;
     }
     auto multiply = [&](int step) {
+        int ln = lane;
+        if constexpr (sizeof(PT) == 8) asm volatile("" : "+v"(ln));   // addresses are formed anew in every step, not held in registers
         // P of the step's rows, two chains per product and lane
-        constexpr int CH = V >= 2 ? 2 : 1;
-        float dot[RS][R][CH];
+        constexpr int CH = sizeof(PT) == 4 && V >= 2 ? 2 : 1;
+        PT dot[RS][R][CH];
 #pragma unroll
         for (int i = 0; i < RS; ++i)
 #pragma unroll
             for (int k = 0; k < R; ++k)
 #pragma unroll
-                for (int x = 0; x < CH; ++x) dot[i][k][x] = 0.f;
+                for (int x = 0; x < CH; ++x) dot[i][k][x] = PT(0);
 #pragma unroll
-        for (int c4 = 0; c4 < one_q_floats(R, V, MEAN) / 4; ++c4) {
-            if (c4 % 3 == 0) asm volatile("" ::: "memory");   // Q is fetched from LDS a little at a time, in every step anew (registers)
-            const f4 q4 = *reinterpret_cast<const f4*>(qs + (c4 * glanes + gl) * 4);
+        for (int c4 = 0; c4 < (NC * R + 3) / 4; ++c4) {
+            if constexpr (sizeof(PT) == 8) {   // nor is M widened ahead of its products
+                asm volatile("" : "+v"(M[0][4 * c4 / (R * V)][4 * c4 / R % V]));
+            }
+            if (c4 % (sizeof(PT) == 8 ? 2 : 3) == 0) asm volatile("" ::: "memory");   // Q is fetched from LDS a little at a time, in every step anew (registers)
+            const f4 q4 = *reinterpret_cast<const f4*>(qs + (c4 * qdist + gl) * 4);
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int c = 4 * c4 + u, k = c % R, x = c / R % V, v = c / (R * V);
                 if (c >= NC * R) continue;
 #pragma unroll
-                for (int i = 0; i < RS; ++i) dot[i][k][x % CH] = fmaf(M[i][v][x], q4[u], dot[i][k][x % CH]);
+                for (int i = 0; i < RS; ++i) dot[i][k][x % CH] = fma((PT)M[i][v][x], (PT)q4[u], dot[i][k][x % CH]);
             }
         }
-        float part[N];
+        PT part[N];
 #pragma unroll
         for (int i = 0; i < RS; ++i)
 #pragma unroll
@@ -242,24 +259,32 @@ __device__ __forceinline__ void one_sweep_tile(const OneTile& t, const OneMat& d
                 if constexpr (CH == 2) part[i * R + k] = dot[i][k][0] + dot[i][k][1];
                 else part[i * R + k] = dot[i][k][0];
             }
-        float sum = few_lane_sums<N>(part);
+        PT sum = few_lane_sums<N>(part);
         if (per_row > 1) {
-            if (lane < N) xsum[step & 1][wave][lane] = sum;
+            if (ln < N) xsum[step & 1][wave][ln] = sum;
             lds_barrier();
-            sum = 0.f;
-            if (lane < N)
-                for (int u = 0; u < per_row; ++u) sum += xsum[step & 1][(group << sh) + u][lane];
+            sum = PT(0);
+            if (ln < N)
+                for (int u = 0; u < per_row; ++u) sum += xsum[step & 1][(group << sh) + u][ln];
         }
-        const float pf = sum;   // lane i * R + k: row i, rank k
+        const float pf = (float)sum;   // lane i * R + k: row i, rank k
         {
-            const int li = lane / R, lk = lane % R, row = step * RS + li;
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(pf), pres, lane < N && lk < ri ? (int)((row * ri + lk) * 4) : (int)kOutOfRange, 0, 0);
+            const int li = ln / R, lk = ln % R, row = step * RS + li;
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(pf), pres, ln < N && lk < ri ? (int)((row * ri + lk) * 4) : (int)kOutOfRange, 0, 0);
 #pragma unroll
             for (int i = 0; i < RS; ++i) {
-                const float pa = __int_as_float(__builtin_amdgcn_ds_bpermute((i * R + ga) << 2, __float_as_int(pf)));
-                const float pb = __int_as_float(__builtin_amdgcn_ds_bpermute((i * R + gb) << 2, __float_as_int(pf)));
+                const float pa = __int_as_float(__builtin_amdgcn_ds_bpermute((i * R + (gab & 15)) << 2, __float_as_int(pf)));
+                const float pb = __int_as_float(__builtin_amdgcn_ds_bpermute((i * R + (gab >> 4)) << 2, __float_as_int(pf)));
                 gsum = fma((double)pa, (double)pb, gsum);
             }
+        }
+        if constexpr (sizeof(PT) == 8) {   // M is widened again below, not kept in both widths
+#pragma unroll
+            for (int i = 0; i < RS; ++i)
+#pragma unroll
+                for (int v = 0; v < NV; ++v)
+#pragma unroll
+                    for (int x = 0; x < V; ++x) asm volatile("" : "+v"(M[i][v][x]));
         }
 #pragma unroll
         for (int i = 0; i < RS; ++i) {
@@ -273,6 +298,7 @@ __device__ __forceinline__ void one_sweep_tile(const OneTile& t, const OneMat& d
                     const double md = (double)M[i][v][x];
 #pragma unroll
                     for (int k = 0; k < R; ++k) S[v][x][k] = fma(md, pd[k], S[v][x][k]);
+                    if constexpr (sizeof(PT) == 8) __builtin_amdgcn_sched_barrier(0);
                 }
         }
     };
@@ -327,7 +353,7 @@ __device__ __forceinline__ void one_sweep_tile(const OneTile& t, const OneMat& d
     double* sdst = spart + d.s_off + (int64_t)t.block * m * ri;
     double* gdst = gpart + d.g_off + (int64_t)t.block * NG;
     constexpr int C = V * R;   // doubles of one column vector
-    constexpr int VG = one_deposit(R, V, MEAN);
+    constexpr int VG = NV == one_nv(V, MEAN) ? one_deposit(R, V, MEAN) : 1;
     const int nthreads = blockDim.x;
     const int stride = nthreads + 1;
     double* gs = reinterpret_cast<double*>(one_lds);   // Q is no longer needed
@@ -370,9 +396,34 @@ __global__ __launch_bounds__(kOneMaxWaves * kWave, 2) void k_one_sweep(const One
     __shared__ double xgram[kOneMaxWaves][R * (R + 1) / 2];
     const OneTile t = tiles[blockIdx.x];
     const OneMat d = mats[t.mat];
-    if (d.vec == 4) one_sweep_tile<R, 4, ADD, GBF, STORE, MEAN>(t, d, grad, err, q, p, spart, gpart, workers, gstride, estride, xsum, xgram);
-    else if (d.vec == 2) one_sweep_tile<R, 2, ADD, GBF, STORE, MEAN>(t, d, grad, err, q, p, spart, gpart, workers, gstride, estride, xsum, xgram);
-    else one_sweep_tile<R, 1, ADD, GBF, STORE, MEAN>(t, d, grad, err, q, p, spart, gpart, workers, gstride, estride, xsum, xgram);
+#define PSGD_ONE_TILE(V)                                                                                                        \
+    one_sweep_tile<R, V, one_nv(V, MEAN), kOneRows, one_depth(R, MEAN), float, ADD, GBF, STORE, MEAN>(                          \
+        t, d, grad, err, q, p, spart, gpart, workers, gstride, estride, xsum, xgram)
+    if (d.vec == 4) PSGD_ONE_TILE(4);
+    else if (d.vec == 2) PSGD_ONE_TILE(2);
+    else PSGD_ONE_TILE(1);
+#undef PSGD_ONE_TILE
+}
+
+// ---- k_one_sweep_wide: rows of up to 8192 elements, bf16 gradients, one worker, M not stored ------------------------------
+//
+// What the sets beyond the memory-side cache take instead of the matrix cores' first two walks: they are bound by bytes, and 18 a step
+// (6 here, 12 in a decompression that forms g + e again) are fewer than 24.  A row takes up to eight wavefronts with 16 columns a
+// lane, whose fp64 sums are half of the registers, so a step is one row, two are in flight (98 KB a compute unit) and one workgroup fills
+// a compute unit.  The products are summed in fp64 as on the matrix cores (error of P against 64 bits 3.7e-8 on either, of Q 1.7e-7 there,
+// 2.6e-8 here).  24-layer transformer-shaped set: 1559 us, 5.0 TB/s.  Every register counts: with 33, 4 and 0 spilled ones, whose
+// reloads wait for all loads before them, it took 3546, 1854 and 1559 us; hence Q at a fixed distance in shared memory, the
+// addresses formed anew and M widened where it is used.
+template <int R>
+__global__ __launch_bounds__(kOneMaxWaves * kWave, 2) void k_one_sweep_wide(const OneMat* __restrict__ mats, const OneTile* __restrict__ tiles,
+                                                                            const void* __restrict__ grad, float* __restrict__ err,
+                                                                            const float* __restrict__ q, float* __restrict__ p,
+                                                                            double* __restrict__ spart, double* __restrict__ gpart) {
+    __shared__ double xsum[2][kOneMaxWaves][kOneRows * kOneMaxRank];
+    __shared__ double xgram[kOneMaxWaves][R * (R + 1) / 2];
+    const OneTile t = tiles[blockIdx.x];
+    const OneMat d = mats[t.mat];
+    one_sweep_tile<R, 4, kOneWideNV, 1, kOneWideDepth, double, true, true, false, false>(t, d, grad, err, q, p, spart, gpart, 1, 0, 0, xsum, xgram);
 }
 
 // ---- k_solve: R from the Gram matrix, P_hat = P R^-1, Q = S R^-1 -------------------------------------------
@@ -541,6 +592,10 @@ static psgd_status one_fail(psgd_plan* plan, hipError_t e, const char* what) {
 }
 
 psgd_status one_sweep_prepare(psgd_plan* plan) {   // more LDS than a workgroup has by default
+    if (plan->one_wide)
+        return one_fail(plan, hipFuncSetAttribute(reinterpret_cast<const void*>(k_one_sweep_wide<kOneMaxRank>),
+                                                  hipFuncAttributeMaxDynamicSharedMemorySize, kOneWideLds),
+                        "shared memory of k_one_sweep_wide");
     hipError_t e = hipSuccess;
     for (bool add : {true, false})
         if (e == hipSuccess)
@@ -563,9 +618,15 @@ psgd_status launch_one_sweep(psgd_plan* plan, const void* grad, float* err, cons
     return one_fail(plan, e, "launch k_one_sweep");
 }
 
-psgd_status launch_solve(psgd_plan* plan, float* q, float* p, void* stream) {
-    const double* spart = plan->one_part;
-    const double* gpart = spart + plan->one_s_doubles;
+psgd_status launch_one_sweep_wide(psgd_plan* plan, const void* grad, float* err, const float* q, float* p, double* spart, double* gpart,
+                                  void* stream) {
+    hipLaunchKernelGGL(k_one_sweep_wide<kOneMaxRank>, dim3((unsigned)plan->one_tiles.size()), dim3(kOneMaxWaves * kWave),
+                       (size_t)plan->one_lds_bytes, static_cast<hipStream_t>(stream), plan->dev.one_mats, plan->dev.one_tiles, grad, err, q,
+                       p, spart, gpart);
+    return one_fail(plan, hipGetLastError(), "launch k_one_sweep_wide");
+}
+
+psgd_status launch_solve(psgd_plan* plan, float* q, float* p, const double* spart, const double* gpart, void* stream) {
 #define PSGD_SOLVE(RR)                                                                                                   \
     case RR:                                                                                                             \
         hipLaunchKernelGGL((k_solve<RR>), dim3((unsigned)plan->solve_tiles.size()), dim3(kBlock), 0,                     \

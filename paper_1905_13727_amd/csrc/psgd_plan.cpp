@@ -139,6 +139,8 @@ static int64_t group_tiles(const psgd_plan* plan) {
 }
 
 
+static void build_one_wide(psgd_plan* plan);
+
 // Matrix-core path: its own tilings and workspace layout.
 static psgd_status build_hr_tables(psgd_plan* plan) {
     const Tuning& tu = plan->tuning;
@@ -240,6 +242,7 @@ static psgd_status build_hr_tables(psgd_plan* plan) {
     order_tiles(plan->hr_tiles1, order);
     order_tiles(plan->hr_tiles3, order);
     order_tiles(plan->hr_tiles4, order);
+    build_one_wide(plan);
     plan->tables_built = true;
     return PSGD_OK;
 }
@@ -277,6 +280,15 @@ static int64_t one_sweep_blocks(const psgd_plan* plan, int waves, int64_t slots,
         largest = std::max(largest, ceil_div(o.n, blocks->back()) * one_row_cost(o, mean));
     }
     return largest;
+}
+
+static void push_solve_tiles(psgd_plan* plan, int32_t mat, const OneMat& o) {
+    // columns of Q per workgroup: fewer, with more threads to a column, where there are many blocks to add
+    const int cl = o.n_blocks >= 16 ? 4 : (o.n_blocks >= 4 ? 6 : 8);
+    for (int64_t c = 0; c < o.m; c += 1 << cl)
+        plan->solve_tiles.push_back({mat, (int32_t)c, (int32_t)std::min<int64_t>(1 << cl, o.m - c), 0, (int16_t)cl});
+    for (int64_t c = 0; c < o.n; c += kBlock)
+        plan->solve_tiles.push_back({mat, (int32_t)c, (int32_t)std::min<int64_t>(kBlock, o.n - c), 1, 8});
 }
 
 // Whether a plan's sets go through one walk over M per iteration instead of two (see k_one_sweep), and its tables.  Ranks up to
@@ -350,17 +362,81 @@ static void build_one_sweep(psgd_plan* plan) {
             even_split(o.n, o.n_blocks, b, &r0, &rn);
             plan->one_tiles.push_back({(int32_t)i, (int32_t)r0, (int32_t)rn, (int32_t)b});
         }
-        // columns of Q per workgroup: fewer, with more threads to a column, where there are many blocks to add
-        const int cl = o.n_blocks >= 16 ? 4 : (o.n_blocks >= 4 ? 6 : 8);
-        for (int64_t c = 0; c < o.m; c += 1 << cl)
-            plan->solve_tiles.push_back({(int32_t)i, (int32_t)c, (int32_t)std::min<int64_t>(1 << cl, o.m - c), 0, (int16_t)cl});
-        for (int64_t c = 0; c < o.n; c += kBlock)
-            plan->solve_tiles.push_back({(int32_t)i, (int32_t)c, (int32_t)std::min<int64_t>(kBlock, o.n - c), 1, 8});
+        push_solve_tiles(plan, (int32_t)i, o);
     }
     plan->one_s_doubles = round_up(sd, 32);
     plan->one_lds_bytes = (int32_t)lds;
     plan->one_bytes = (plan->one_s_doubles + gd) * (int64_t)sizeof(double);
     plan->one_sweep = plan->one_bytes <= kOneMaxBytes;
+}
+
+// psgd_step on a matrix-core plan in one walk over M that stores nothing but P (k_one_sweep_wide): one worker, bf16 gradients, rank 4, a
+// set beyond the memory-side cache, rows of at most 8192 elements.  The partial S lie in `out`, each matrix's within its own region,
+// which the decompression writes afterwards; the partial Gram matrices in the workspace.  24-layer transformer-shaped set, us a step:
+// 5234 on the matrix cores, 4227 this way (k_one_sweep_wide 1559, k_hr_decomp with g added again 2677, where k_hr_right, k_hr_left and
+// k_hr_decomp took 2166, 796 and 2154).  Other sets, before / after: transformers of 77, 91, 127, 138, 203, 216 and 304 M elements 357 / 309,
+// 465 / 398, 706 / 506, 924 / 678, 1083 / 771, 1104 / 894 and 1367 / 1121; 200 matrices of 500 x 1000 678 / 465; 300000 x 300 772 / 563; 21000 x 4096
+// 448 / 382.  Rows that take all eight wavefronts, which then wait for each other at every row, lose where they are all there is (6
+// of 2000 x 8192 470 / 532, 110 of 100 x 8192 417 / 511) and are a third of the transformers': the line is at half of the elements.
+// Above rank 4 a row of 8192 and its S do not fit a compute unit's registers.
+static void build_one_wide(psgd_plan* plan) {
+    plan->one_wide = false;
+    plan->one_mats.clear(); plan->one_tiles.clear(); plan->solve_tiles.clear();
+    const Tuning& tu = plan->tuning;
+    const Tuning def;
+    const int R = plan->rank;
+    // keys that ask for the matrix-core kernels or for their tiles get them
+    const bool others = tu.bf16_valu >= 0 || tu.hr_k1_rows != def.hr_k1_rows || tu.hr_k1_cols != def.hr_k1_cols || tu.hr_k3_rows != def.hr_k3_rows;
+    if (R != kOneMaxRank || plan->workers != 1 || plan->grad_dtype != PSGD_BF16 || plan->mats.empty() || !tu.one_sweep ||
+        (tu.one_sweep < 0 && (others || !plan->stream_hints)))
+        return;
+    const int64_t osz = plan->out_dtype == PSGD_BF16 ? 2 : 4;
+    int64_t total = 0, eight = 0;
+    for (const MatDesc& d : plan->mats) {
+        if (d.m > (int64_t)kOneMaxWaves * kWave * kOneWideNV * 4 || (int64_t)d.n * osz < (int64_t)d.r * (int64_t)sizeof(double)) return;
+        total += (int64_t)d.n * d.m;
+        if (d.m > (int64_t)kOneMaxWaves / 2 * kWave * kOneWideNV * 4) eight += (int64_t)d.n * d.m;
+    }
+    if (eight > total / 2 && tu.one_sweep < 0) return;
+    // Four blocks for every compute unit, dealt largest first: what one block too many costs in the last generation is a quarter of a
+    // compute unit's share, and the partial S (70 MB of the 24-layer set's 26 GB) are little.
+    const int64_t elems = ceil_div(total, (int64_t)kResCUs * 4);
+    int64_t gd = 0;
+    for (size_t i = 0; i < plan->mats.size(); ++i) {
+        const MatDesc& d = plan->mats[i];
+        OneMat o{};
+        o.off = d.off; o.p_off = d.p_off; o.q_off = d.q_off;
+        o.n = d.n; o.m = d.m; o.r = d.r; o.vec = 4;
+        while (((int64_t)kWave << o.waves_log2) * kOneWideNV * 4 < d.m) ++o.waves_log2;
+        const int64_t groups = kOneMaxWaves >> o.waves_log2;
+        const int64_t want = std::max<int64_t>(1, ((int64_t)o.n * o.m + elems / 2) / elems);
+        const int64_t room = (int64_t)d.n * osz / ((int64_t)d.r * (int64_t)sizeof(double));   // blocks whose S the matrix's part of `out` holds
+        o.n_blocks = (int32_t)std::min(std::min(ceil_div(o.n, groups * kOneWideDepth), want), room);
+        o.s_off = d.off * osz / (int64_t)sizeof(double);   // d.off is a multiple of 64 elements
+        o.g_off = gd;
+        gd += (int64_t)o.n_blocks * (R * (R + 1) / 2);
+        for (int64_t b = 0; b < o.n_blocks; ++b) {
+            int64_t r0, rn;
+            even_split(o.n, o.n_blocks, b, &r0, &rn);
+            plan->one_tiles.push_back({(int32_t)i, (int32_t)r0, (int32_t)rn, (int32_t)b});
+        }
+        push_solve_tiles(plan, (int32_t)i, o);
+        plan->one_mats.push_back(o);
+    }
+    std::stable_sort(plan->one_tiles.begin(), plan->one_tiles.end(), [&](const OneTile& a, const OneTile& b) {
+        return (int64_t)a.nrows * plan->one_mats[a.mat].m > (int64_t)b.nrows * plan->one_mats[b.mat].m;
+    });
+    plan->one_waves = kOneMaxWaves;
+    plan->one_lds_bytes = kOneWideLds;
+    plan->one_wide = gd * (int64_t)sizeof(double) <= plan->sizes.workspace_bytes;
+}
+
+// Whether a call's buffers let it: `out` is scratch for fp64 values before it is written, and g is read after that.
+static bool one_wide_call(const psgd_plan* plan, const void* grad, const void* out) {
+    if (!plan->one_wide || reinterpret_cast<uintptr_t>(out) % 16) return false;
+    const char *g = static_cast<const char*>(grad), *o = static_cast<const char*>(out);
+    const int64_t gb = plan->sizes.grad_stride * 2, ob = plan->sizes.out_elems * (plan->out_dtype == PSGD_BF16 ? 2 : 4);
+    return g + gb <= o || o + ob <= g;
 }
 
 psgd_status build_tables(psgd_plan* plan) {
@@ -379,7 +455,7 @@ psgd_status build_tables(psgd_plan* plan) {
             if (d.m % 4 != 0 || d.m > kHrMaxCols || d.n > kHrMaxRows) hr_low = false;
     }
     plan->hr = plan->rank > kValuMaxRank || hr_low;
-    plan->one_sweep = false;
+    plan->one_sweep = plan->one_wide = false;
     if (plan->hr) return build_hr_tables(plan);
     if (plan->out_dtype != PSGD_F32 && tu.k4_nv != 1) return PSGD_EINVAL;   // bf16 output: one column vector per lane
     if (tu.k1_rows < 0 || tu.k3_rows < 0 || tu.k4_rows < 0 || tu.k1_nv < 1 ||
@@ -862,7 +938,7 @@ psgd_status psgd_plan_worker_mean(const psgd_plan* plan, int32_t* taken, int64_t
 
 psgd_status psgd_plan_one_sweep(const psgd_plan* plan, int32_t* taken, int64_t* bytes) {
     if (!plan) return PSGD_EINVAL;
-    if (taken) *taken = plan->one_sweep ? 1 : 0;
+    if (taken) *taken = plan->one_sweep || plan->one_wide ? 1 : 0;
     if (bytes) *bytes = plan->one_sweep ? plan->one_bytes : 0;
     return PSGD_OK;
 }
@@ -942,7 +1018,8 @@ psgd_status psgd_decompress(psgd_plan* plan, const float* p, const float* q, flo
 psgd_status psgd_step(psgd_plan* plan, const void* grad, float* err, float* q, float* p, void* out,
                       void* workspace, void* hip_stream) {
     if (!plan || bad_ptrs(grad, err, q, p, workspace) || !out) return PSGD_EINVAL;
-    if (plan->resident_ok) return launch_resident_step(plan, grad, err, q, p, out, workspace, hip_stream);
+    if (plan->resident_ok || one_wide_call(plan, grad, out))   // a step of its own, not the two calls
+        return launch_resident_step(plan, grad, err, q, p, out, workspace, hip_stream);
     psgd_status st = launch_compress(plan, grad, err, q, p, workspace, hip_stream);
     if (st != PSGD_OK) return st;
     return launch_decompress(plan, p, q, err, grad, out, workspace, hip_stream);
@@ -961,6 +1038,7 @@ psgd_status psgd_step_iterations(psgd_plan* plan, const void* grad, float* err, 
                                  void* workspace, void* hip_stream, int32_t iterations) {
     if (!plan || bad_ptrs(grad, err, q, p, workspace) || !out || iterations < 1 || iterations > 64) return PSGD_EINVAL;
     if (plan->resident_ok) return launch_resident_step(plan, grad, err, q, p, out, workspace, hip_stream, UpdateArgs(), iterations);
+    if (iterations == 1) return psgd_step(plan, grad, err, q, p, out, workspace, hip_stream);
     psgd_status st = launch_compress(plan, grad, err, q, p, workspace, hip_stream);
     for (int32_t it = 1; it < iterations && st == PSGD_OK; ++it)
         st = launch_compress(plan, nullptr, err, q, p, workspace, hip_stream, false);

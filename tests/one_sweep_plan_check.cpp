@@ -2,6 +2,7 @@
 // tests/test_one_sweep.py: every row of every matrix belongs to exactly one block, every row of P and Q is solved exactly once, the
 // partial sums lie apart within the plan's memory, a row fits the lanes of its wavefronts and the workgroup's shared memory its uses.
 #include <cstdio>
+#include <cstdint>
 #include <cstdlib>
 #include <random>
 
@@ -85,7 +86,61 @@ static void check(const std::vector<psgd_shape>& s, int rank, int W, psgd_dtype 
     psgd_plan_destroy(plan);
 }
 
+// The walk of the matrix-core plans: every row in one block, partial S within the matrix's own part of `out`, blocks in falling size.
+static void check_wide() {
+    const std::vector<std::vector<psgd_shape>> sets = {
+        {{50304, 2048}, {2048, 2048}, {8192, 2048}, {2048, 8192}, {2048, 1}}, {{21000, 4096}, {16, 8}, {32, 8192}, {5, 1}}, {{100000, 1024}}, {{6000, 8192}, {12004, 4096}}};
+    for (auto& s : sets)
+        for (psgd_dtype od : {PSGD_BF16, PSGD_F32}) {
+            psgd_plan* plan = nullptr;
+            CHECK(psgd_plan_create(s.data(), (int)s.size(), 4, 1, PSGD_BF16, od, &plan) == PSGD_OK);
+            CHECK(plan->hr && plan->one_wide && !plan->one_sweep && plan->one_mats.size() == plan->mats.size());
+            const int64_t osz = od == PSGD_BF16 ? 2 : 4;
+            std::vector<std::vector<int>> rows, p_rows, q_rows;
+            int64_t g_at = 0, last = INT64_MAX;
+            for (size_t i = 0; i < plan->one_mats.size(); ++i) {
+                const OneMat& o = plan->one_mats[i];
+                CHECK(o.n_blocks >= 1 && o.m % 4 == 0 && o.m <= (kWave << o.waves_log2) * kOneWideNV * 4 && (1 << o.waves_log2) <= kOneMaxWaves);
+                CHECK(o.s_off * 8 == plan->mats[i].off * osz && (int64_t)o.n_blocks * o.m * o.r * 8 <= (int64_t)o.n * o.m * osz);
+                CHECK(o.g_off == g_at);
+                g_at += (int64_t)o.n_blocks * 10;
+                rows.emplace_back(o.n, 0);
+                p_rows.emplace_back(o.n, 0);
+                q_rows.emplace_back(o.m, 0);
+            }
+            CHECK(g_at * 8 <= plan->sizes.workspace_bytes);
+            std::vector<std::vector<int>> block_seen(rows.size());
+            for (size_t i = 0; i < rows.size(); ++i) block_seen[i].assign(plan->one_mats[i].n_blocks, 0);
+            for (const OneTile& t : plan->one_tiles) {
+                CHECK(t.nrows >= 1 && t.row0 >= 0 && t.row0 + t.nrows <= plan->one_mats[t.mat].n);
+                for (int r = 0; r < t.nrows; ++r) rows[t.mat][t.row0 + r] += 1;
+                block_seen[t.mat].at(t.block) += 1;
+                const int64_t size = (int64_t)t.nrows * plan->one_mats[t.mat].m;
+                CHECK(size <= last);
+                last = size;
+            }
+            for (const SolveTile& t : plan->solve_tiles)
+                for (int k = 0; k < t.count; ++k) (t.rows ? p_rows : q_rows)[t.mat].at(t.first + k) += 1;
+            for (auto* part : {&rows, &p_rows, &q_rows, &block_seen})
+                for (auto& v : *part)
+                    for (int x : v) CHECK(x == 1);
+            CHECK(psgd_plan_set_tuning(plan, "hr_k3_rows", 1024) == PSGD_OK && plan->hr && !plan->one_wide);
+            CHECK(psgd_plan_set_tuning(plan, "hr_k3_rows", 2048) == PSGD_OK && plan->one_wide);
+            CHECK(psgd_plan_set_tuning(plan, "one_sweep", 0) == PSGD_OK && !plan->one_wide);
+            psgd_plan_destroy(plan);
+        }
+    struct { std::vector<psgd_shape> s; int rank, W; psgd_dtype gd; } no[] = {
+        {{{50304, 2048}}, 5, 1, PSGD_BF16}, {{{50304, 2048}}, 4, 2, PSGD_BF16}, {{{50304, 2048}}, 4, 1, PSGD_F32}, {{{11000, 8196}}, 4, 1, PSGD_BF16},
+        {{{50304, 2048}, {15, 64}}, 4, 1, PSGD_BF16}, {{{6000, 8192}, {12000, 4092}}, 4, 1, PSGD_BF16}};
+    for (auto& c : no) {
+        psgd_plan* plan = nullptr;
+        CHECK(psgd_plan_create(c.s.data(), (int)c.s.size(), c.rank, c.W, c.gd, PSGD_BF16, &plan) == PSGD_OK && plan->hr && !plan->one_wide);
+        psgd_plan_destroy(plan);
+    }
+}
+
 int main() {
+    check_wide();
     // Which plans take it, and that nothing of the other route moves: every line of the rule from both sides.
     struct { std::vector<psgd_shape> s; int rank, W; bool taken; } rule[] = {
         {{{900, 6144}}, 2, 1, true},  {{{900, 6148}}, 2, 1, false}, {{{900, 4096}}, 2, 2, true}, {{{900, 4100}}, 2, 2, false},

@@ -252,3 +252,88 @@ def test_one_walk_is_no_further_from_64_bits_than_two(shape, rank, workers):
         rel = lambda x, y: float((x.double().view(-1) - y.reshape(-1)).norm() / y.norm())
         far[one] = (rel(p[: n * rank], P), rel(q[: m * rank], Q), rel(out[: n * m], P @ Q.T))
     assert all(a <= 1.1 * b for a, b in zip(far[1], far[0])), far
+
+
+# rows of one, two, four and eight wavefronts of 16 columns a lane, full and one vector over; fewer rows than groups, rows that end a
+# step early; a matrix whose part of a bf16 `out` holds one block's sums only, a rank of three
+WIDE_HR = [(40, 1024), (130, 1028), (33, 2048), (64, 2052), (17, 4100), (70, 8192), (16, 512), (257, 36), (300, 8188), (32, 4), (77,)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("out_bf16", [True, False])
+def test_matrix_core_step_in_one_walk(out_bf16):
+    """psgd_step of a matrix-core plan in one walk that stores no M and keeps its partial sums in `out`, against the two calls, which
+    take the matrix cores, over two steps; gaps of err and out untouched.  A misaligned out and one that overlaps the gradient take
+    the two calls, bit for bit."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1905_13727_amd import binding as B
+    dev = torch.device("cuda:0")
+    stream = torch.cuda.current_stream(dev).cuda_stream
+    shapes, odt = WIDE_HR, torch.bfloat16 if out_bf16 else torch.float32
+    if not out_bf16:
+        shapes = shapes + [(8, 640)]   # fp32: half as many rows hold a block's sums
+    plan = B.Plan(shapes, 4, 1, B.PSGD_BF16, B.PSGD_BF16 if out_bf16 else B.PSGD_F32)
+    plan.set_tuning("bf16_valu", 0)
+    assert plan.path() == "matrix cores" and plan.one_sweep() == (False, 0)
+    plan.set_tuning("one_sweep", 1)
+    assert plan.path() == "matrix cores" and plan.one_sweep() == (True, 0)
+    s = plan.sizes
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(11)
+    live = torch.zeros(s.out_elems, dtype=torch.bool, device=dev)
+    for t, shape in enumerate(shapes):
+        off = plan.offsets(t)[0]
+        live[off: off + int(np.prod(shape))] = True
+    q0, e0 = torch.randn(s.q_elems, generator=gen, device=dev), 0.5 * torch.randn(s.err_stride, generator=gen, device=dev)
+    grads = [torch.randn(s.grad_stride, generator=gen, device=dev).to(torch.bfloat16) for _ in range(2)]
+
+    def run(how, out):
+        err, q, p = e0.clone(), q0.clone(), torch.zeros(s.p_elems, device=dev)
+        ws = torch.full((s.workspace_bytes // 4 + 64,), float("nan"), device=dev)
+        for g in grads:
+            if how == "split":
+                plan.compress(g, err, q, p, ws, stream)
+                plan.decompress(p, q, err, g, out, ws, stream)
+            elif how == "iterations":
+                plan.step_iterations(g, err, q, p, out, ws, 1, stream)
+            else:
+                plan.step(g, err, q, p, out, ws, stream)
+        plan.check(stream)
+        return err, q, p, out.clone()
+
+    fresh = lambda: torch.full((s.out_elems,), 3.0, dtype=odt, device=dev)
+    a, b, c = run("step", fresh()), run("split", fresh()), run("iterations", fresh())
+    for x, y in zip(a, c):
+        assert torch.equal(x, y)           # one iteration is the step
+    assert (a[3][~live] == 3.0).all() and torch.equal(a[0][~live[: s.err_stride]], e0[~live[: s.err_stride]])
+    for t, shape in enumerate(shapes):     # fp64 against fp32 sums of up to 8192 products, times the condition of random panels
+        off, p_off, q_off, r = plan.offsets(t)
+        n = int(np.prod(shape))
+        pairs = [(a[3][off: off + n], b[3][off: off + n], 2.0 ** -8 if out_bf16 else 2e-5)]
+        if r:
+            pairs += [(a[0][off: off + n], b[0][off: off + n], 2e-5), (a[1][q_off: q_off + shape[1] * r], b[1][q_off: q_off + shape[1] * r], 2e-5),
+                      (a[2][p_off: p_off + shape[0] * r], b[2][p_off: p_off + shape[0] * r], 2e-5)]
+        scale = float(a[0].norm() / a[0].numel() ** 0.5) * n ** 0.5   # full-rank matrices leave an error memory of roundings
+        for x, y, tol in pairs:
+            x, y = x.float(), y.float()
+            assert torch.isfinite(x).all() and float((x - y).norm()) <= tol * max(float(y.norm()), scale), (t, shape)
+    off = torch.full((s.out_elems + 8,), 3.0, dtype=odt, device=dev)[2 if out_bf16 else 1:][: s.out_elems]
+    for x, y in zip(run("step", off), b):
+        assert torch.equal(x, y)           # out not aligned to 16 bytes
+    if out_bf16:
+        both = torch.zeros(s.grad_stride + s.out_elems, dtype=odt, device=dev)
+        got = []
+        for how in ("step", "split"):
+            both[: s.grad_stride] = grads[0]
+            err, q, p = e0.clone(), q0.clone(), torch.zeros(s.p_elems, device=dev)
+            ws = torch.empty(s.workspace_bytes // 4 + 64, device=dev)
+            if how == "step":
+                plan.step(both, err, q, p, both, ws, stream)
+            else:
+                plan.compress(both, err, q, p, ws, stream)
+                plan.decompress(p, q, err, both, both, ws, stream)
+            plan.check(stream)
+            got.append((err, q, p, both[: s.out_elems][live].clone()))
+        for x, y in zip(*got):
+            assert torch.equal(x, y)       # out in the gradient's place
