@@ -292,7 +292,7 @@ __device__ __forceinline__ float sum_parts(const float* __restrict__ src, int np
 template <int R>
 __device__ __forceinline__ void sum_parts_row(const float* __restrict__ src, int r, int nparts, int64_t stride,
                                               float (&row)[R]) {
-    constexpr int U = R <= 2 ? 8 : (R <= 4 ? 4 : 2);
+    constexpr int U = R <= 2 ? 8 : 4;
 #pragma unroll
     for (int k = 0; k < R; ++k) row[k] = 0.f;
     int c = 0;
@@ -442,6 +442,23 @@ __global__ __launch_bounds__(kOrthoBlock) void k_ortho(const MatDesc* __restrict
 // factorises (fp64, r <= 8) and solves P_hat R = P row by row.  A pivot <= 1e-30 (the squared norm
 // Gram-Schmidt would find for that column at its turn) gives a zero column.
 
+// the wavefront's sums of the upper triangle, to LDS
+template <int R>
+__device__ __forceinline__ void deposit_gram(const double (&g)[R][R], double* red, int lane) {
+    constexpr int N = R * (R + 1) / 2;
+    double x[N];
+    int at = 0;   // where this lane's sum goes
+#pragma unroll
+    for (int a = 0, l = 0; a < R; ++a)
+#pragma unroll
+        for (int b = a; b < R; ++b, ++l) {
+            x[l] = g[a][b];
+            if (lane == l) at = a * kValuMaxRank + b;
+        }
+    const double v = lane_sums<N>(x);
+    if (lane < N) red[at] = v;
+}
+
 __global__ __launch_bounds__(kBlock) void k_gram(const MatDesc* __restrict__ mats, const Tile* __restrict__ tiles,
                                                  const float* __restrict__ ws, float* __restrict__ p,
                                                  double* __restrict__ gram, int workers, int pre_reduced) {
@@ -471,14 +488,7 @@ __global__ __launch_bounds__(kBlock) void k_gram(const MatDesc* __restrict__ mat
             for (int b = a; b < kValuMaxRank; ++b)
                 if (b < r) g[a][b] += (double)row[a] * (double)row[b];
     }
-#pragma unroll
-    for (int a = 0; a < kValuMaxRank; ++a)
-#pragma unroll
-        for (int b = a; b < kValuMaxRank; ++b)
-            if (b < r) {
-                const double v = wave_sum(g[a][b]);
-                if (lane == 0) red[wave][a * kValuMaxRank + b] = v;
-            }
+    deposit_gram<kValuMaxRank>(g, red[wave], lane);
     __syncthreads();
     if (tid < r * r) {
         const int a = tid / r, b = tid % r;
@@ -534,36 +544,17 @@ __global__ __launch_bounds__(kBlock) void k_chol_apply(const MatDesc* __restrict
     }
     __syncthreads();
     if (tid == 0) {
-        // Every index below is a compile-time constant (loops unrolled to the largest rank, rows and columns
-        // past r switched off by predicates), so the matrix lives in registers; R overwrites G's upper triangle.
-        double G[kValuMaxRank][kValuMaxRank];
+        double G[kValuMaxRank][kValuMaxRank], inv[kValuMaxRank];
 #pragma unroll
         for (int a = 0; a < kValuMaxRank; ++a)
 #pragma unroll
             for (int b = a; b < kValuMaxRank; ++b) G[a][b] = b < r ? Gs[a * r + b] : 0.0;
-        // Cholesky, row by row of R (upper): R_jj = sqrt(G_jj - sum_k R_kj^2), R_jc = (G_jc - sum_k R_kj R_kc) / R_jj
+        cholesky_rows<kValuMaxRank>(G, inv, r);
 #pragma unroll
-        for (int j = 0; j < kValuMaxRank; ++j) {
-            if (j < r) {
-                double piv = G[j][j];
+        for (int a = 0; a < kValuMaxRank; ++a) {
+            rinv[a] = inv[a];
 #pragma unroll
-                for (int k = 0; k < j; ++k) piv -= G[k][j] * G[k][j];
-                const bool dead = piv <= 1e-30;
-                const double rjj = dead ? 0.0 : sqrt(piv);
-                const double rj = dead ? 0.0 : 1.0 / rjj;
-                rinv[j] = rj;
-                G[j][j] = rjj;
-                Rm[j][j] = rjj;
-#pragma unroll
-                for (int c = j + 1; c < kValuMaxRank; ++c) {
-                    double v = G[j][c];
-#pragma unroll
-                    for (int k = 0; k < j; ++k) v -= G[k][j] * G[k][c];
-                    v = dead ? 0.0 : v * rj;     // a zero column takes no part in the later ones
-                    G[j][c] = v;
-                    if (c < r) Rm[j][c] = v;
-                }
-            }
+            for (int b = a; b < kValuMaxRank; ++b) Rm[a][b] = G[a][b];
         }
     }
     __syncthreads();
@@ -640,14 +631,7 @@ __global__ __launch_bounds__(kBlock) void k_gram_chol(const MatDesc* __restrict_
     for (int a = 0; a < R; ++a)
 #pragma unroll
         for (int b = a; b < R; ++b) g[a][b] = (b < r && have) ? (double)row[a] * (double)row[b] : 0.0;
-#pragma unroll
-    for (int a = 0; a < R; ++a)
-#pragma unroll
-        for (int b = a; b < R; ++b)
-            if (b < r) {
-                const double v = wave_sum(g[a][b]);
-                if (lane == 0) red[wave][a * kValuMaxRank + b] = v;
-            }
+    deposit_gram<R>(g, red[wave], lane);
     __syncthreads();
     const int nent = r * r;
     if (tid < nent) {
@@ -701,34 +685,17 @@ __global__ __launch_bounds__(kBlock) void k_gram_chol(const MatDesc* __restrict_
     }
     __syncthreads();
     if (tid == 0) {
-        double G[R][R];
+        double G[R][R], inv[R];
 #pragma unroll
         for (int a = 0; a < R; ++a)
 #pragma unroll
             for (int b = a; b < R; ++b) G[a][b] = b < r ? Gs[a * r + b] : 0.0;
-        // Cholesky, row by row of R (upper): R_jj = sqrt(G_jj - sum_k R_kj^2), R_jc = (G_jc - sum_k R_kj R_kc) / R_jj
+        cholesky_rows<R>(G, inv, r);
 #pragma unroll
-        for (int j = 0; j < R; ++j) {
-            if (j < r) {
-                double piv = G[j][j];
+        for (int a = 0; a < R; ++a) {
+            rinv[a] = inv[a];
 #pragma unroll
-                for (int k = 0; k < j; ++k) piv -= G[k][j] * G[k][j];
-                const bool dead = piv <= 1e-30;
-                const double rjj = dead ? 0.0 : sqrt(piv);
-                const double rj = dead ? 0.0 : 1.0 / rjj;
-                rinv[j] = rj;
-                G[j][j] = rjj;
-                Rm[j][j] = rjj;
-#pragma unroll
-                for (int c = j + 1; c < R; ++c) {
-                    double v = G[j][c];
-#pragma unroll
-                    for (int k = 0; k < j; ++k) v -= G[k][j] * G[k][c];
-                    v = dead ? 0.0 : v * rj;     // a zero column takes no part in the later ones
-                    G[j][c] = v;
-                    if (c < r) Rm[j][c] = v;
-                }
-            }
+            for (int b = a; b < R; ++b) Rm[a][b] = G[a][b];
         }
     }
     __syncthreads();

@@ -52,16 +52,6 @@ __device__ __forceinline__ float graw_at(const graw<V, BF>& g, int x) {
 
 constexpr int pow2_at_least(int n) { return n <= 1 ? 1 : 2 * pow2_at_least((n + 1) / 2); }
 
-__device__ __forceinline__ float lane_read(float v, int src_lane) {
-    return __int_as_float(__builtin_amdgcn_ds_bpermute(src_lane << 2, __float_as_int(v)));
-}
-__device__ __forceinline__ double lane_read(double v, int src_lane) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_ds_bpermute(src_lane << 2, (int)(b & 0xffffffffLL));
-    const int hi = __builtin_amdgcn_ds_bpermute(src_lane << 2, (int)(b >> 32));
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
 // N <= 8 sums over the 64 lanes at once, in float or double: lane l < N returns the sum of x[l] (lane_sums is the one for more).  The values are handed
 // over in halves between partners whose lane bit differs; the lane bits that chose nothing are added up afterwards.
 template <int N, typename T>
@@ -512,29 +502,17 @@ __global__ __launch_bounds__(kBlock) void k_solve(const OneMat* __restrict__ mat
     }
     __syncthreads();
     if (tid == kBlock - 1) {   // the factor, by one thread whose wavefront sums no columns below
-        double g[R][R];
+        double g[R][R], inv[R];
 #pragma unroll
         for (int a = 0; a < R; ++a)
 #pragma unroll
             for (int b = a; b < R; ++b) g[a][b] = G[a * R - a * (a - 1) / 2 + (b - a)];
+        cholesky_rows<R>(g, inv, R);   // columns past the matrix's own rank: entries of zero
 #pragma unroll
-        for (int j = 0; j < R; ++j) {
-            double piv = g[j][j];
+        for (int a = 0; a < R; ++a) {
+            rinv[a] = inv[a];
 #pragma unroll
-            for (int k = 0; k < j; ++k) piv -= g[k][j] * g[k][j];
-            const bool dead = piv <= 1e-30;   // also the columns past the matrix's own rank, whose entries are zero
-            const double rjj = dead ? 0.0 : sqrt(piv);
-            const double rj = dead ? 0.0 : 1.0 / rjj;
-            rinv[j] = rj;
-#pragma unroll
-            for (int b = j + 1; b < R; ++b) {
-                double v = g[j][b];
-#pragma unroll
-                for (int k = 0; k < j; ++k) v -= g[k][j] * g[k][b];
-                v = dead ? 0.0 : v * rj;   // a zero column takes no part in the later ones
-                g[j][b] = v;
-                Rm[j][b] = v;
-            }
+            for (int b = a + 1; b < R; ++b) Rm[a][b] = g[a][b];
         }
     }
     if (!t.rows && sl == 0 && c < t.count) {
