@@ -120,10 +120,11 @@ def device_gradients(wl, lay, plan, workers, seed, torch, dev, dtype=None):
     return grad
 
 
-def byte_models(s, W, gsz, osz, mean, fused_update=False, iterations=1, one_sweep=False):
+def byte_models(s, W, gsz, osz, mean, fused_update=False, iterations=1, one_sweep=False, unstored=False):
     """Algorithmic bytes per launch of each kernel (what the kernel itself has to move), and of a whole streaming step.
     mean: the products are taken of the mean over the workers (psgd_plan_worker_mean); one_sweep: M is walked once before
-    the decompression (psgd_plan_one_sweep)."""
+    the decompression (psgd_plan_one_sweep); unstored: that walk stores no M and the decompression adds g and e again (a
+    matrix-core plan's psgd_step)."""
     payload_mat, L = s.payload_elems - s.n_vec_elems, s.n_vec_elems
     m_bytes = payload_mat * 4 * (1 if mean else W)                          # what the products read after the first sweep
     kernel_bytes = {
@@ -138,6 +139,11 @@ def byte_models(s, W, gsz, osz, mean, fused_update=False, iterations=1, one_swee
         extra = (payload_mat + L) * (16 - osz)
         kernel_bytes["k_resident"] += extra
         kernel_bytes["k_decomp"] += extra
+    if unstored:
+        kernel_bytes["k_ef_right"] = payload_mat * (gsz + 4)
+        kernel_bytes["k_left"] = 0
+        kernel_bytes["k_decomp"] += payload_mat * gsz
+        return kernel_bytes, int(s.bytes_min) + payload_mat * (gsz + 4)
     if one_sweep:         # nothing but M is stored, and an iteration walks every worker's M once
         kernel_bytes["k_ef_right"] = payload_mat * W * (gsz + 8 if iterations == 1 else 4)
         kernel_bytes["k_left"] = 0
@@ -413,8 +419,11 @@ def main():
     L = s.n_vec_elems
     gsz, osz = (2 if gdt == "bf16" else 4), (2 if odt == "bf16" else 4)
     mean = plan.worker_mean()[0]
-    one_sweep = plan.one_sweep()[0] and not resident
-    kernel_bytes, stream_bytes = byte_models(s, W, gsz, osz, mean, args.update == "fused", args.iterations, one_sweep)
+    one_sweep = plan.one_sweep()[0] and not resident and not sparse
+    unstored = one_sweep and plan.path() == "matrix cores"
+    if unstored and (args.update == "fused" or args.iterations > 1):
+        one_sweep = unstored = False   # those calls of a matrix-core plan keep M
+    kernel_bytes, stream_bytes = byte_models(s, W, gsz, osz, mean, args.update == "fused", args.iterations, one_sweep, unstored)
     dom = max(kernel_bytes, key=lambda k: kavg.get(k, 0.0))
     achieved = kernel_bytes[dom] / (kavg[dom] * 1e-3) / 1e9 if kavg[dom] > 0 else 0.0
     grad_bytes = W * (payload_mat + L) * gsz
@@ -428,7 +437,7 @@ def main():
     if (sparse and dom != "k_ef_add_zero") or (not sparse and dom == "k_ef_add_zero"):
         traffic = None
     compressor_label = {"powersgd": "PowerSGD", "random_block": "Random Block", "random_k": "Random K"}[args.compressor]
-    if args.update != "none" or args.iterations != 1 or tune or (one_sweep and dom == "k_ef_right"):
+    if args.update != "none" or args.iterations != 1 or tune or unstored or (one_sweep and dom == "k_ef_right"):
         traffic, traffic_source = None, None   # the counters were taken on the plain step with the planner's own choices
     if resident and args.update != "separate":
         cold_dom_ms = cold_ms["median"] if cold_ms else None
@@ -455,7 +464,8 @@ def main():
                    "compressor": args.compressor,
                    "mode": "elementwise sweep + kept entries (two kernels)" if sparse else
                            "resident (one kernel, M kept in registers)" if resident else
-                           ("matrix cores (one kernel per phase)" if plan.path() == "matrix cores"
+                           ("matrix cores (one walk that stores no M before the decompression)" if unstored
+                            else "matrix cores (one kernel per phase)" if plan.path() == "matrix cores"
                             else "streaming (one walk over M before the decompression)" if one_sweep
                             else "streaming (one kernel per phase)"),
                    "matrices": int(s.n_matrices), "matrix_elems": int(payload_mat), "vector_elems": int(L),

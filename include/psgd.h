@@ -149,7 +149,7 @@ PSGD_API psgd_status psgd_plan_offsets(const psgd_plan* plan, int32_t tensor, in
  *                 workers (non-temporal accesses to M and the error memory above 320 MB; below it, one worker,
  *                 to the momentum and parameters of the fused update where the three together exceed 320 MB),
  *                 0 never, 1 always (M and the error memory)
- *   gram_fused    orthogonalisation over row blocks: 1 (default) Gram matrices and factorisation in one launch where the
+ *   gram_fused    orthogonalisation over row blocks: -1 (default) or 1 Gram matrices and factorisation in one launch where the
  *                 device holds all row blocks of the launch at once, 0 in two launches, 2 (TEST ONLY) in one
  *                 launch unconditionally: its waits may then time out, see psgd_plan_check
  *   gram_spin     polls before a wait in that launch gives up, 1 .. 2^24 (default 2^18)
@@ -322,7 +322,7 @@ PSGD_API psgd_status psgd_plan_kept(const psgd_plan* plan, int32_t tensor, int64
  * psgd_plan_kernel_times copies the accumulated milliseconds per kernel (array
  * of PSGD_N_KERNELS doubles, order given by psgd_kernel_name) and the number of
  * accumulated steps, then clears the accumulators.  Where psgd_plan_one_sweep
- * holds, the first entry is k_one_sweep and the second k_solve.  A plan in resident mode
+ * holds, the first entry is the one walk and the second k_solve.  A plan in resident mode
  * (see psgd_step) runs one kernel per step, index PSGD_KERNEL_RESIDENT; the
  * baseline steps (psgd_random_block_step, psgd_random_k_step) fill the last two
  * entries and wait for the stream at their end like psgd_decompress. */

@@ -1,13 +1,13 @@
 // HIP kernels for gfx950 (MI355X) and their launchers.
 //
 // One PowerSGD step (arXiv 1905.13727, Algorithm 1 inside the error-feedback
-// loop of Algorithm 2) is five to seven grouped launches over work-lists built by the
-// planner; every launch covers all matrices of the model and all W workers:
+// loop of Algorithm 2) is three to seven grouped launches over work-lists built by the
+// planner (up to rank 4 k_one_sweep and k_solve, in psgd_onesweep.hip, stand in for all before k_decomp where rows fit); every launch covers all matrices of the model and all W workers:
 //
 //   k_ef_right    M_w = g_w + e_w (stored in e_w's place) fused with the row dot
 //                 products of P_w = M_w Q               (Alg. 2 "Delta_w", Alg. 1 "P <- M Q");
 //                 without the add, one more subspace iteration on a stored M (Appendix G.7)
-//   k_ef_right_mean  the same on large sets of four workers or more: M_w of all workers, their mean, and the products of the
+//   k_ef_right_mean  the same on large sets of four workers or more that the one walk does not take: M_w of all workers, their mean, and the products of the
 //                 mean, which the launches up to Q then work on
 //   k_gram_chol   mean over workers / column chunks, then the orthonormal factor Gram-Schmidt
 //                 gives, by Cholesky-QR over many workgroups in one launch; k_gram,
