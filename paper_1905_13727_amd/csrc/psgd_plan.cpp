@@ -3,7 +3,9 @@
 // No HIP call is made in this file.
 #include <algorithm>
 #include <cstring>
+#include <functional>
 #include <new>
+#include <queue>
 
 #include "psgd_internal.h"
 
@@ -255,9 +257,10 @@ static int64_t one_row_cost(const OneMat& o, bool mean) {
     return (o.m + ((int64_t)kWave << o.waves_log2) * one_nv(o.vec, mean) * o.vec) / 2;
 }
 
-// Row blocks per matrix for `slots` workgroups: all on the device at once (a second generation of workgroups adds its first loads
-// and last sums, 6 us, and was never faster), and within that as little in the largest as can be.  Returns that one's cost.
-static int64_t one_sweep_blocks(const psgd_plan* plan, int waves, int64_t slots, std::vector<int64_t>* blocks) {
+// Row blocks per matrix, `deals` for each of the `slots` workgroups that the device holds at once.  With one deal there are no more of
+// them than slots (a second generation of workgroups adds its first loads and last sums, 6 us, and where the elements divide evenly
+// was never faster), and within that as little in the largest as can be.  With several, the hardware deals them out, largest first.
+static void one_sweep_blocks(const psgd_plan* plan, int waves, int64_t slots, int deals, std::vector<int64_t>* blocks) {
     const bool mean = plan->workers > 1;
     int64_t total = 0;
     for (const OneMat& o : plan->one_mats) total += o.n * one_row_cost(o, mean);
@@ -266,20 +269,39 @@ static int64_t one_sweep_blocks(const psgd_plan* plan, int waves, int64_t slots,
         const int64_t most = ceil_div(o.n, groups * kOneRows * one_depth(plan->rank, mean));   // a full pipeline for every group
         return std::min(most, ceil_div(o.n * one_row_cost(o, mean), cost));
     };
-    int64_t cost = std::max<int64_t>(1, ceil_div(total, slots));
-    for (;;) {
+    int64_t cost = std::max<int64_t>(1, ceil_div(total, slots * deals));
+    while (deals == 1) {
         int64_t tiles = 0;
         for (const OneMat& o : plan->one_mats) tiles += blocks_of(o, cost);
         if (tiles <= slots || cost >= total) break;
         cost += ceil_div(cost, 64);
     }
     blocks->clear();
-    int64_t largest = 0;
-    for (const OneMat& o : plan->one_mats) {
-        blocks->push_back(blocks_of(o, cost));
-        largest = std::max(largest, ceil_div(o.n, blocks->back()) * one_row_cost(o, mean));
+    for (const OneMat& o : plan->one_mats) blocks->push_back(blocks_of(o, cost));
+}
+
+// When the last block is done, in elements: every workgroup takes the next one of the list, largest first, as it ends one, and pays
+// `extra` for the new one's first loads and the old one's last sums.
+static double one_sweep_span(const psgd_plan* plan, int64_t slots, const std::vector<int64_t>& blocks, double extra) {
+    const bool mean = plan->workers > 1;
+    std::vector<double> costs;
+    for (size_t i = 0; i < blocks.size(); ++i) {
+        const OneMat& o = plan->one_mats[i];
+        costs.insert(costs.end(), (size_t)blocks[i], (double)(ceil_div(o.n, blocks[i]) * one_row_cost(o, mean)));
     }
-    return largest;
+    std::sort(costs.begin(), costs.end(), std::greater<double>());
+    std::priority_queue<double, std::vector<double>, std::greater<double>> ends;
+    double last = 0;
+    for (size_t i = 0; i < costs.size(); ++i) {
+        double at = 0;
+        if ((int64_t)i >= slots) {
+            at = ends.top() + extra;
+            ends.pop();
+        }
+        ends.push(at + costs[i]);
+        last = std::max(last, at + costs[i]);
+    }
+    return last;
 }
 
 static void push_solve_tiles(psgd_plan* plan, int32_t mat, const OneMat& o) {
@@ -324,26 +346,33 @@ static void build_one_sweep(psgd_plan* plan) {
         plan->one_mats.push_back(o);
     }
     // Two workgroups of four wavefronts on a compute unit, or one of eight, which writes half the partial S (LSTM-shaped set, rank 4, 1 / 2
-    // workers 159 / 302 and 157 / 287 us) but divides the matrices more coarsely (80 matrices of 24 M elements 128 / 133): the
-    // cheaper by the time of the largest block, of the partial S written and read, and of the longest sum over blocks.
+    // workers 159 / 302 and 157 / 287 us) but divides the matrices more coarsely (80 matrices of 24 M elements 128 / 133); and one, two
+    // or four blocks for each: the cheapest by the time to the last block, of the partial S written and read, and of the longest sum
+    // over blocks.  More than one where the matrices are so many that a block for each of the workgroups divides the large ones too
+    // coarsely: whole steps, two walks / one block / several, rank 2: 600 of 64 x 9 and one of 1000 x 2560 61 / 576 / 57 us (3 workers 129 / 1849 /
+    // 97), 400 of 32 x 9 and 20 of 512 x 2304 132 / 137 / 124, 600 of 64 ... 1024 rows and columns 497 / 605 / 434, 300 of 1000 x 1000 1555 / 1593 / 1439,
+    // 1000 of 100 x 100 90 / 96 / 79.
     const double bytes = (double)W * ((plan->grad_dtype == PSGD_BF16 ? 2 : 4) + 8);
     double best = 0;
     std::vector<int64_t> blocks, trial;
     for (int waves : {4, 8}) {
         if ((1 << max_log2) > waves) continue;
         const int64_t slots = (int64_t)kResCUs * (kOneMaxWaves / waves);
-        const int64_t cost = one_sweep_blocks(plan, waves, slots, &trial);
-        double partial = 0;
-        int64_t longest = 0;
-        for (size_t i = 0; i < trial.size(); ++i) {
-            partial += 16.0 * trial[i] * plan->one_mats[i].m * plan->one_mats[i].r;
-            longest = std::max(longest, trial[i]);
-        }
-        const double us = ((double)cost * slots * bytes + partial) / 6e6 + 0.025 * longest + (waves == 8 ? 2.0 : 0.0);
-        if (blocks.empty() || us < best) {
-            best = us;
-            blocks = trial;
-            plan->one_waves = waves;
+        const double per_us = 6e6 / (slots * bytes);   // elements that a workgroup walks in a microsecond while all of them do
+        for (int deals : {1, 2, 4}) {
+            one_sweep_blocks(plan, waves, slots, deals, &trial);
+            double partial = 0;
+            int64_t longest = 0;
+            for (size_t i = 0; i < trial.size(); ++i) {
+                partial += 16.0 * trial[i] * plan->one_mats[i].m * plan->one_mats[i].r;
+                longest = std::max(longest, trial[i]);
+            }
+            const double us = one_sweep_span(plan, slots, trial, 6.0 * per_us) / per_us + partial / 6e6 + 0.025 * longest + (waves == 8 ? 2.0 : 0.0);
+            if (blocks.empty() || us < best) {
+                best = us;
+                blocks = trial;
+                plan->one_waves = waves;
+            }
         }
     }
     const int64_t NG = R * (R + 1) / 2;
@@ -364,6 +393,10 @@ static void build_one_sweep(psgd_plan* plan) {
         }
         push_solve_tiles(plan, (int32_t)i, o);
     }
+    if ((int64_t)plan->one_tiles.size() > (int64_t)kResCUs * (kOneMaxWaves / plan->one_waves))   // dealt out: what is left for the end is small
+        std::stable_sort(plan->one_tiles.begin(), plan->one_tiles.end(), [&](const OneTile& a, const OneTile& b) {
+            return a.nrows * one_row_cost(plan->one_mats[a.mat], mean) > b.nrows * one_row_cost(plan->one_mats[b.mat], mean);
+        });
     plan->one_s_doubles = round_up(sd, 32);
     plan->one_lds_bytes = (int32_t)lds;
     plan->one_bytes = (plan->one_s_doubles + gd) * (int64_t)sizeof(double);

@@ -1,0 +1,89 @@
+// Host-only check of which sets the one walk over M takes and how it divides them, built with g++ and the sanitizers by
+// tests/test_one_sweep_rule.py.
+#include <algorithm>
+#include <cstdint>
+#include <cstdio>
+#include <cstdlib>
+#include <functional>
+#include <queue>
+#include <vector>
+
+#include "psgd_internal.h"
+
+namespace psgd {
+void free_tables(psgd_plan*) {}
+psgd_status set_profiling(psgd_plan*, bool) { return PSGD_EHIP; }
+psgd_status check_plan(psgd_plan*, void*) { return PSGD_EHIP; }
+psgd_status launch_sparse_step(psgd_plan*, const void*, float*, const int64_t*, const int64_t*, float*, void*, void*) { return PSGD_EHIP; }
+psgd_status static_workspace(psgd_plan*, void**) { return PSGD_EHIP; }
+psgd_status read_trace(psgd_plan*, uint64_t*, int64_t, int64_t*) { return PSGD_EHIP; }
+psgd_status launch_resident_step(psgd_plan*, const void*, float*, float*, float*, void*, void*, void*, const UpdateArgs&, int) { return PSGD_EHIP; }
+psgd_status launch_compress(psgd_plan*, const void*, float*, float*, float*, void*, void*, bool) { return PSGD_EHIP; }
+psgd_status launch_decompress(psgd_plan*, const float*, const float*, float*, const void*, void*, void*, void*, const UpdateArgs&) { return PSGD_EHIP; }
+}  // namespace psgd
+
+#define CHECK(c)                                                    \
+    do {                                                            \
+        if (!(c)) {                                                 \
+            std::printf("FAIL %s:%d %s\n", __FILE__, __LINE__, #c); \
+            std::exit(1);                                           \
+        }                                                           \
+    } while (0)
+
+using namespace psgd;
+typedef std::vector<psgd_shape> Set;
+
+static psgd_plan* make(const Set& s, int rank, int W, psgd_dtype gd = PSGD_F32, psgd_dtype od = PSGD_F32) {
+    psgd_plan* plan = nullptr;
+    CHECK(psgd_plan_create(s.data(), (int)s.size(), rank, W, gd, od, &plan) == PSGD_OK);
+    return plan;
+}
+
+static Set many(int n, psgd_shape s, int more = 0, psgd_shape t = {1, 1}) {
+    Set v((size_t)n, s);
+    v.insert(v.end(), (size_t)more, t);
+    return v;
+}
+
+// Sets of more matrices than there are workgroups at once: the last workgroup to end has no more than twice its share of the elements,
+// dealt in the order of the list, and every row lies in one block.
+static void check_many() {
+    Set powers, steps;
+    for (int i = 0; i < 600; ++i) powers.push_back({64 << (i % 5), 64 << (i / 5 % 5)});
+    for (int i = 0; i < 480; ++i) steps.push_back({100 + 37 * i % 900, 50 + 91 * i % 1900});
+    const Set sets[] = {many(600, {64, 9}, 1, {1000, 2560}), many(400, {32, 9}, 20, {512, 2304}), many(400, {32, 9}, 100, {512, 2304}), powers, steps,
+                        many(300, {1000, 1000}), many(250, {64, 9}, 1, {1000, 2560})};
+    for (const Set& s : sets)
+        for (int W : {1, 3}) {
+            psgd_plan* plan = make(s, 2, W);
+            CHECK(plan->one_sweep && plan->one_bytes <= kOneMaxBytes);
+            const size_t slots = (size_t)kResCUs * (kOneMaxWaves / plan->one_waves);
+            std::vector<std::vector<int>> rows;
+            for (const OneMat& o : plan->one_mats) rows.emplace_back(o.n, 0);
+            int64_t total = 0, last = 0;
+            std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>> ends;
+            for (const OneTile& t : plan->one_tiles) {
+                int64_t at = 0;
+                if (ends.size() >= slots) {
+                    at = ends.top();
+                    ends.pop();
+                }
+                at += (int64_t)t.nrows * plan->one_mats[t.mat].m;
+                ends.push(at);
+                last = std::max(last, at);
+                total += (int64_t)t.nrows * plan->one_mats[t.mat].m;
+                CHECK(t.block >= 0 && t.block < plan->one_mats[t.mat].n_blocks);
+                for (int r = 0; r < t.nrows; ++r) rows[t.mat].at(t.row0 + r) += 1;
+            }
+            for (auto& v : rows)
+                for (int x : v) CHECK(x == 1);
+            CHECK(last <= 2 * total / (int64_t)slots + 4 * kOneRows * 2560);   // or a full pipeline of the longest rows
+            psgd_plan_destroy(plan);
+        }
+}
+
+int main() {
+    check_many();
+    std::printf("OK\n");
+    return 0;
+}
