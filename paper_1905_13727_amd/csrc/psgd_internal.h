@@ -118,6 +118,7 @@ struct RTile {
 constexpr int kOneMaxRank = 4;
 constexpr int kOneMaxWaves = 8;     // wavefronts of a workgroup, and of a row
 constexpr int kOneRows = 2;         // rows of a step
+constexpr int kOneStepWorkers = 8;  // from this many workers on small sets have groups of a single step (one_sweep_blocks)
 constexpr int64_t kOneMaxBytes = int64_t(64) << 20;   // plan-owned partial sums
 // Column vectors a lane owns (12 columns; fewer with several workers, whose steps take the registers of two more sets of rows, and of
 // rows that are read element by element), and steps whose loads are in flight: what 256 registers hold beside the lane's fp64

@@ -260,13 +260,23 @@ static int64_t one_row_cost(const OneMat& o, bool mean) {
 // Row blocks per matrix, `deals` for each of the `slots` workgroups that the device holds at once.  With one deal there are no more of
 // them than slots (a second generation of workgroups adds its first loads and last sums, 6 us, and where the elements divide evenly
 // was never faster), and within that as little in the largest as can be.  With several, the hardware deals them out, largest first.
+//
+// A group of wavefronts walks two steps at least: every block leaves a partial S behind.  One where that makes so few blocks that much
+// of the chip is idle (below half of the slots from eight workers on, whose steps are long, below a quarter with one worker at ranks
+// whose ring holds one step).  Whole steps, us, two steps / one: 32 workers, rank 2, five matrices of 0.2 M elements 128 / 89, 20 of 0.4 M 167 / 124; 8 workers, the same
+// 40 / 30 and 52 / 43, but 8 of 512 x 320 (256 blocks at two steps) 45.4 / 46.6; one worker, rank 4, 900 x 640 (57) 24.2 / 22.5, but 12 of 300 x 400 (228) 25.2 / 27.5,
+// 8 of 512 x 320 24.4 / 27.4, 900 x 2048 32.1 / 36.4.
 static void one_sweep_blocks(const psgd_plan* plan, int waves, int64_t slots, int deals, std::vector<int64_t>* blocks) {
     const bool mean = plan->workers > 1;
+    const int64_t few = plan->workers >= kOneStepWorkers ? slots / 2 : (one_depth(plan->rank, mean) == 1 ? slots / 4 : 0);
+    int64_t steps = 2, at_two = 0;
+    for (const OneMat& o : plan->one_mats) at_two += ceil_div(o.n, (waves >> o.waves_log2) * kOneRows * 2);
+    if (at_two < few) steps = 1;
     int64_t total = 0;
     for (const OneMat& o : plan->one_mats) total += o.n * one_row_cost(o, mean);
     auto blocks_of = [&](const OneMat& o, int64_t cost) {
         const int64_t groups = waves >> o.waves_log2;
-        const int64_t most = ceil_div(o.n, groups * kOneRows * one_depth(plan->rank, mean));   // a full pipeline for every group
+        const int64_t most = ceil_div(o.n, groups * kOneRows * steps);
         return std::min(most, ceil_div(o.n * one_row_cost(o, mean), cost));
     };
     int64_t cost = std::max<int64_t>(1, ceil_div(total, slots * deals));

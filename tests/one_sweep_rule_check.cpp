@@ -26,7 +26,8 @@ psgd_status launch_decompress(psgd_plan*, const float*, const float*, float*, co
     do {                                                            \
         if (!(c)) {                                                 \
             std::printf("FAIL %s:%d %s\n", __FILE__, __LINE__, #c); \
-            std::exit(1);                                           \
+            std::fflush(stdout);                                    \
+            std::_Exit(1);                                          \
         }                                                           \
     } while (0)
 
@@ -82,8 +83,28 @@ static void check_many() {
         }
 }
 
+// A group of wavefronts walks two steps at least; one where two would leave fewer blocks than half of the workgroups that the device
+// holds from eight workers on, than a quarter with one worker at ranks 3 and 4.
+static void check_steps() {
+    for (const Set& s : {many(1, {37, 90}), many(3, {100, 200}), many(11, {160, 300}), many(15, {400, 300}), many(8, {512, 320}), many(20, {400, 300})})
+        for (int rank : {1, 2, 3, 4})
+            for (int W : {1, 2, 4, 8, 32}) {
+                psgd_plan* plan = make(s, rank, W);
+                CHECK(plan->one_sweep);
+                const int64_t slots = kResCUs * (kOneMaxWaves / plan->one_waves), rows = (plan->one_waves >> plan->one_mats[0].waves_log2) * kOneRows;
+                const int64_t n = plan->one_mats[0].n, at_two = (int64_t)s.size() * ((n + 2 * rows - 1) / (2 * rows));
+                const int64_t steps = at_two < (W >= 8 ? slots / 2 : (W == 1 && rank >= 3 ? slots / 4 : 0)) ? 1 : 2;
+                for (const OneMat& o : plan->one_mats) {
+                    CHECK(o.n_blocks <= (n + steps * rows - 1) / (steps * rows));
+                    if (s.size() <= 3) CHECK(o.n_blocks == (n + steps * rows - 1) / (steps * rows));
+                }
+                psgd_plan_destroy(plan);
+            }
+}
+
 int main() {
     check_many();
+    check_steps();
     std::printf("OK\n");
     return 0;
 }
