@@ -120,6 +120,9 @@ constexpr int kOneMaxWaves = 8;     // wavefronts of a workgroup, and of a row
 constexpr int kOneRows = 2;         // rows of a step
 constexpr int kOneStepWorkers = 8;  // from this many workers on small sets have groups of a single step (one_sweep_blocks)
 constexpr int64_t kOneMaxBytes = int64_t(64) << 20;   // plan-owned partial sums
+// Lines of one_sweep_pays, in elements of a worker, and in bytes of partial S
+constexpr int64_t kOneThinElems = int64_t(1) << 19, kOneThin4Elems = int64_t(1) << 22;
+constexpr int64_t kOnePartialBytes = 3500000, kOnePartialElems = int64_t(7) << 19, kOnePartialElems4 = int64_t(1) << 23;
 // Column vectors a lane owns (12 columns; fewer with several workers, whose steps take the registers of two more sets of rows, and of
 // rows that are read element by element), and steps whose loads are in flight: what 256 registers hold beside the lane's fp64
 // sums (rank 4: 96 of them).  LSTM-shaped set, rank 4, k_one_sweep: 12 columns, one step 69 us; 6 columns and two wavefronts to a

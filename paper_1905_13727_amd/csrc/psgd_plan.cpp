@@ -323,6 +323,29 @@ static void push_solve_tiles(psgd_plan* plan, int32_t mat, const OneMat& o) {
         plan->solve_tiles.push_back({mat, (int32_t)c, (int32_t)std::min<int64_t>(kBlock, o.n - c), 1, 8});
 }
 
+// Whether the one walk is also the faster one (the planner's own choice; `partial`: bytes of the partial S).  Us, two walks / one:
+//  - one worker, rows of 4 or 2 columns a lane that leave two thirds of the lanes idle: M is then read again from the caches faster than
+//    the idle lanes' instructions pass.  Rows of even lengths at every size: 20 of 500 x 250, rank 2 25.3 / 30.8; 20 of 2000 x 66 33.8 / 40.2; LSTM-shaped, rows
+//    of 130, 4.3 M elements 45 / 54; of 250, 4 M 34.3 / 37.4 (9 M 60.3 / 60.6; rows of 301, 5.2 M 46.4 / 40.6).  Multiples of 4 up to 4 M elements from rank 2 on: LSTM-shaped, rows of 100,
+//    1.2 M, rank 2 / 4 27.8 / 29.7 and 30.8 / 34.1; of 200, 3 M 31.4 / 32.9 and 34.2 / 37.1 (9 M 59.4 / 56.2 and 63.7 / 62.9).
+//  - partial S that weigh as much as what the second walk would read: one worker, rank 2, 6 of 256 x 2304 (3.5 M elements, 7 MB) 30.5 / 32.3, 20 of 128 x
+//    1152 28.1 / 31.1, 10 of 20 x 6144 22.1 / 28.7; rank 4, 10 of 100 x 3000 31.8 / 36.0, 900 x 2048 29.0 / 32.1, ResNet18-shaped, 1.8, 2.8 and 6.3 M 29.2 / 31.9, 32.7 / 35.1 and 44.5 / 46.4.
+//    Two workers, rank 4, 10 of 100 x 3000 (3 M elements, 24 MB) 41.0 / 45.5, 900 x 4095 50.6 / 57.0; but ResNet18-shaped, 2.8 M, 14 MB 46.0 / 42.5, 900 x 3000, 22 MB 44.6 / 42.8.
+static bool one_sweep_pays(const psgd_plan* plan, int64_t partial) {
+    const int64_t W = plan->workers, N = plan->sizes.n_mat_elems;
+    const int R = plan->rank;
+    const bool mean = W > 1;
+    int64_t thin2 = 0, thin4 = 0;
+    for (const OneMat& o : plan->one_mats) {
+        if (o.vec == 1 || (int64_t)o.m * 3 > (int64_t)kWave * one_nv(o.vec, mean) * o.vec) continue;
+        (o.vec == 2 ? thin2 : thin4) += (int64_t)o.n * o.m;
+    }
+    if (W == 1 && N >= kOneThinElems && (thin2 > N / 2 || (R >= 2 && N < kOneThin4Elems && thin2 + thin4 > N / 2))) return false;
+    if (partial <= kOnePartialBytes) return true;
+    if (W == 1) return (double)partial <= 1.9 * N || N >= (R <= 2 ? kOnePartialElems : kOnePartialElems4);
+    return partial <= 3 * W * N;
+}
+
 // Whether a plan's sets go through one walk over M per iteration instead of two (see k_one_sweep), and its tables.  Ranks up to
 // kOneMaxRank, every row short enough for the registers of one workgroup, partial sums of at most kOneMaxBytes.  Whole steps, us, two
 // walks / one: LSTM-shaped set, rank 4, 1 / 2 / 4 workers 171 / 337 / 718 and 157 / 287 / 632; rank 1, 2, 3 167, 169, 171 and 149, 154, 153;
@@ -410,7 +433,7 @@ static void build_one_sweep(psgd_plan* plan) {
     plan->one_s_doubles = round_up(sd, 32);
     plan->one_lds_bytes = (int32_t)lds;
     plan->one_bytes = (plan->one_s_doubles + gd) * (int64_t)sizeof(double);
-    plan->one_sweep = plan->one_bytes <= kOneMaxBytes;
+    plan->one_sweep = plan->one_bytes <= kOneMaxBytes && (tu.one_sweep > 0 || one_sweep_pays(plan, sd * (int64_t)sizeof(double)));
 }
 
 // psgd_step on a matrix-core plan in one walk over M that stores nothing but P (k_one_sweep_wide): one worker, bf16 gradients, rank 4, a

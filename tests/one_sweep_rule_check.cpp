@@ -57,7 +57,7 @@ static void check_many() {
     for (const Set& s : sets)
         for (int W : {1, 3}) {
             psgd_plan* plan = make(s, 2, W);
-            CHECK(plan->one_sweep && plan->one_bytes <= kOneMaxBytes);
+            CHECK(psgd_plan_set_tuning(plan, "one_sweep", 1) == PSGD_OK && plan->one_sweep && plan->one_bytes <= kOneMaxBytes);
             const size_t slots = (size_t)kResCUs * (kOneMaxWaves / plan->one_waves);
             std::vector<std::vector<int>> rows;
             for (const OneMat& o : plan->one_mats) rows.emplace_back(o.n, 0);
@@ -90,7 +90,7 @@ static void check_steps() {
         for (int rank : {1, 2, 3, 4})
             for (int W : {1, 2, 4, 8, 32}) {
                 psgd_plan* plan = make(s, rank, W);
-                CHECK(plan->one_sweep);
+                CHECK(psgd_plan_set_tuning(plan, "one_sweep", 1) == PSGD_OK && plan->one_sweep);
                 const int64_t slots = kResCUs * (kOneMaxWaves / plan->one_waves), rows = (plan->one_waves >> plan->one_mats[0].waves_log2) * kOneRows;
                 const int64_t n = plan->one_mats[0].n, at_two = (int64_t)s.size() * ((n + 2 * rows - 1) / (2 * rows));
                 const int64_t steps = at_two < (W >= 8 ? slots / 2 : (W == 1 && rank >= 3 ? slots / 4 : 0)) ? 1 : 2;
@@ -102,7 +102,32 @@ static void check_steps() {
             }
 }
 
+struct Line { Set s; int rank, W; bool taken; };
+
+// Each line of the rule from both sides; a plan that is asked for the one walk gets it on either, and the two walks' workspace is not
+// touched by the choice.
+static void check_lines(const std::vector<Line>& lines) {
+    for (const Line& c : lines) {
+        psgd_plan* plan = make(c.s, c.rank, c.W);
+        if (plan->one_sweep != c.taken) std::printf("%lld x %lld, %d matrices, rank %d, %d workers\n", (long long)c.s[0].rows, (long long)c.s[0].cols, (int)c.s.size(), c.rank, c.W);
+        CHECK(plan->one_sweep == c.taken);
+        const int64_t ws = plan->sizes.workspace_bytes;
+        CHECK(psgd_plan_set_tuning(plan, "one_sweep", 1) == PSGD_OK && plan->one_sweep && plan->sizes.workspace_bytes == ws);
+        CHECK(psgd_plan_set_tuning(plan, "one_sweep", 0) == PSGD_OK && !plan->one_sweep && plan->sizes.workspace_bytes == ws);
+        psgd_plan_destroy(plan);
+    }
+}
+
+// One worker: rows that leave two thirds of the lanes idle; partial sums as heavy as M.  Several: partial sums heavier than three words an element.
+static const std::vector<Line> kOneWorker = {
+    {many(20, {500, 250}), 2, 1, false}, {many(20, {500, 250}), 1, 1, false}, {many(20, {500, 258}), 2, 1, true}, {many(20, {500, 250}), 2, 2, true},
+    {many(1, {50000, 250}), 2, 1, false}, {many(4, {500, 250}), 2, 1, true}, {many(20, {2000, 100}), 2, 1, false}, {many(20, {2000, 100}), 1, 1, true},
+    {many(20, {3000, 100}), 2, 1, true}, {many(20, {2000, 101}), 2, 1, true}, {many(20, {500, 250}, 20, {500, 300}), 2, 1, true},
+    {many(10, {100, 3000}), 4, 1, false}, {many(10, {100, 3000}), 2, 1, false}, {many(10, {1000, 3000}), 4, 1, true}, {many(1, {900, 640}), 4, 1, true},
+    {many(10, {100, 3000}), 4, 2, false}, {many(10, {100, 3000}), 2, 2, true}, {many(10, {100, 3000}), 4, 3, true}};
+
 int main() {
+    check_lines(kOneWorker);
     check_many();
     check_steps();
     std::printf("OK\n");
