@@ -121,6 +121,7 @@ constexpr int kOneRows = 2;         // rows of a step
 constexpr int kOneStepWorkers = 8;  // from this many workers on small sets have groups of a single step (one_sweep_blocks)
 constexpr int64_t kOneMaxBytes = int64_t(64) << 20;   // plan-owned partial sums
 // Lines of one_sweep_pays, in elements of a worker, and in bytes of partial S
+constexpr int64_t kOneMeanWorkers = 8;
 constexpr int64_t kOneThinElems = int64_t(1) << 19, kOneThin4Elems = int64_t(1) << 22;
 constexpr int64_t kOnePartialBytes = 3500000, kOnePartialElems = int64_t(7) << 19, kOnePartialElems4 = int64_t(1) << 23;
 // Column vectors a lane owns (12 columns; fewer with several workers, whose steps take the registers of two more sets of rows, and of

@@ -331,16 +331,26 @@ static void push_solve_tiles(psgd_plan* plan, int32_t mat, const OneMat& o) {
 //  - partial S that weigh as much as what the second walk would read: one worker, rank 2, 6 of 256 x 2304 (3.5 M elements, 7 MB) 30.5 / 32.3, 20 of 128 x
 //    1152 28.1 / 31.1, 10 of 20 x 6144 22.1 / 28.7; rank 4, 10 of 100 x 3000 31.8 / 36.0, 900 x 2048 29.0 / 32.1, ResNet18-shaped, 1.8, 2.8 and 6.3 M 29.2 / 31.9, 32.7 / 35.1 and 44.5 / 46.4.
 //    Two workers, rank 4, 10 of 100 x 3000 (3 M elements, 24 MB) 41.0 / 45.5, 900 x 4095 50.6 / 57.0; but ResNet18-shaped, 2.8 M, 14 MB 46.0 / 42.5, 900 x 3000, 22 MB 44.6 / 42.8.
+//  - sets that otherwise take the mean first, beyond the memory-side cache: storing and reading the mean is 8 of 12 W + 8 bytes an element, so what the one walk saves
+//    is little with many workers, and rows of eight wavefronts, which wait for each other at every step, cost more.  Rank 2, ResNet18-shaped,
+//    8.5 M elements, 16 / 32 workers 512 / 525 and 1003 / 1051, 2.8 M, 32 workers 413 / 472; 40 of 256 x 1024, 16 / 32 579 / 593 and 1141 / 1189; 6 of 2000 x 4096, 4 / 16
+//    719 / 753 and 2584 / 2878, 110 of 100 x 4096, 8 workers 1289 / 1344; up to eight workers other rows 289 / 283 (ResNet18-shaped, 8), 320 / 311 (256 x 1024, 8).  Rows that do
+//    not fill the mean's chunks of 256 columns gain at any number: of 648, 16 workers 2137 / 2045, of 300, 16 / 32 441 / 396 and
+//    846 / 756, of 2052, 16 1092 / 1006.
 static bool one_sweep_pays(const psgd_plan* plan, int64_t partial) {
     const int64_t W = plan->workers, N = plan->sizes.n_mat_elems;
     const int R = plan->rank;
     const bool mean = W > 1;
-    int64_t thin2 = 0, thin4 = 0;
+    int64_t thin2 = 0, thin4 = 0, eight = 0, filled = 0;
     for (const OneMat& o : plan->one_mats) {
+        const int64_t chunks = ceil_div(o.m, kWave * o.vec);   // of the mean's walk: one column vector a lane
+        if ((int64_t)o.m * 16 >= chunks * kWave * o.vec * 15) filled += (int64_t)o.n * o.m;
+        if ((1 << o.waves_log2) == kOneMaxWaves) eight += (int64_t)o.n * o.m;
         if (o.vec == 1 || (int64_t)o.m * 3 > (int64_t)kWave * one_nv(o.vec, mean) * o.vec) continue;
         (o.vec == 2 ? thin2 : thin4) += (int64_t)o.n * o.m;
     }
     if (W == 1 && N >= kOneThinElems && (thin2 > N / 2 || (R >= 2 && N < kOneThin4Elems && thin2 + thin4 > N / 2))) return false;
+    if (plan->mean_first && W * N * (int64_t)sizeof(float) > kStreamHintBytes && filled > N / 2 && (W > kOneMeanWorkers || eight > N / 2)) return false;
     if (partial <= kOnePartialBytes) return true;
     if (W == 1) return (double)partial <= 1.9 * N || N >= (R <= 2 ? kOnePartialElems : kOnePartialElems4);
     return partial <= 3 * W * N;

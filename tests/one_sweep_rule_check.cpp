@@ -126,7 +126,15 @@ static const std::vector<Line> kOneWorker = {
     {many(10, {100, 3000}), 4, 1, false}, {many(10, {100, 3000}), 2, 1, false}, {many(10, {1000, 3000}), 4, 1, true}, {many(1, {900, 640}), 4, 1, true},
     {many(10, {100, 3000}), 4, 2, false}, {many(10, {100, 3000}), 2, 2, true}, {many(10, {100, 3000}), 4, 3, true}};
 
+// Sets that would take the mean first, beyond the memory-side cache: above eight workers, or rows of eight wavefronts, that fill the
+// mean's chunks of columns.
+static const std::vector<Line> kMeanFirst = {
+    {many(40, {256, 1024}), 2, 8, true}, {many(40, {256, 1024}), 2, 9, false}, {many(18, {256, 1024}), 2, 16, true}, {many(40, {256, 648}), 2, 16, true},
+    {many(40, {256, 1026}), 2, 16, true}, {many(12, {2000, 4096}), 2, 4, false}, {many(12, {2000, 2048}), 2, 4, true}, {many(12, {2000, 4096}), 2, 3, true},
+    {many(2, {2000, 4096}), 2, 4, true}, {many(4, {2000, 2052}), 2, 16, true}};
+
 int main() {
+    check_lines(kMeanFirst);
     check_lines(kOneWorker);
     check_many();
     check_steps();
