@@ -411,6 +411,7 @@ static void build_one_sweep(psgd_plan* plan) {
                 longest = std::max(longest, trial[i]);
             }
             const double us = one_sweep_span(plan, slots, trial, 6.0 * per_us) / per_us + partial / 6e6 + 0.025 * longest + (waves == 8 ? 2.0 : 0.0);
+            if (deals > 1 && partial / 2 > 0.99 * kOneMaxBytes) break;   // with the Gram matrices, more than the plan may hold
             if (blocks.empty() || us < best) {
                 best = us;
                 blocks = trial;

@@ -83,6 +83,18 @@ static void check_many() {
         }
 }
 
+// A finer division is not taken where its partial sums are more than the plan may hold and those of a coarser one are not.
+static void check_memory() {
+    Set s;
+    for (int i = 0; i < 24; ++i) s.insert(s.end(), {{1024, 1024}, {1024, 1024}, {1024, 1024}, {1024, 1024}, {4096, 1024}, {1024, 4096}});
+    s.push_back({50304, 1024});
+    for (int rank : {1, 2, 3, 4}) {
+        psgd_plan* plan = make(s, rank, 1);
+        CHECK(plan->one_sweep && plan->one_bytes <= kOneMaxBytes);
+        psgd_plan_destroy(plan);
+    }
+}
+
 // A group of wavefronts walks two steps at least; one where two would leave fewer blocks than half of the workgroups that the device
 // holds from eight workers on, than a quarter with one worker at ranks 3 and 4.
 static void check_steps() {
@@ -137,6 +149,7 @@ int main() {
     check_lines(kMeanFirst);
     check_lines(kOneWorker);
     check_many();
+    check_memory();
     check_steps();
     std::printf("OK\n");
     return 0;
