@@ -337,19 +337,24 @@ static void push_solve_tiles(psgd_plan* plan, int32_t mat, const OneMat& o) {
 //    719 / 753 and 2584 / 2878, 110 of 100 x 4096, 8 workers 1289 / 1344; up to eight workers other rows 289 / 283 (ResNet18-shaped, 8), 320 / 311 (256 x 1024, 8).  Rows that do
 //    not fill the mean's chunks of 256 columns gain at any number: of 648, 16 workers 2137 / 2045, of 300, 16 / 32 441 / 396 and
 //    846 / 756, of 2052, 16 1092 / 1006.
+//  - small sets of more than sixteen workers with most elements in rows that are not multiples of 4: a group's walk over all workers is a chain of
+//    narrow accesses.  32 workers, rank 2, five matrices of 0.2 M elements 67 / 89, 20 of 0.4 M 114 / 124, 40 of 1 M 289 / 314 (16 workers 47 / 50, 69.9 / 68.9 and
+//    139 / 147); but 24 of 9 M 1559 / 1442, and in rows of multiples of 4, 1.1 and 1.3 M, 288 / 266 and 175 / 150.
 static bool one_sweep_pays(const psgd_plan* plan, int64_t partial) {
     const int64_t W = plan->workers, N = plan->sizes.n_mat_elems;
     const int R = plan->rank;
     const bool mean = W > 1;
-    int64_t thin2 = 0, thin4 = 0, eight = 0, filled = 0;
+    int64_t thin2 = 0, thin4 = 0, eight = 0, filled = 0, narrow = 0;
     for (const OneMat& o : plan->one_mats) {
         const int64_t chunks = ceil_div(o.m, kWave * o.vec);   // of the mean's walk: one column vector a lane
         if ((int64_t)o.m * 16 >= chunks * kWave * o.vec * 15) filled += (int64_t)o.n * o.m;
         if ((1 << o.waves_log2) == kOneMaxWaves) eight += (int64_t)o.n * o.m;
+        if (o.vec != 4) narrow += (int64_t)o.n * o.m;
         if (o.vec == 1 || (int64_t)o.m * 3 > (int64_t)kWave * one_nv(o.vec, mean) * o.vec) continue;
         (o.vec == 2 ? thin2 : thin4) += (int64_t)o.n * o.m;
     }
     if (W == 1 && N >= kOneThinElems && (thin2 > N / 2 || (R >= 2 && N < kOneThin4Elems && thin2 + thin4 > N / 2))) return false;
+    if (W > 16 && N < kMeanElemsPerWorker * W && narrow > N / 2) return false;
     if (plan->mean_first && W * N * (int64_t)sizeof(float) > kStreamHintBytes && filled > N / 2 && (W > kOneMeanWorkers || eight > N / 2)) return false;
     if (partial <= kOnePartialBytes) return true;
     if (W == 1) return (double)partial <= 1.9 * N || N >= (R <= 2 ? kOnePartialElems : kOnePartialElems4);

@@ -145,7 +145,13 @@ static const std::vector<Line> kMeanFirst = {
     {many(40, {256, 1026}), 2, 16, true}, {many(12, {2000, 4096}), 2, 4, false}, {many(12, {2000, 2048}), 2, 4, true}, {many(12, {2000, 4096}), 2, 3, true},
     {many(2, {2000, 4096}), 2, 4, true}, {many(4, {2000, 2052}), 2, 16, true}};
 
+// Small sets of many workers in narrow rows.
+static const std::vector<Line> kNarrow = {
+    {many(5, {200, 201}), 2, 17, false}, {many(5, {200, 201}), 2, 16, true}, {many(5, {200, 200}), 2, 32, true}, {many(5, {700, 601}), 2, 32, true},
+    {many(5, {700, 601}), 2, 33, false}};
+
 int main() {
+    check_lines(kNarrow);
     check_lines(kMeanFirst);
     check_lines(kOneWorker);
     check_many();
