@@ -421,6 +421,8 @@ def main():
     mean = plan.worker_mean()[0]
     one_sweep = plan.one_sweep()[0] and not resident and not sparse
     unstored = one_sweep and plan.path() == "matrix cores"
+    if one_sweep and args.iterations > 1 and plan.worker_mean()[1]:
+        one_sweep = False              # several iterations go over the stored mean, in two walks each
     if unstored and (args.update == "fused" or args.iterations > 1):
         one_sweep = unstored = False   # those calls of a matrix-core plan keep M
     kernel_bytes, stream_bytes = byte_models(s, W, gsz, osz, mean, args.update == "fused", args.iterations, one_sweep, unstored)

@@ -20,8 +20,8 @@
  * All data buffers are DEVICE pointers owned by the caller (allocate them with
  * any allocator; the tests use PyTorch).  The library owns only the plan, its
  * small device-side descriptor tables and, for some plans, partial sums of at
- * most 64 MiB (psgd_plan_one_sweep) or one buffer of N floats
- * (psgd_plan_worker_mean).  No entry point
+ * most 64 MiB (psgd_plan_one_sweep), one buffer of N floats
+ * (psgd_plan_worker_mean), or both.  No entry point
  * throws or aborts; every failure is a psgd_status.
  *
  * Flat layout (all offsets in elements, reported by psgd_plan_sizes /
@@ -182,9 +182,9 @@ PSGD_API psgd_status psgd_plan_set_tuning(psgd_plan* plan, const char* key, int6
  * Everything is enqueued on hip_stream; the call does not synchronise, allocate
  * or read back, except that a plan's first GPU call allocates and uploads its
  * descriptor tables (one hipMalloc, one synchronous copy; where one_sweep holds, a
- * second hipMalloc for its partial sums, without which M is walked twice; else, where
- * worker_mean holds, a second hipMalloc of 4 N bytes for the mean over the workers of
- * M, without which, should it fail, each worker's M is multiplied by itself).
+ * second hipMalloc for its partial sums, without which M is walked twice; where worker_mean
+ * holds instead, or several iterations go over the mean (psgd_step_iterations), a hipMalloc of
+ * 4 N bytes for the mean over the workers of M, without which each worker's M is multiplied by itself).
  * Vector-shaped tensors are not touched by this call. */
 PSGD_API psgd_status psgd_compress(psgd_plan* plan, const void* grad, float* err, float* q, float* p,
                           void* workspace, void* hip_stream);
@@ -261,8 +261,10 @@ PSGD_API psgd_status psgd_step_static(psgd_plan* plan, const void* grad, float* 
 /* One whole step with `iterations` subspace iterations (Appendix G.7, "best-approximation PowerSGD"; Table 2):
  * the same quantities as psgd_compress, iterations - 1 calls of psgd_iterate, psgd_decompress.  iterations = 1 is
  * psgd_step.  A plan in resident mode (see psgd_step) keeps M on chip through all the iterations: one kernel, each
- * element of g, e read once and of e', Delta' written once whatever the count; otherwise the calls above in
- * sequence.  Start it from a fresh random Q for the variants without warm start.
+ * element of g, e read once and of e', Delta' written once whatever the count.  A plan that takes the one walk over M
+ * (one_sweep) but would otherwise take the mean first (worker_mean), with more than 20 * 2^20 elements of all workers, stores the mean over
+ * the workers and iterates on that (psgd_plan_worker_mean gives the memory; the values differ from the calls' by rounding).
+ * Otherwise the calls above in sequence.  Start it from a fresh random Q for the variants without warm start.
  * Errors: PSGD_EINVAL also for iterations outside 1 .. 64. */
 PSGD_API psgd_status psgd_step_iterations(psgd_plan* plan, const void* grad, float* err, float* q, float* p,
                                           void* out, void* workspace, void* hip_stream, int32_t iterations);
@@ -382,7 +384,7 @@ PSGD_API psgd_status psgd_plan_worker_mean(const psgd_plan* plan, int32_t* taken
  * from those of the two walks by rounding only), and the device memory the plan holds for the partial sums, which no field of
  * psgd_sizes counts.  Before the plan's first GPU call both are the planner's choice, after it what holds: 0 and 0 where the
  * device does not hold the one-launch orthogonalisation or the memory could not be had.  With several workers the products are
- * then of the mean over the workers (psgd_plan_worker_mean says 1, and 0 bytes).  A plan in resident mode uses it in
+ * then of the mean over the workers (psgd_plan_worker_mean says 1, and 0 bytes unless several iterations go over the stored mean).  A plan in resident mode uses it in
  * psgd_compress and psgd_iterate, a matrix-core plan in psgd_step alone (with 0 bytes held, and as the two calls where out is not
  * aligned to 16 bytes or overlaps grad).  Either output may be NULL; PSGD_EINVAL for a NULL plan. */
 PSGD_API psgd_status psgd_plan_one_sweep(const psgd_plan* plan, int32_t* taken, int64_t* bytes);

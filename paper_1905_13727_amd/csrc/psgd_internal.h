@@ -120,6 +120,12 @@ constexpr int kOneMaxWaves = 8;     // wavefronts of a workgroup, and of a row
 constexpr int kOneRows = 2;         // rows of a step
 constexpr int kOneStepWorkers = 8;  // from this many workers on small sets have groups of a single step (one_sweep_blocks)
 constexpr int64_t kOneMaxBytes = int64_t(64) << 20;   // plan-owned partial sums
+// psgd_step_iterations on a plan that takes the one walk: above this many elements of all workers the mean is stored and every further
+// iteration reads it twice (8 bytes an element) instead of every worker's M once (4 W).  Whole calls, us, mean / one walk: 4 workers,
+// two and four iterations, ResNet18-shaped, 1.1 M elements 60 / 52 and 106 / 100, 2.8 M 83 / 79 and 138 / 139, 8.5 M 187 / 189 and 272 / 294, LSTM-shaped, rows of 648,
+// 31.6 M 609 / 645 and 781 / 880, rows of 300, 5.2 M (20.6 M in all) 156 / 131 and 229 / 191; 40 of 256 x 1024 187 / 195 and 269 / 276; 8 workers, three iterations, ResNet18-shaped 1.1 M 111 / 103,
+// 2.8 M 190 / 200, 8.5 M 363 / 444; 16 workers, four, 1.1 M 218 / 213, 2.8 M 333 / 382, rows of 300 540 / 624.
+constexpr int64_t kIterMeanElems = int64_t(20) << 20;
 // Lines of one_sweep_pays, in elements of a worker, and in bytes of partial S
 constexpr int64_t kOneMeanWorkers = 8;
 constexpr int64_t kOneThinElems = int64_t(1) << 19, kOneThin4Elems = int64_t(1) << 22;
@@ -278,6 +284,7 @@ struct psgd_plan {
     // one walk over M per iteration
     bool one_sweep = false;                 // taken (after the upload: the partial sums' memory is there)
     bool one_wide = false;                  // matrix-core plans: psgd_step's own walk (k_one_sweep_wide)
+    bool iter_mean = false;                 // psgd_step_iterations, more than one: two walks over the mean, held in mbar, instead
     int32_t one_waves = 0;                  // wavefronts of a workgroup
     int32_t one_lds_bytes = 0;
     int64_t one_s_doubles = 0, one_bytes = 0;   // partial S, and partial S and Gram matrices: plan-owned
@@ -334,6 +341,8 @@ psgd_status launch_compress(psgd_plan* plan, const void* grad, float* err, float
 psgd_status launch_decompress(psgd_plan* plan, const float* p, const float* q, float* err,
                               const void* grad, void* out, void* workspace, void* stream,
                               const UpdateArgs& upd = UpdateArgs());
+// psgd_compress in two walks over M, on a plan whose tables are on the device; grad = nullptr: M is what the call before left
+psgd_status launch_two_walks(psgd_plan* plan, const void* grad, float* err, float* q, float* p, void* workspace, void* stream, bool add);
 // P and the partial S and Gram matrices, then P_hat and Q from them (one walk over M)
 psgd_status launch_one_sweep(psgd_plan* plan, const void* grad, float* err, const float* q, float* p, void* stream, bool add);
 psgd_status launch_solve(psgd_plan* plan, float* q, float* p, const double* spart, const double* gpart, void* stream);

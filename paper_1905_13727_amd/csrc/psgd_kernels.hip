@@ -1262,7 +1262,7 @@ psgd_status upload_tables(psgd_plan* plan) {
         }
     }
     // the mean over the workers of M; without it every worker's M is multiplied by itself
-    if (plan->mean_first && !plan->hr && !plan->one_sweep && plan->gram_fused &&
+    if (plan->mean_first && !plan->hr && (!plan->one_sweep || plan->iter_mean) && plan->gram_fused &&
         hipMalloc(reinterpret_cast<void**>(&plan->mbar), (size_t)plan->sizes.n_mat_elems * sizeof(float)) != hipSuccess) {
         plan->mbar = nullptr;
         (void)hipGetLastError();
@@ -1474,18 +1474,13 @@ psgd_status launch_compress(psgd_plan* plan, const void* grad, float* err, float
                             void* stream, bool add) {
     psgd_status st = check_ready(plan);
     if (st != PSGD_OK) return st;
-    const bool again = !grad;
-    if (!grad) grad = err;   // not dereferenced
-    if (plan->hr) return hr_compress(plan, grad, err, q, p, workspace, stream, add);
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    float* ws = static_cast<float*>(workspace);
-    const void* g = grad;
+    if (plan->hr) return hr_compress(plan, grad ? grad : err, err, q, p, workspace, stream, add);   // nothing added: not dereferenced
     if (plan->mats.empty()) return PSGD_OK;
-
-    PSGD_MARK(0);
-    plan->compress_marked = plan->profiling;
     if (plan->one_sweep) {
-        st = launch_one_sweep(plan, g, err, q, p, stream, add);
+        hipStream_t s = static_cast<hipStream_t>(stream);
+        PSGD_MARK(0);
+        plan->compress_marked = plan->profiling;
+        st = launch_one_sweep(plan, grad ? grad : err, err, q, p, stream, add);
         if (st != PSGD_OK) return st;
         PSGD_MARK(1);
         st = launch_solve(plan, q, p, plan->one_part, plan->one_part + plan->one_s_doubles, stream);
@@ -1493,6 +1488,18 @@ psgd_status launch_compress(psgd_plan* plan, const void* grad, float* err, float
         for (int i = 2; i <= 4; ++i) PSGD_MARK(i);   // no second walk, no reduction of Q
         return PSGD_OK;
     }
+    return launch_two_walks(plan, grad, err, q, p, workspace, stream, add);
+}
+
+psgd_status launch_two_walks(psgd_plan* plan, const void* grad, float* err, float* q, float* p, void* workspace,
+                             void* stream, bool add) {
+    psgd_status st = PSGD_OK;
+    const bool again = !grad;
+    const void* g = grad ? grad : err;   // nothing added: not dereferenced
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    float* ws = static_cast<float*>(workspace);
+    PSGD_MARK(0);
+    plan->compress_marked = plan->profiling;
     // Several workers: the products are taken of the mean over the workers.  It lives in plan-owned memory, which is
     // no new restriction where gram_fused holds (calls of one plan must not overlap there); elsewhere, and where that
     // memory could not be had, every worker's M is multiplied by itself.

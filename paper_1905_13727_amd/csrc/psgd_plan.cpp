@@ -537,7 +537,7 @@ psgd_status build_tables(psgd_plan* plan) {
             if (d.m % 4 != 0 || d.m > kHrMaxCols || d.n > kHrMaxRows) hr_low = false;
     }
     plan->hr = plan->rank > kValuMaxRank || hr_low;
-    plan->one_sweep = plan->one_wide = false;
+    plan->one_sweep = plan->one_wide = plan->iter_mean = false;
     if (plan->hr) return build_hr_tables(plan);
     if (plan->out_dtype != PSGD_F32 && tu.k4_nv != 1) return PSGD_EINVAL;   // bf16 output: one column vector per lane
     if (tu.k1_rows < 0 || tu.k3_rows < 0 || tu.k4_rows < 0 || tu.k1_nv < 1 ||
@@ -676,6 +676,7 @@ psgd_status build_tables(psgd_plan* plan) {
     plan->stream_hints = tu.stream_hints < 0 ? W * plan->sizes.n_mat_elems * (int64_t)sizeof(float) > kStreamHintBytes
                                              : tu.stream_hints != 0;
     build_one_sweep(plan);
+    plan->iter_mean = plan->one_sweep && tu.one_sweep < 0 && plan->mean_first && W * plan->sizes.n_mat_elems > kIterMeanElems;
     build_resident(plan, (int64_t)kResCUs * kResBlocksPerCU);
     plan->sizes.workspace_bytes =
         std::max<int64_t>(plan->sizes.workspace_bytes, plan->res_ws_floats * (int64_t)sizeof(float));
@@ -1007,9 +1008,9 @@ psgd_status psgd_plan_path(const psgd_plan* plan, int32_t* path) {
 
 psgd_status psgd_plan_worker_mean(const psgd_plan* plan, int32_t* taken, int64_t* bytes) {
     if (!plan) return PSGD_EINVAL;
-    if (plan->one_sweep) {   // the mean is formed as M is walked, and held nowhere
+    if (plan->one_sweep) {   // the mean is formed as M is walked; held for several iterations in one call alone
         if (taken) *taken = plan->workers > 1 ? 1 : 0;
-        if (bytes) *bytes = 0;
+        if (bytes) *bytes = (plan->uploaded ? plan->mbar != nullptr : plan->iter_mean) ? plan->sizes.n_mat_elems * (int64_t)sizeof(float) : 0;
         return PSGD_OK;
     }
     const bool held = plan->uploaded ? plan->mbar != nullptr : plan->mean_first;
@@ -1121,6 +1122,7 @@ psgd_status psgd_step_iterations(psgd_plan* plan, const void* grad, float* err, 
     if (!plan || bad_ptrs(grad, err, q, p, workspace) || !out || iterations < 1 || iterations > 64) return PSGD_EINVAL;
     if (plan->resident_ok) return launch_resident_step(plan, grad, err, q, p, out, workspace, hip_stream, UpdateArgs(), iterations);
     if (iterations == 1) return psgd_step(plan, grad, err, q, p, out, workspace, hip_stream);
+    if (plan->iter_mean) return launch_resident_step(plan, grad, err, q, p, out, workspace, hip_stream, UpdateArgs(), iterations);
     psgd_status st = launch_compress(plan, grad, err, q, p, workspace, hip_stream);
     for (int32_t it = 1; it < iterations && st == PSGD_OK; ++it)
         st = launch_compress(plan, nullptr, err, q, p, workspace, hip_stream, false);

@@ -637,9 +637,10 @@ psgd_status resident_check_device(psgd_plan* plan) {
 // The step on the streaming kernels: what a plan without (or no longer with) a resident tiling runs.
 static psgd_status streamed_step(psgd_plan* plan, const void* grad, float* err, float* q, float* p, void* out,
                                  void* workspace, void* stream, const UpdateArgs& upd, int iterations) {
-    psgd_status st = launch_compress(plan, grad, err, q, p, workspace, stream);
-    for (int it = 1; it < iterations && st == PSGD_OK; ++it)
-        st = launch_compress(plan, nullptr, err, q, p, workspace, stream, false);
+    const bool on_mean = iterations > 1 && plan->iter_mean && plan->mbar && plan->gram_fused;
+    auto compress = on_mean ? launch_two_walks : launch_compress;
+    psgd_status st = compress(plan, grad, err, q, p, workspace, stream, true);
+    for (int it = 1; it < iterations && st == PSGD_OK; ++it) st = compress(plan, nullptr, err, q, p, workspace, stream, false);
     if (st != PSGD_OK) return st;
     return launch_decompress(plan, p, q, err, grad, out, workspace, stream, upd);
 }

@@ -150,7 +150,25 @@ static const std::vector<Line> kNarrow = {
     {many(5, {200, 201}), 2, 17, false}, {many(5, {200, 201}), 2, 16, true}, {many(5, {200, 200}), 2, 32, true}, {many(5, {700, 601}), 2, 32, true},
     {many(5, {700, 601}), 2, 33, false}};
 
+// Several iterations in one call go over the stored mean: where the mean would be taken first without the one walk, above 20 * 2^20
+// elements of all workers.  The memory for it is reported, and none where it is not used.
+static void check_iterations() {
+    struct { Set s; int W; bool one, mean; } cases[] = {{many(1, {1200, 1200}), 16, true, true}, {many(1, {1200, 1000}), 16, true, false}, {many(1, {1024, 1280}), 16, true, false}, {many(1, {1028, 1280}), 16, true, true},
+                                                        {many(5, {1200, 1200}), 3, true, false}, {many(5, {1200, 1200}), 4, true, true}, {many(5, {1200, 1201}), 4, true, false}};
+    for (auto& c : cases) {
+        psgd_plan* plan = make(c.s, 2, c.W);
+        CHECK(plan->one_sweep == c.one && plan->iter_mean == c.mean);
+        int32_t taken = -1;
+        int64_t bytes = -1;
+        CHECK(psgd_plan_worker_mean(plan, &taken, &bytes) == PSGD_OK && taken == 1 && bytes == (c.mean ? plan->sizes.n_mat_elems * 4 : 0));
+        for (int64_t v : {0, 1}) CHECK(psgd_plan_set_tuning(plan, "one_sweep", v) == PSGD_OK && !plan->iter_mean);
+        CHECK(psgd_plan_set_tuning(plan, "one_sweep", -1) == PSGD_OK && plan->iter_mean == c.mean);
+        psgd_plan_destroy(plan);
+    }
+}
+
 int main() {
+    check_iterations();
     check_lines(kNarrow);
     check_lines(kMeanFirst);
     check_lines(kOneWorker);

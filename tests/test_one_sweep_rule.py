@@ -63,3 +63,40 @@ def test_many_matrices_equal_the_two_walks(shapes, workers):
         for key, at, size in (("out", off, n * m), ("p", p_off, n * r), ("q", q_off, m * r)):
             a, b = got[0][1][key][at: at + size], got[1][1][key][at: at + size]
             assert torch.isfinite(a).all() and float((a - b).norm()) <= 2e-5 * float(b.norm()), (t, key)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("bf16", [False, True])
+def test_several_iterations_go_over_the_stored_mean(bf16):
+    """One call of two and of three iterations on a plan that takes the one walk: bit for bit what the two walks over the mean give, and
+    within rounding what the calls apart give (fp32 sums of 1200 products in other orders, times the condition of random panels); one
+    iteration, and the calls apart, are the one walk."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    stream = torch.cuda.current_stream().cuda_stream
+    shapes, workers = [(1200, 1200)], 16
+    plan, walks, never = _plans(shapes, 2, workers, ({}, {"one_sweep": 0}, {"one_sweep": 1}), bf16)
+
+    def run(pl, its, split=False):
+        x = _state(plan, workers, 7, bf16)
+        for _ in range(2):
+            if split:
+                pl.compress(x["grad"], x["err"], x["q"], x["p"], x["ws"], stream)
+                for _ in range(its - 1):
+                    pl.iterate(x["err"], x["q"], x["p"], x["ws"], stream)
+                pl.decompress(x["p"], x["q"], x["err"], x["grad"], x["out"], x["ws"], stream)
+            elif its == 1:
+                pl.step(x["grad"], x["err"], x["q"], x["p"], x["out"], x["ws"], stream)
+            else:
+                pl.step_iterations(x["grad"], x["err"], x["q"], x["p"], x["out"], x["ws"], its, stream)
+        pl.check(stream)
+        return [x[k] for k in ("err", "q", "p", "out")]
+
+    for its in (2, 3):
+        a, b, c, d = run(plan, its), run(walks, its), run(plan, its, split=True), run(never, its, split=True)
+        assert all(torch.equal(x, y) for x, y in zip(a, b))
+        assert all(torch.equal(x, y) for x, y in zip(c, d))
+        assert all(float((x - y).norm()) <= 2e-5 * float(y.norm()) for x, y in zip(a, c))
+    assert all(torch.equal(x, y) for x, y in zip(run(plan, 1), run(never, 1)))
+    assert plan.one_sweep()[0] and plan.worker_mean() == (True, 4 * 1200 * 1200) and walks.worker_mean() == (True, 4 * 1200 * 1200)
+    assert never.worker_mean() == (True, 0)
