@@ -119,6 +119,7 @@ constexpr int kOneMaxRank = 4;
 constexpr int kOneMaxWaves = 8;     // wavefronts of a workgroup, and of a row
 constexpr int kOneRows = 2;         // rows of a step
 constexpr int kOneStepWorkers = 8;  // from this many workers on small sets have groups of a single step (one_sweep_blocks)
+constexpr int64_t kOneStepElems = int64_t(1) << 19;
 constexpr int64_t kOneMaxBytes = int64_t(64) << 20;   // plan-owned partial sums
 // psgd_step_iterations on a plan that takes the one walk: above this many elements of all workers the mean is stored and every further
 // iteration reads it twice (8 bytes an element) instead of every worker's M once (4 W).  Whole calls, us, mean / one walk: 4 workers,

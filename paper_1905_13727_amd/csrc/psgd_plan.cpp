@@ -262,13 +262,14 @@ static int64_t one_row_cost(const OneMat& o, bool mean) {
 // was never faster), and within that as little in the largest as can be.  With several, the hardware deals them out, largest first.
 //
 // A group of wavefronts walks two steps at least: every block leaves a partial S behind.  One where that makes so few blocks that much
-// of the chip is idle (below half of the slots from eight workers on, whose steps are long, below a quarter with one worker at ranks
-// whose ring holds one step).  Whole steps, us, two steps / one: 32 workers, rank 2, five matrices of 0.2 M elements 128 / 89, 20 of 0.4 M 167 / 124; 8 workers, the same
-// 40 / 30 and 52 / 43, but 8 of 512 x 320 (256 blocks at two steps) 45.4 / 46.6; one worker, rank 4, 900 x 640 (57) 24.2 / 22.5, but 12 of 300 x 400 (228) 25.2 / 27.5,
+// of the chip is idle (below half of the slots on sets under 2^19 elements from eight workers on, whose steps are long, below a quarter
+// with one worker at ranks whose ring holds one step).  Whole steps, us, two steps / one: 32 workers, rank 2, five matrices of 0.2 M elements 128 / 89, 20 of 0.4 M 167 / 124; 8 workers, the same
+// 40 / 30 and 52 / 43, but ResNet18-shaped of 0.9 M, 8 / 16 workers 53.5 / 57.7 and 92 / 104; one worker, rank 4, 900 x 640 (57) 24.2 / 22.5, but 12 of 300 x 400 (228) 25.2 / 27.5,
 // 8 of 512 x 320 24.4 / 27.4, 900 x 2048 32.1 / 36.4.
 static void one_sweep_blocks(const psgd_plan* plan, int waves, int64_t slots, int deals, std::vector<int64_t>* blocks) {
     const bool mean = plan->workers > 1;
-    const int64_t few = plan->workers >= kOneStepWorkers ? slots / 2 : (one_depth(plan->rank, mean) == 1 ? slots / 4 : 0);
+    const bool many = plan->workers >= kOneStepWorkers && plan->sizes.n_mat_elems < kOneStepElems;
+    const int64_t few = many ? slots / 2 : (one_depth(plan->rank, mean) == 1 ? slots / 4 : 0);
     int64_t steps = 2, at_two = 0;
     for (const OneMat& o : plan->one_mats) at_two += ceil_div(o.n, (waves >> o.waves_log2) * kOneRows * 2);
     if (at_two < few) steps = 1;

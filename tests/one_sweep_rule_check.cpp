@@ -96,16 +96,16 @@ static void check_memory() {
 }
 
 // A group of wavefronts walks two steps at least; one where two would leave fewer blocks than half of the workgroups that the device
-// holds from eight workers on, than a quarter with one worker at ranks 3 and 4.
+// holds on sets under 2^19 elements from eight workers on, than a quarter with one worker at ranks 3 and 4.
 static void check_steps() {
-    for (const Set& s : {many(1, {37, 90}), many(3, {100, 200}), many(11, {160, 300}), many(15, {400, 300}), many(8, {512, 320}), many(20, {400, 300})})
+    for (const Set& s : {many(1, {37, 90}), many(3, {100, 200}), many(3, {128, 1500}), many(11, {160, 300}), many(15, {400, 300}), many(8, {512, 320}), many(20, {400, 300})})
         for (int rank : {1, 2, 3, 4})
             for (int W : {1, 2, 4, 8, 32}) {
                 psgd_plan* plan = make(s, rank, W);
                 CHECK(psgd_plan_set_tuning(plan, "one_sweep", 1) == PSGD_OK && plan->one_sweep);
                 const int64_t slots = kResCUs * (kOneMaxWaves / plan->one_waves), rows = (plan->one_waves >> plan->one_mats[0].waves_log2) * kOneRows;
                 const int64_t n = plan->one_mats[0].n, at_two = (int64_t)s.size() * ((n + 2 * rows - 1) / (2 * rows));
-                const int64_t steps = at_two < (W >= 8 ? slots / 2 : (W == 1 && rank >= 3 ? slots / 4 : 0)) ? 1 : 2;
+                const int64_t steps = at_two < (W >= 8 && plan->sizes.n_mat_elems < kOneStepElems ? slots / 2 : (W == 1 && rank >= 3 ? slots / 4 : 0)) ? 1 : 2;
                 for (const OneMat& o : plan->one_mats) {
                     CHECK(o.n_blocks <= (n + steps * rows - 1) / (steps * rows));
                     if (s.size() <= 3) CHECK(o.n_blocks == (n + steps * rows - 1) / (steps * rows));
