@@ -461,6 +461,8 @@ static void build_one_sweep(psgd_plan* plan) {
 // 465 / 398, 706 / 506, 924 / 678, 1083 / 771, 1104 / 894 and 1367 / 1121; 200 matrices of 500 x 1000 678 / 465; 300000 x 300 772 / 563; 21000 x 4096
 // 448 / 382.  Rows that take all eight wavefronts, which then wait for each other at every row, lose where they are all there is (6
 // of 2000 x 8192 470 / 532, 110 of 100 x 8192 417 / 511) and are a third of the transformers': the line is at half of the elements.
+// Rows that leave three quarters of a wavefront's 1024 columns empty lose too where they are most (1000000 x 100 897 / 980, 3000000 x 32 2021 /
+// 2578, 2200 of 200 x 200 637 / 703, 600000 x 160 753 / 754; 400000 x 256 625 / 549, 1000 of 300 x 300 672 / 558).
 // Above rank 4 a row of 8192 and its S do not fit a compute unit's registers.
 static void build_one_wide(psgd_plan* plan) {
     plan->one_wide = false;
@@ -474,13 +476,14 @@ static void build_one_wide(psgd_plan* plan) {
         (tu.one_sweep < 0 && (others || !plan->stream_hints)))
         return;
     const int64_t osz = plan->out_dtype == PSGD_BF16 ? 2 : 4;
-    int64_t total = 0, eight = 0;
+    int64_t total = 0, eight = 0, thin = 0;
     for (const MatDesc& d : plan->mats) {
         if (d.m > (int64_t)kOneMaxWaves * kWave * kOneWideNV * 4 || (int64_t)d.n * osz < (int64_t)d.r * (int64_t)sizeof(double)) return;
         total += (int64_t)d.n * d.m;
         if (d.m > (int64_t)kOneMaxWaves / 2 * kWave * kOneWideNV * 4) eight += (int64_t)d.n * d.m;
+        if (d.m < kWave * kOneWideNV) thin += (int64_t)d.n * d.m;
     }
-    if (eight > total / 2 && tu.one_sweep < 0) return;
+    if ((eight > total / 2 || thin > total / 2) && tu.one_sweep < 0) return;
     // Four blocks for every compute unit, dealt largest first: what one block too many costs in the last generation is a quarter of a
     // compute unit's share, and the partial S (70 MB of the 24-layer set's 26 GB) are little.
     const int64_t elems = ceil_div(total, (int64_t)kResCUs * 4);

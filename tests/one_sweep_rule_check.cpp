@@ -167,7 +167,20 @@ static void check_iterations() {
     }
 }
 
+// The walk of the matrix-core plans: not where most elements lie in rows that leave three quarters of a wavefront's columns empty.
+static void check_wide_lines() {
+    struct { Set s; bool taken; } cases[] = {{many(1, {400000, 256}), true}, {many(1, {400000, 252}), false}, {many(2200, {200, 200}), false},
+                                             {many(1, {300000, 200}, 1, {100000, 1024}), true}, {many(1, {600000, 200}, 1, {100000, 1024}), false}};
+    for (auto& c : cases) {
+        psgd_plan* plan = make(c.s, 4, 1, PSGD_BF16, PSGD_BF16);
+        CHECK(plan->hr && plan->one_wide == c.taken);
+        CHECK(psgd_plan_set_tuning(plan, "one_sweep", 1) == PSGD_OK && plan->one_wide);
+        psgd_plan_destroy(plan);
+    }
+}
+
 int main() {
+    check_wide_lines();
     check_iterations();
     check_lines(kNarrow);
     check_lines(kMeanFirst);
