@@ -532,7 +532,8 @@ psgd_status build_tables(psgd_plan* plan) {
     // those kernels take (24-layer transformer-shaped set, ms per step, streaming / matrix cores: rank 2: 5.17 / 5.15,
     // rank 4: 5.28 / 5.17, rank 8: 6.43 / 5.19).
     const bool bf16 = plan->grad_dtype != PSGD_F32 || plan->out_dtype != PSGD_F32;
-    if (tu.bf16_valu < -1 || tu.bf16_valu > 1 || tu.worker_mean < -1 || tu.worker_mean > 1) return PSGD_EINVAL;
+    if (tu.bf16_valu < -1 || tu.bf16_valu > 1 || tu.worker_mean < -1 || tu.worker_mean > 1 || tu.one_sweep < -1 || tu.one_sweep > 1)
+        return PSGD_EINVAL;
     bool hr_low = bf16 && tu.bf16_valu == 0;
     if (bf16 && tu.bf16_valu < 0 && plan->rank >= 4 &&
         plan->workers * plan->sizes.n_mat_elems * (int64_t)sizeof(float) > kStreamHintBytes) {
@@ -549,7 +550,7 @@ psgd_status build_tables(psgd_plan* plan) {
         tu.k4_nv > kMaxVecPerLaneK3 || tu.res_rows < 0 || tu.res_rows > kResRows || tu.resident < 0 || tu.resident > 2 ||
         tu.res_spin < 1 || tu.res_spin > (int64_t(1) << 30) || tu.res_max_blocks < 0 || tu.res_max_blocks > 65535 ||
         tu.stream_hints < -1 || tu.stream_hints > 1 || tu.xcd_order < -1 || tu.gram_fused < -1 || tu.gram_fused > 2 || tu.gram_spin < 1 ||
-        tu.gram_spin > (1 << 24) || tu.ortho_rows < 0 || tu.ortho_rows > kOrthoMaxRows || tu.one_sweep < -1 || tu.one_sweep > 1)
+        tu.gram_spin > (1 << 24) || tu.ortho_rows < 0 || tu.ortho_rows > kOrthoMaxRows)
         return PSGD_EINVAL;
     const size_t nm = plan->mats.size();
     // k_ef_right and k_left address the rows of a wavefront's strip (a quarter of the tile's rows) with 31-bit

@@ -179,7 +179,19 @@ static void check_wide_lines() {
     }
 }
 
+// one_sweep out of its range is refused whatever kernels the plan runs, and leaves the plan as it was.
+static void check_range() {
+    for (int rank : {2, 4, 16}) {
+        psgd_plan* plan = make(many(1, {50304, 2048}), rank, 1, PSGD_BF16, PSGD_BF16);
+        const bool wide = plan->one_wide, one = plan->one_sweep;
+        for (int64_t bad : {-9, -2, 2, 7}) CHECK(psgd_plan_set_tuning(plan, "one_sweep", bad) == PSGD_EINVAL && plan->one_wide == wide && plan->one_sweep == one);
+        CHECK(psgd_plan_set_tuning(plan, "xcd_order", 1) == PSGD_OK && plan->one_wide == wide && plan->one_sweep == one);
+        psgd_plan_destroy(plan);
+    }
+}
+
 int main() {
+    check_range();
     check_wide_lines();
     check_iterations();
     check_lines(kNarrow);
