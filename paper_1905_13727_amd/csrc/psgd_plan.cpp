@@ -473,7 +473,7 @@ static void build_one_wide(psgd_plan* plan) {
     // keys that ask for the matrix-core kernels or for their tiles get them
     const bool others = tu.bf16_valu >= 0 || tu.hr_k1_rows != def.hr_k1_rows || tu.hr_k1_cols != def.hr_k1_cols || tu.hr_k3_rows != def.hr_k3_rows;
     if (R != kOneMaxRank || plan->workers != 1 || plan->grad_dtype != PSGD_BF16 || plan->mats.empty() || !tu.one_sweep ||
-        (tu.one_sweep < 0 && (others || !plan->stream_hints)))
+        !tu.stream_hints || (tu.one_sweep < 0 && (others || !plan->stream_hints)))   // its accesses are non-temporal
         return;
     const int64_t osz = plan->out_dtype == PSGD_BF16 ? 2 : 4;
     int64_t total = 0, eight = 0, thin = 0;

@@ -175,6 +175,8 @@ static void check_wide_lines() {
         psgd_plan* plan = make(c.s, 4, 1, PSGD_BF16, PSGD_BF16);
         CHECK(plan->hr && plan->one_wide == c.taken);
         CHECK(psgd_plan_set_tuning(plan, "one_sweep", 1) == PSGD_OK && plan->one_wide);
+        CHECK(psgd_plan_set_tuning(plan, "stream_hints", 0) == PSGD_OK && !plan->one_wide);   // its accesses to M are non-temporal
+        CHECK(psgd_plan_set_tuning(plan, "stream_hints", 1) == PSGD_OK && plan->one_wide);
         psgd_plan_destroy(plan);
     }
 }
