@@ -367,6 +367,8 @@ psgd_status launch_sparse_step(psgd_plan* plan, const void* grad, float* err, co
                                const int64_t* indices, float* vals, void* out, void* stream);
 psgd_status read_trace(psgd_plan* plan, uint64_t* out, int64_t capacity, int64_t* n_written);
 psgd_status resident_check_device(psgd_plan* plan);
+// Every whole step that is not the calls in sequence: the resident kernel; a matrix-core plan's one walk that stores no M (no update, one
+// iteration, buffers that let it); several iterations on the stored mean.  What a plan has none of for this call runs as the calls do.
 psgd_status launch_resident_step(psgd_plan* plan, const void* grad, float* err, float* q, float* p, void* out,
                                  void* workspace, void* stream, const UpdateArgs& upd = UpdateArgs(), int iterations = 1);
 // The resident kernel's synchronisation words (units of unsigned), one 256-byte line each: an error word

@@ -647,7 +647,7 @@ static psgd_status streamed_step(psgd_plan* plan, const void* grad, float* err, 
 
 psgd_status launch_resident_step(psgd_plan* plan, const void* grad, float* err, float* q, float* p, void* out,
                                  void* workspace, void* stream, const UpdateArgs& upd, int iterations) {
-    if (plan->one_wide) return hr_step_wide(plan, grad, err, q, p, out, workspace, stream);   // matrix-core plans come here for psgd_step alone
+    if (plan->one_wide && !upd.mom && iterations == 1) return hr_step_wide(plan, grad, err, q, p, out, workspace, stream);
     if (!plan->uploaded) {
         psgd_status st = upload_tables(plan);
         if (st != PSGD_OK) return st;
