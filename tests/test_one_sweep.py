@@ -310,14 +310,14 @@ def test_matrix_core_step_in_one_walk(out_bf16):
     for t, shape in enumerate(shapes):     # fp64 against fp32 sums of up to 8192 products, times the condition of random panels
         off, p_off, q_off, r = plan.offsets(t)
         n = int(np.prod(shape))
-        pairs = [(a[3][off: off + n], b[3][off: off + n], 2.0 ** -8 if out_bf16 else 2e-5)]
-        if r:
-            pairs += [(a[0][off: off + n], b[0][off: off + n], 2e-5), (a[1][q_off: q_off + shape[1] * r], b[1][q_off: q_off + shape[1] * r], 2e-5),
-                      (a[2][p_off: p_off + shape[0] * r], b[2][p_off: p_off + shape[0] * r], 2e-5)]
+        pairs = [(a[3][off: off + n], b[3][off: off + n], 2.0 ** -8 if out_bf16 else 2e-5, 0.0)]
         scale = float(a[0].norm() / a[0].numel() ** 0.5) * n ** 0.5   # full-rank matrices leave an error memory of roundings
-        for x, y, tol in pairs:
+        if r:
+            pairs += [(a[0][off: off + n], b[0][off: off + n], 2e-5, scale), (a[1][q_off: q_off + shape[1] * r], b[1][q_off: q_off + shape[1] * r], 2e-5, 0.0),
+                      (a[2][p_off: p_off + shape[0] * r], b[2][p_off: p_off + shape[0] * r], 2e-5, 0.0)]
+        for x, y, tol, floor in pairs:
             x, y = x.float(), y.float()
-            assert torch.isfinite(x).all() and float((x - y).norm()) <= tol * max(float(y.norm()), scale), (t, shape)
+            assert torch.isfinite(x).all() and float((x - y).norm()) <= tol * max(float(y.norm()), floor), (t, shape)
     off = torch.full((s.out_elems + 8,), 3.0, dtype=odt, device=dev)[2 if out_bf16 else 1:][: s.out_elems]
     for x, y in zip(run("step", off), b):
         assert torch.equal(x, y)           # out not aligned to 16 bytes
