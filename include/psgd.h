@@ -148,19 +148,25 @@ PSGD_API psgd_status psgd_plan_offsets(const psgd_plan* plan, int32_t tensor, in
  *   stream_hints  cache policy of the second and third sweep: -1 (default) by the size of M over all
  *                 workers (non-temporal accesses to M and the error memory above 320 MB; below it, one worker,
  *                 to the momentum and parameters of the fused update where the three together exceed 320 MB),
- *                 0 never, 1 always (M and the error memory)
+ *                 0 never, 1 always (M and the error memory).  Resident plans, psgd_step_update: -1 non-temporal accesses to momentum and
+ *                 parameters from 4,000,000 elements on (behind other work 2 to 9 % faster than 0; a step repeated on one state with
+ *                 nothing in between 3 to 8 % slower), 0 and 1 ordinary ones
  *   gram_fused    orthogonalisation over row blocks: -1 (default) or 1 Gram matrices and factorisation in one launch where the
  *                 device holds all row blocks of the launch at once, 0 in two launches, 2 (TEST ONLY) in one
  *                 launch unconditionally: its waits may then time out, see psgd_plan_check
  *   gram_spin     polls before a wait in that launch gives up, 1 .. 2^24 (default 2^18)
  *   one_sweep     streaming kernels, rank <= 4, where gram_fused holds: P = M Q and Q = M^T P_hat in one walk over M instead of
  *                 two (psgd_plan_one_sweep); -1 (default) wherever every row fits one workgroup's registers (6144 elements, 4096
- *                 with several workers, 3072 of even and 4096 of odd lengths) and the partial sums 64 MiB, unless another key asks
- *                 for kernels of the two walks (k1_*, k3_*, ortho_rows, worker_mean, gram_fused = 0, 1 or 2), 0 never, 1 also then.
+ *                 with several workers, 3072 of even and 4096 of odd lengths) and the partial sums 64 MiB, unless the planner expects two
+ *                 walks to be faster or another key asks for their kernels (k1_*, k3_*, ortho_rows, worker_mean, gram_fused = 0, 1 or
+ *                 2), 0 never, 1 also then.
  *                 Matrix-core kernels at rank 4, one worker, bf16 gradients, M above 320 MB and rows of at most 8192 elements: psgd_step
- *                 the same way unless bf16_valu or an hr_* key is set (1: also then and on smaller sets)
+ *                 the same way unless bf16_valu, hr_k1_* or hr_k3_rows is set or more than half of the elements are in rows above
+ *                 4096 or under 256 (1: also then and on smaller sets).  Never with stream_hints = 0, nor where a matrix has fewer
+ *                 rows than eight bytes a rank column need of its part of out (16 with bf16 out, 8 with fp32): the whole set then
+ *                 keeps the three walks
  *   worker_mean   streaming kernels, where gram_fused holds: products of the mean over the workers' M instead of each
- *                 worker's own; -1 (default) from four workers and 2^20 elements on (2^16 per worker above sixteen workers) when
+ *                 worker's own (the one walk always takes those of the mean); -1 (default) on sets that the one walk does not take, from four workers and 2^20 elements on (2^16 per worker above sixteen workers) when
  *                 the rows of 15 in 16 elements are multiples of 4, 0 never, 1 with any two workers
  *   ortho_rows    panels of at most this many rows (0 .. 1024) are orthogonalised by one workgroup with modified
  *                 Gram-Schmidt in LDS instead of Cholesky-QR over row blocks; default 0: none

@@ -90,8 +90,12 @@ constexpr int kResCUs = 256;         // MI355X compute units: the planner's prov
 constexpr int kResBlocksPerCU = 2;   // 256-thread workgroups per compute unit (8 wavefronts, 2 per SIMD)
 // Resident step fused with the update: from this many elements on momentum and parameters go around the caches (stream_hints < 0).
 // Four states of a set in turn, us, ordinary / around: ResNet18-shaped, 11.2 M elements, rank 2 / 4 70.4 / 80.8 and 62.7 / 72.5; 6.3 M,
-// rank 1 45.9 and 39.4; 3.9 M, rank 2 32.1 and 34.9; 2.8 M, rank 4 34.5 and 36.8; five matrices 15.9 and 16.8.  One state alone over and over,
-// which the memory-side cache then holds, loses by it above the line: 11.2 M 58.4 / 67.1 and 62.7 / 72.8, 6.3 M 35.8 and 38.7.
+// rank 1 45.9 and 39.4; 3.9 M, rank 2 32.1 and 34.9; 2.8 M, rank 4 34.5 and 36.8; five matrices 15.9 and 16.8.  What else runs between the steps
+// decides on either side of the line.  One state behind 512 MB of other work: 11.2 M, rank 1 / 2 / 4 68.8 / 73.0 / 85.9 and 67.3 / 71.7 / 83.2, 6.3 M 46.6 / 49.7 / 60.2 and
+// 44.7 / 46.8 / 57.7, 3.9 M 41.5 / 42.0 / 52.8 and 38.8 / 40.2 / 48.4, 2.1 M 35.5 / 36.6 / 41.2 and 32.9 / 34.2 / 39.8, 0.7 M 25.4 / 26.7 / 31.2 and 24.8 / 26.1 / 30.4; with nothing in between, where the
+// memory-side cache holds it: 11.2 M 58.0 / 61.3 / 70.5 and 61.8 / 65.2 / 75.5, 6.3 M 39.3 / 42.4 / 52.1 and 41.6 / 45.4 / 55.0, 3.9 M 31.8 / 35.2 / 43.8 and 33.0 / 37.3 / 46.4, 2.1 M 24.3 / 28.0 / 37.3 and
+// 24.6 / 28.8 / 38.6; behind 96 MB, rank 2, 11.2 M 66.1 / 63.9, 8.5 M 51.3 / 54.2, 3.9 M 34.9 / 36.8, 0.7 M 20.8 / 21.2.  Small sets go with small networks and little
+// other work, large ones with much, so the line stays between them.
 constexpr int64_t kResAroundElems = 4000000;
 constexpr int kResTracePoints = 16;  // diagnostic timestamps per workgroup of the resident kernel
 

@@ -501,7 +501,7 @@ __global__ __launch_bounds__(kBlock) void k_solve(const OneMat* __restrict__ mat
         G[tid] = v;
     }
     __syncthreads();
-    if (tid == kBlock - 1) {   // the factor, by one thread whose wavefront sums no columns below
+    if (tid == kBlock - 1) {   // the factor, by one thread (whose wavefront sums no columns below where several slices share one)
         double g[R][R], inv[R];
 #pragma unroll
         for (int a = 0; a < R; ++a)
