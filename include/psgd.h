@@ -330,7 +330,7 @@ PSGD_API psgd_status psgd_plan_kept(const psgd_plan* plan, int32_t tensor, int64
  * psgd_plan_kernel_times copies the accumulated milliseconds per kernel (array
  * of PSGD_N_KERNELS doubles, order given by psgd_kernel_name) and the number of
  * accumulated steps, then clears the accumulators.  Where psgd_plan_one_sweep
- * holds, the first entry is the one walk and the second k_solve.  A plan in resident mode
+ * holds, the first entry is the one walk and the second k_solve (several iterations over the stored mean: the kernels of the two walks).  A plan in resident mode
  * (see psgd_step) runs one kernel per step, index PSGD_KERNEL_RESIDENT; the
  * baseline steps (psgd_random_block_step, psgd_random_k_step) fill the last two
  * entries and wait for the stream at their end like psgd_decompress. */

@@ -33,7 +33,7 @@ constexpr int kOrthoMaxRows = 1024; // largest value of the tuning key ortho_row
 // workers is too long (32 workers: 1.1 M elements 287 / 293 and 149 / 158, 2.0 M 255 / 278, but 2.1 M 471 / 457, 2.8 M 487 / 416).  Three
 // workers (ResNet18-shaped 168 / 157, with the update 198 / 193) and sets below 2^20 elements (0.7 M, 4 workers 38.7 / 35.8; five matrices,
 // 16 workers 36.5 / 36.9) have not been measured over a range, and stay with each worker by itself.  Sets that build_one_sweep
-// takes (rank <= 4, rows that fit a workgroup) are walked once instead: the line holds above that rank and for longer rows.
+// takes (rank <= 4, rows that fit a workgroup, one_sweep_pays) are walked once instead: the line holds for the others.
 constexpr int kMeanWorkers = 4;
 constexpr int64_t kMeanElems = int64_t(1) << 20;
 constexpr int64_t kMeanElemsPerWorker = int64_t(1) << 16;
